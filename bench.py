@@ -222,10 +222,8 @@ def work_model(kernel, results, dims, solves):
                    (8 nnz) and their products (8 rs)
     k_cg_pass_b    the same words (bit-transposed) + u (8 (kr - rs)) + the product (8 M),
                    and the player-major lists (4 nnz + 8 (M + 1)), the entries of u
-                   they select (8 nnz) and their products (8 M)
-    k_cg_rows      the pass-A partial products of the bit rows (8 npc (kr - rs), npc
-                   taken as ceil(ceil(M/64) / 16)) and u written (8 (kr - rs))
-    k_cg_update    five fp64 vectors of M read (R^T u, r, p, s, x) and four written
+                   they select (8 nnz) and their products (8 M); the vector steps (four
+                   fp64 vectors of M read and written)
     k_solve_mid / k_solve_one_batch (one-workgroup solves)
                    M^3/6 (Cholesky) + 2 M^2 (two triangular solves) MACs, 2 flop each
     k_gram         K_R M(M+1)/2 pair counts over the random rows, 1 popcount-AND
@@ -245,12 +243,7 @@ def work_model(kernel, results, dims, solves):
             if base == "k_cg_pass_a":
                 tot += iters * (bits + 12.0 * nnz + 16.0 * rs + 8.0)
             elif base == "k_cg_pass_b":
-                tot += iters * (bits + 12.0 * nnz + 16.0 * M + 8.0)
-            elif base == "k_cg_rows":
-                npc = -(-wpr // 16)
-                tot += iters * 8.0 * (npc + 1) * (kr - rs)
-            elif base == "k_cg_update":
-                tot += iters * 72.0 * M
+                tot += iters * (bits + 12.0 * nnz + 80.0 * M + 8.0)
         return tot, "GB/s", "hbm", HBM_PEAK_GBS
     tot = 0.0
     for r in results:
@@ -287,9 +280,9 @@ def work_model(kernel, results, dims, solves):
 
 
 CANDIDATES = {
-    "batch": ["k_cg_pass_a", "k_cg_pass_b", "k_cg_rows", "k_cg_update", "k_wide_l1", "k_eval_rows_mx_batch", "k_eval_rows_batch",
+    "batch": ["k_cg_pass_a", "k_cg_pass_b", "k_wide_l1", "k_eval_rows_mx_batch", "k_eval_rows_batch",
               "k_solve_one_batch", "k_eval_l2_batch", "k_gram_batch", "k_rhs_tile_batch", "k_sample"],
-    "streams": ["k_cg_pass_a", "k_cg_pass_b", "k_cg_rows", "k_cg_update", "k_wide_l1", "k_solve_mid", "k_eval_rows_mx", "k_eval_l2",
+    "streams": ["k_cg_pass_a", "k_cg_pass_b", "k_wide_l1", "k_solve_mid", "k_eval_rows_mx", "k_eval_l2",
                 "k_rhs_tile", "k_gram", "k_sample"],
 }
 

@@ -20,26 +20,25 @@ struct CgState {
 // Buffers of the iterative solver, carved from the solve workspace.
 struct CgWs {
   double* x;       // M: psi
-  double* r;       // words_per_row * 64: residual, zero beyond M
+  double* r;       // M + 1: residual, then a zero
   double* p;       // M: search direction
   double* s;       // M: A p
-  double* upart;   // npc x kr: partial products R r per player chunk
-  double* u;       // nrb * 64: R r, zero beyond kr
-  double* qpart;   // nrc x M: partial products R^T u per row chunk
-  double* uu;      // nbu x 2: partial |u|^2 and |m|.u
-  double* usp;     // nsa x 2: the same over the sparse rows, per pass-A workgroup
-  double* rr;      // 3 x nbc: partial r.r of iterations t mod 3
+  double* us;      // rs: R r of the sparse rows
+  char* rdig;      // digits of r, MFMA operands over the players
+  char* udig;      // digits of R r of the bit rows, MFMA operands over these rows
+  double* uu;      // (2 nbits + rbd0) x 2: partial |u|^2 and |m|.u
+  double* rr;      // 3 x 2 words_per_row: partial r.r of iterations t mod 3
+  double* mx;      // 2 x 2 x 2 words_per_row: largest |r| and |s|, by iteration parity
   double* hist;    // 2: step lengths of even and odd iterations
+  int32_t* ex;     // 3: fixed-point exponents of r (even and odd iterations) and u
   int32_t* sz;     // kr: sizes of the random representative rows
   uint64_t* blocked;  // nrb x words_per_row x 64: the random rows in row blocks
   CgState* st;
   // sparse rows (random rows [0, rs), the smallest coalitions): their players
-  int64_t* csr_ptr;   // rs + 1: players of each sparse row, ascending
-  int32_t* csr_idx;   // nnz
+  int64_t* ell_ptr;   // rbd0 + 1: entries per row of the blocks of 64 sparse rows before each
+  int32_t* ell_idx;   // nell: players of the sparse rows, ascending, padded with M; entry i of a block's rows contiguous
   int64_t* csc_ptr;   // M + 1: rows of each player, ascending
   int32_t* csc_row;   // nnz
-  double* qs;         // M: R_s^T u
-  int64_t* sitem;     // nsi: pass-A work items over the sparse rows, (first row << 8) | log2(lanes per row)
   int32_t* segcnt;    // 8 x max(rs, M): per-segment list lengths while the lists are built
 };
 
@@ -49,14 +48,8 @@ struct CgShape {
   int64_t M, wpr, kr, nrb;
   int64_t rs, nnz;         // sparse rows [0, rs) (whole row blocks), their players
   int64_t rbd0;            // first row block of the bit products (rs / 64)
-  int64_t npc, pwords;     // product R r: player chunks of pwords words
-  int64_t nrc, rbc;        // product R^T u: row chunks of rbc row blocks
-  int64_t nbu, nbc;        // partial sums of the row pass (the sparse rows' total, then one per
-                           // workgroup of bit rows; also its workgroups), workgroups of the player passes
-  int64_t nsa, nsb;        // sparse workgroups of pass A (rows) and pass B (players)
-  int64_t nsi;             // pass A's work items over the sparse rows (64 / lanes-per-row rows each)
-  int32_t lgb;             // pass B: log2 of the lanes per player list (64 / 2^lgb players per wavefront)
-  int64_t nrcd;            // row chunks of pass B's bit rows (0 without bit rows)
+  int64_t nbits;           // row blocks of the bit products
+  int64_t nell;            // padded entries of the sparse rows' lists
 };
 // The split of the random rows [rb0, rb0 + kr) of a class table into sparse
 // rows (coalition size at most M / kSparseDiv, whole blocks of 64 rows) and
@@ -65,7 +58,8 @@ CgShape cg_shape(int64_t M, int64_t wpr, int64_t kr, int64_t rb0, const gnnshap_
 CgWs cg_carve(Carver& c, const CgShape& sh);
 
 // The problem handed over by the solve entry point: the bit-transposed random
-// rows T (nrb x M), the same rows in row blocks (word w of the 64 rows of
+// rows T (word rb of the 64 players of block w contiguous, block after block:
+// T[(w nrb + rb) 64 + j % 64], zero beyond M), the same rows in row blocks (word w of the 64 rows of
 // block rb contiguous, rows beyond kr zero),
 // the summed right-hand side dv (M, before centring) with its per-block sums
 // bsum (nb of them), the class table (device) and the enumerated part alpha.

@@ -15,51 +15,57 @@
 // carry s = A p along: with w = A r, gamma = r.r and delta = r.w,
 //     beta = gamma / gamma_prev, a = gamma / (delta - beta gamma / a_prev),
 //     p = r + beta p, s = w + beta s, x += a p, r -= a s.
-// Every vector a pass reads was finished by an earlier kernel.  Each
-// workgroup turns its slice of that vector into nibble tables in LDS (sums of
-// the vector over every subset of 4 consecutive entries); each lane then
-// loads its own mask word with ordinary vector loads and adds one table entry
-// per 4 bits (a bit extract, an address and an fp64 add per nibble, instead
-// of a multiply-add per bit).  delta needs no extra reduction:
-// r.A r = alpha |r|^2 + 2 w_r |R r|^2 for r in 1-perp.
+// Every vector a pass reads was finished by an earlier kernel.  delta needs no
+// extra reduction: r.A r = alpha |r|^2 + 2 w_r |R r|^2 for r in 1-perp.
+//
+// Products with the bits run on the matrix cores, exactly.  A vector v is
+// held as integers rint(|v_j| 2^e) < 2^62 (e from a bound on |v|, so the
+// largest entries keep all 53 bits of their fp64 value), split into 16
+// base-16 digits with the sign of v_j.  A digit is exact in fp6 (e2m3 holds
+// 0..15 eighths), a mask bit left in place in its nibble is an fp4 number
+// (0001 = 0.5, 0010 = 1.0; e2m1), so v_mfma_f32_16x16x128_f8f6f4 contracts
+// 16 bit rows x 128 entries with the 16 digits in one instruction: every
+// product is a whole number of eighths and every sum stays below 2^24 of
+// them, so fp32 accumulation loses nothing (segments of kSegGroups groups
+// keep it so for any number of rows).  The digit sums are combined in fp64.
+// What rounds is the integer (2^-62 of the bound, which is within a factor
+// of 2^10 of the largest entry) and the last 16-term fp64 combination, less
+// than the thousands of fp64 additions of a direct sum; and the result does
+// not depend on how the work is split over wavefronts.
 //
 // Rows of small coalitions are mostly zero bits: the random rows whose size
 // is at most M / kSparseDiv (the first ones: the plan orders random classes
 // by ascending size), in whole blocks of 64 rows, are kept as lists of their
-// players instead (sparse rows), built once per solve from the bits, row by
-// row and player by player (both in ascending order).  In pass A a group of
-// L lanes sums one row's list (each lane at most about four entries, then a
-// fixed butterfly over the group), L fixed per block of 64 rows from the
-// block's largest row, so a wavefront takes 64 / L rows at once; in pass B
-// groups of lanes sized from the mean list length sum the players' lists.
+// players instead (sparse rows), built once per solve from the bits: for pass
+// A padded to the largest row of their block (its rows' sizes are nearly
+// equal), entry i of the 64 rows contiguous, so a workgroup reads a block's
+// lists and the entries of r they name without following pointers; for pass
+// B by player, in ascending row order, eight lanes summing one player's list.
 //
-// Per iteration t:
-//   pass A   stopping test on gamma_t; partial products R r of the bit rows
-//            over player chunks (lane = row, the rows' words in row blocks)
-//            and, in workgroups of their own in the same launch, u = R r of
-//            the sparse rows (a wavefront sums r over a row's players);
-//   rows     u of the bit rows (the sum of their chunks); partial |u|^2, |m|.u;
-//   pass B   partial products R^T u of the bit rows over row chunks (lane =
-//            player, words of the bit-transposed rows) and, in workgroups of
-//            their own, the sparse rows' R_s^T u (a wavefront per player);
-//   update   w = alpha r + 2 w_r (R^T u - mean), the scalars, the vector steps
-//            and the partial sums of the new gamma.
-// Vectors and every sum are fp64; partial sums are reduced in a fixed order,
-// so repeated solves give the same bits.  The iteration stops when
+// Per iteration t, two launches:
+//   pass A   stopping test on gamma_t; u = R r of the bit rows (a workgroup
+//            per 64 rows, its wavefronts sharing the players), the digits of
+//            u, partial |u|^2 and |m|.u; in workgroups of their own the same
+//            for the sparse rows (u itself, no digits);
+//   pass B   a workgroup per 64 players, its wavefronts sharing the bit rows:
+//            R^T u plus the sparse rows' R_s^T u, then w = alpha r +
+//            2 w_r (R^T u - mean), the scalars, the vector steps of these
+//            players, the digits of the new r and the partial sums of the
+//            new gamma.
+// Vectors and sums of products are fp64; partial sums are kept per 64 rows
+// or players and reduced in a fixed order, so repeated solves give the same
+// bits, alone or in a group.  The iteration stops when
 // |r| <= kTol |r_0| or after kMaxIt iterations; the host queues iterations in
 // chunks and checks a flag the device writes to mapped host memory, so at
 // most one chunk runs idle.
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <vector>
 
 #include "cg.h"
-#include "nibble.h"
 
 namespace {
-
-using gnnshap::build_tables;
-using gnnshap::nibble_dots;
 
 // Relative residual at which the iteration stops.  On the Reddit-shaped
 // targets (10,793-30,000 players, 100,000 coalitions) phi then differs from
@@ -69,42 +75,37 @@ using gnnshap::nibble_dots;
 constexpr double kTol = 1e-6;
 constexpr int64_t kMaxIt = 4000;
 constexpr int64_t kChunk = 8;        // iterations queued between stopping checks
-constexpr int kWaves = 16;           // waves per workgroup of both passes
-constexpr int kTabA = 32;            // pass A: words of r's tables per workgroup (64 KiB of LDS)
-constexpr int kTabB = 32;            // pass B: row blocks of u's tables per workgroup
-constexpr int kPerWaveGroup = 2;     // row blocks (pass A) and player words (pass B) per wavefront
-                                     // in a group of several systems; one for a system alone
-constexpr int64_t kFill = 4096;      // (row block, chunk) pairs of a pass per system, at least
+constexpr int kWaves = 8;            // waves per workgroup of both passes
+constexpr int kThreads = kWaves * 64;
+constexpr int kSegGroups = 4096;     // K groups (256 entries) a wavefront accumulates in fp32: 2^20 x 15 < 2^24
 constexpr int64_t kSparseDiv = 128;   // sparse rows: coalition size at most M / kSparseDiv
+constexpr int kFixedBits = 62;        // |fixed-point entries| stay below 2^62
+constexpr uint64_t kSign = uint64_t(1) << 63;
 
 struct Args {
-  const uint64_t* blocked;   // the bit rows in row blocks (pass A)
-  const uint64_t* T;         // the bit rows transposed (pass B)
+  const uint64_t* blocked;   // the random rows in row blocks (pass A)
+  const uint64_t* T;         // the random rows transposed (pass B)
   const int32_t* sz;
-  int64_t M, wpr, kr, nrb, npc, pwords, nrc, rbc, nbu, nbc;
-  int64_t rs, rbd0, nsa, nsb, nrcd, nxa, nxb, nsi;
-  int32_t pw;                // row blocks / player words per wavefront of the two passes (their grids)
-  int32_t lgb;     // pass B: log2 of the lanes summing one player's list
-  const int64_t* sitem;
-  const int64_t* csr_ptr;
-  const int32_t* csr_idx;
+  int64_t M, wpr, kr, nrb;
+  int64_t rs, rbd0, nbits;   // sparse rows, their blocks (the first bit block), bit blocks
+  const int64_t* ell_ptr;
+  const int32_t* ell_idx;
   const int64_t* csc_ptr;
   const int32_t* csc_row;
-  double* qs;
   double alpha, wr2, tol2;
   int64_t maxit;
-  int32_t has_random;
   double* x;
-  double* r;       // wpr * 64 (zero beyond M)
+  double* r;       // M + 1 (r[M] = 0: the lists' padding)
   double* p;
   double* s;
-  double* upart;
-  double* u;       // nrb * 64 (zero beyond kr)
-  double* qpart;
-  double* uu;
-  double* usp;     // 2 x nsa: pass A's sparse-row partials
-  double* rr;      // 3 x nbc
+  double* us;      // rs: R r of the sparse rows
+  char* rdig;      // digits of r (digit_bytes(wpr))
+  char* udig;      // digits of R r of the bit rows (digit_bytes(nbits))
+  double* uu;      // 2 x (2 nbits + rbd0): partial |u|^2 and |m|.u
+  double* rr;      // 3 x 2 wpr: partial r.r of iterations t mod 3
+  double* mx;      // 2 x 2 x 2 wpr: largest |r| and |s| per 32 players, by iteration parity
   double* hist;    // step length of even and odd iterations
+  int32_t* ex;     // fixed-point exponents: r of even and odd iterations, u
   gnnshap::CgState* st;
   int32_t* host_flag;  // mapped host memory: [0] done, [1] iterations
 };
@@ -127,40 +128,254 @@ __device__ __forceinline__ int member_of(const GroupArgs& g, int64_t& bid) {
   return m;
 }
 
+// v of the lane that DPP control CTRL (within rows of 16 lanes) selects.
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, true));
+}
+
+// Sum over rows of 16 lanes, in every lane: lanes xor 1, xor 2 (quad_perm),
+// then the mirrored half row and the mirrored row, whose sums the earlier
+// steps have made equal within their quads and halves.
+__device__ __forceinline__ double row_sum_d(double v) {
+  v += row_move<0xB1>(v);
+  v += row_move<0x4E>(v);
+  v += row_move<0x141>(v);
+  return v + row_move<0x140>(v);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Sum and maximum over each half wavefront, in its first lane.
+__device__ __forceinline__ double half_sum_d(double v) {
+  v = row_sum_d(v);
+  return v + __shfl_xor(v, 16);
+}
+
+__device__ __forceinline__ double half_max_d(double v) {
+  v = fmax(v, row_move<0xB1>(v));
+  v = fmax(v, row_move<0x4E>(v));
+  v = fmax(v, row_move<0x141>(v));
+  v = fmax(v, row_move<0x140>(v));
+  return fmax(v, __shfl_xor(v, 16));
+}
+
+// Sum and maximum over a wavefront, in every lane.
 __device__ __forceinline__ double wave_sum_d(double v) {
+  v = row_sum_d(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+__device__ __forceinline__ double wave_max_d(double v) {
+  v = fmax(v, row_move<0xB1>(v));
+  v = fmax(v, row_move<0x4E>(v));
+  v = fmax(v, row_move<0x141>(v));
+  v = fmax(v, row_move<0x140>(v));
+  return fmax(fmax(lane_value(v, 0), lane_value(v, 16)), fmax(lane_value(v, 32), lane_value(v, 48)));
+}
+
+// Sum (or maximum) of n values a[stride * i] by one whole wave in a fixed
+// order, sixteen loads in flight; every lane gets the same bits.
+template <bool MAX = false>
+__device__ __forceinline__ double wave_fixed(const double* __restrict__ a, int64_t n, int64_t stride = 1) {
+  const int lane = threadIdx.x & 63;
+  double s = 0.0;
+  for (int64_t i = 0; i < n; i += 1024) {
+    double v[16];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+    for (int q = 0; q < 16; ++q) {
+      const int64_t k = i + 64 * q + lane;
+      v[q] = k < n ? a[k * stride] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) s = MAX ? fmax(s, v[q]) : s + v[q];
+  }
+  return MAX ? wave_max_d(s) : wave_sum_d(s);
 }
 
-// Sum of a block's values v over its threads (blockDim.x a multiple of 64,
-// at most 1024); the result is returned to every thread.
-__device__ __forceinline__ double block_sum_d(double v, double* red) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  v = wave_sum_d(v);
-  __syncthreads();
-  if (lane == 0) red[wv] = v;
-  __syncthreads();
-  double s = 0.0;
-  for (int i = 0; i < nw; ++i) s += red[i];
-  return s;
+// ---- fixed-point vectors and their digits ---------------------------------------------------
+
+// Exponent e with bound * 2^e < 2^kFixedBits, for a finite bound >= every |v_j|.
+__device__ __forceinline__ int fixed_exponent(double bound) {
+  const int lg = static_cast<int>(__double_as_longlong(bound > 1e-270 ? bound : 1e-270) >> 52) - 1023;
+  const int e = kFixedBits - 1 - lg;
+  return e > 960 ? 960 : (e < -900 ? -900 : e);
 }
 
-// Sum of n values by one whole wave in a fixed order: lane l adds entries
-// l, l + 64, ..., then a fixed butterfly; every wave gets the same bits.
-__device__ __forceinline__ double wave_fixed_sum(const double* __restrict__ a, int64_t n, int64_t stride = 1) {
-  double s = 0.0;
-  for (int64_t i = threadIdx.x & 63; i < n; i += 64) s += a[i * stride];
-  return wave_sum_d(s);
+// rint(|v| 2^e) with the sign of v in bit 63.
+__device__ __forceinline__ uint64_t to_fixed(double v, int e) {
+  const double m = __builtin_rint(__builtin_ldexp(__builtin_fabs(v), e));
+  return static_cast<uint64_t>(m < 4.6e18 ? m : 4.6e18) | (v < 0.0 ? kSign : 0);
 }
 
-// r = dv - mean(dv) (zero beyond M), x = p = s = 0, partial gamma_0; u zero
-// beyond kr; sizes of the random rows.  Grid: nbc workgroups of 256.
+// A digit array holds, for every group of 256 entries (four 64-entry blocks)
+// and half h of its blocks (a unit: 32 entries), one MFMA operand: lane g * 16 + d has digit d of
+// the 32 entries h of block g as 32 fp6 numbers (24 bytes), the first 16
+// bytes of the 64 lanes first, then their last 8.  Operand element 8 t + i is
+// entry 4 i + t of the 32: the order in which the bits of a 32-bit mask word,
+// taken as w & 0x11111111, w & 0x22222222 and the same of w >> 2, fill an fp4
+// operand.  Bits taken as 0001 weigh 0.5, as 0010 1.0, so their digits are
+// stored as quarters and eighths: every product is an eighth.
+constexpr int64_t kOperand = 1536;
+constexpr int64_t digit_bytes(int64_t nblocks) { return (nblocks + 3) / 4 * 2 * kOperand; }
+
+// Thread (d, t) = (q / 4 % 16, q % 4), q < 64: the eight elements 8 t .. 8 t +
+// 7 (48 bits) of digit d of unit `u` (half u % 2 of block u / 2) from its 32
+// fixed-point entries.
+__device__ __forceinline__ void store_digits(const uint64_t* fixed, int q, int64_t u, char* dig) {
+  const int t = q & 3, d = q >> 2;
+  uint64_t bits = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const uint64_t v = fixed[4 * i + t];
+    const uint32_t n = static_cast<uint32_t>((v & ~kSign) >> (4 * d)) & 15u;
+    const uint32_t mag = (t & 1) ? n : n + (n < 8u ? n : 8u);   // e2m3 codes of n / 8 and n / 4
+    bits |= static_cast<uint64_t>(mag | static_cast<uint32_t>(v >> 63) << 5) << (6 * i);
+  }
+  char* op = dig + ((u >> 3) * 2 + (u & 1)) * kOperand;
+  const int lane = static_cast<int>((u >> 1) & 3) * 16 + d;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int hw = 3 * t + k;   // halfword of the lane's 24 bytes
+    char* at = hw < 8 ? op + lane * 16 + 2 * hw : op + 1024 + lane * 8 + 2 * (hw - 8);
+    *reinterpret_cast<uint16_t*>(at) = static_cast<uint16_t>(bits >> (16 * k));
+  }
+}
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// The digit operand of half h of group q.
+__device__ __forceinline__ v8i load_operand(const char* __restrict__ dig, int q, int h) {
+  const char* op = dig + (static_cast<int64_t>(q) * 2 + h) * kOperand;
+  const int lane = threadIdx.x & 63;
+  const v4i lo = *reinterpret_cast<const v4i*>(op + lane * 16);
+  const v2i hi = *reinterpret_cast<const v2i*>(op + 1024 + lane * 8);
+  return v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
+}
+
+// acc += the bits of 32-bit mask words m times the digit operand b.
+__device__ __forceinline__ v4f mma_half(uint32_t m, v8i b, v4f acc) {
+  const uint32_t m2 = m >> 2;
+  const v8i a = {static_cast<int>(m & 0x11111111u), static_cast<int>(m & 0x22222222u),
+                 static_cast<int>(m2 & 0x11111111u), static_cast<int>(m2 & 0x22222222u), 0, 0, 0, 0};
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, acc, 4, 2, 0, 0, 0, 0);
+}
+
+// A workgroup's product of 16 TW bit rows (or players' columns) with the
+// digits in dig, over nk 64-entry blocks: TW tiles of 16, tile t's words of
+// block k at src[base[t] + 64 k + lane % 16].  Its wavefronts take groups of
+// four blocks in turn; block g of a group is read by lanes 16 g .. (beyond nk
+// the last one, whose digits are zero).
+template <int TW>
+struct BitProducts {
+  // the registers of one group: words of the tiles, digits of both halves
+  struct Stage {
+    uint64_t w[TW];
+    v8i b0, b1;
+  };
+  const char* src[TW];
+  const char* dig;
+  int nk;
+  Stage s;   // the next group
+
+  // Tiles t0 .. t0 + TW - 1 (beyond nt the last one, whose results are not
+  // used) of `words`: blocks of four tiles, `len` 64-word blocks of entries
+  // each, of which `first` .. first + nkb - 1 are multiplied.
+  __device__ __forceinline__ void set(const uint64_t* words, int64_t first, int64_t t0, int64_t nt, int64_t len,
+                                      int64_t nkb, const char* digits) {
+    nk = static_cast<int>(nkb);
+    dig = digits;
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      const int64_t g = t0 + t < nt ? t0 + t : nt - 1;
+      src[t] = reinterpret_cast<const char*>(words + ((g >> 2) * len + first) * 64 + (g & 3) * 16);
+    }
+  }
+
+  __device__ __forceinline__ void load(int q) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t at = static_cast<uint32_t>(min(4 * q + (lane >> 4), nk - 1)) * 512u + (lane & 15) * 8u;
+#pragma unroll
+    for (int t = 0; t < TW; ++t) s.w[t] = *reinterpret_cast<const uint64_t*>(src[t] + at);
+    s.b0 = load_operand(dig, q, 0);
+    s.b1 = load_operand(dig, q, 1);
+  }
+
+  __device__ __forceinline__ void multiply(v4f (&a)[TW]) const {
+#pragma unroll
+    for (int t = 0; t < TW; ++t) a[t] = mma_half(static_cast<uint32_t>(s.w[t]), s.b0, a[t]);
+#pragma unroll
+    for (int t = 0; t < TW; ++t) a[t] = mma_half(static_cast<uint32_t>(s.w[t] >> 32), s.b1, a[t]);
+  }
+
+  // this wavefront's first group, so that its loads run under whatever comes before run()
+  __device__ __forceinline__ void start(int wave) { load(min(wave, (nk + 3) / 4 - 1)); }
+
+  // row[c] (wavefronts 0 .. TW - 1): 2^-e times the product of row 16 wave + 4 (lane / 16) + c,
+  // in all 16 lanes of a row of lanes.  The digit sums of the wavefronts are
+  // added (whole eighths) and combined in fp64.  buf: kWaves * TW * 256 floats.
+  // Every thread calls it; it ends behind a barrier that covers all LDS
+  // writes before it.
+  __device__ __forceinline__ void run(int wave, int e, float* buf, double (&row)[4]) {
+    const int lane = threadIdx.x & 63;
+    const int nq = (nk + 3) / 4;
+    row[0] = row[1] = row[2] = row[3] = 0.0;
+    for (int seg = 0; seg < nq; seg += kSegGroups * kWaves) {
+      const int end = min(seg + kSegGroups * kWaves, nq);
+      v4f a[TW] = {};
+      int q = seg + wave;
+      if (seg > 0) load(min(q, end - 1));
+      // one group in registers: the next one is loaded into them as soon as
+      // they are multiplied, and the other wavefronts of the CU (three
+      // workgroups fit) multiply meanwhile; two groups in flight with half
+      // the workgroups per CU measured the same
+      for (; q < end; q += kWaves) {
+        multiply(a);
+        __builtin_amdgcn_sched_barrier(0);
+        load(min(q + kWaves, end - 1));
+      }
+      if (seg > 0) __syncthreads();
+      v4f* out = reinterpret_cast<v4f*>(buf) + wave * TW * 64 + lane;
+#pragma unroll
+      for (int t = 0; t < TW; ++t) out[64 * t] = a[t];
+      __syncthreads();
+      if (wave < TW) {
+        const v4f* in = reinterpret_cast<const v4f*>(buf) + wave * 64 + lane;
+        v4f sum = in[0];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) sum += in[w * TW * 64];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) row[c] += static_cast<double>(sum[c]);
+      }
+    }
+    // lane 16 g + d holds digit d: times 16^d (and 8: the sums are in eighths), then over the digits
+    const double weight = __longlong_as_double(static_cast<long long>(1023 + 4 * (lane & 15) + 3) << 52);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) row[c] = __builtin_ldexp(row_sum_d(row[c] * weight), -e);
+  }
+};
+
+// The value of lane 16 g + d, d < 4: row[d].
+__device__ __forceinline__ double pick_row(const double (&row)[4], int lane) {
+  const double lo = (lane & 1) ? row[1] : row[0], hi = (lane & 1) ? row[3] : row[2];
+  return (lane & 2) ? hi : lo;
+}
+
+// r = dv - mean(dv), x = p = s = 0, partial gamma_0 and largest |r| per 32
+// players; digit arrays cleared; sizes of the random rows.
+// Grid: ceil(wpr / 4) workgroups of 256.
 __global__ void __launch_bounds__(256) k_cg_init(Args a, const double* __restrict__ dv,
                                                  const double* __restrict__ bsum, int64_t nb,
                                                  const gnnshap_class* __restrict__ cls, int64_t ncls, int64_t rb0,
                                                  int32_t* sz) {
-  __shared__ double red[4];
   __shared__ double mean;
   if (threadIdx.x == 0) {
     double sm = 0.0;
@@ -169,26 +384,29 @@ __global__ void __launch_bounds__(256) k_cg_init(Args a, const double* __restric
   }
   __syncthreads();
   const int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  double r2 = 0.0;
-  if (j < a.wpr * 64) {
-    const double rj = j < a.M ? dv[j] - mean : 0.0;
+  const double rj = j < a.M ? dv[j] - mean : 0.0;
+  if (j < a.M) {
     a.r[j] = rj;
-    r2 = rj * rj;
-    if (j < a.M) {
-      a.x[j] = 0.0;
-      a.p[j] = 0.0;
-      a.s[j] = 0.0;
-    }
+    a.x[j] = 0.0;
+    a.p[j] = 0.0;
+    a.s[j] = 0.0;
   }
-  const double sb = block_sum_d(r2, red);
-  if (threadIdx.x == 0) a.rr[blockIdx.x] = sb;   // gamma_0: slot 0
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  const double r2 = half_sum_d(rj * rj), rm = half_max_d(__builtin_fabs(rj));
+  if ((threadIdx.x & 31) == 0 && j < a.wpr * 64) {
+    a.rr[j / 32] = r2;   // gamma_0: slot 0
+    a.mx[j / 32] = rm;
+    a.mx[2 * a.wpr + j / 32] = 0.0;
+  }
+  if (j == 0) {
+    a.r[a.M] = 0.0;
     a.st->done = 0;
     a.st->iters = 0;
     a.st->status = 0;
   }
   const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
-  for (int64_t b = a.kr + j; b < a.nrb * 64; b += stride) a.u[b] = 0.0;
+  const uint4 zero = {0, 0, 0, 0};
+  for (int64_t i = j; i < digit_bytes(a.wpr) / 16; i += stride) reinterpret_cast<uint4*>(a.rdig)[i] = zero;
+  for (int64_t i = j; i < digit_bytes(a.nbits) / 16; i += stride) reinterpret_cast<uint4*>(a.udig)[i] = zero;
   // row sizes: class of row rb0 + b by binary search over row_begin
   for (int64_t b = j; b < a.kr; b += stride) {
     const int64_t row = rb0 + b;
@@ -201,316 +419,313 @@ __global__ void __launch_bounds__(256) k_cg_init(Args a, const double* __restric
   }
 }
 
-// Lanes per sparse row (as log2) for a block of 64 rows whose largest row
-// has c players: the power of two that gives each lane at most about four
-// entries, at most 64.  Host and device use the same rule.
-__host__ __device__ __forceinline__ int sparse_lanes_log2(int64_t c) {
-  const int64_t need = (c + 3) / 4;
-  int lg = 0;
-  while (lg < 6 && (int64_t(1) << lg) < need) ++lg;
-  return lg;
+// The digits of r_0, one workgroup per 64 players.
+__global__ void __launch_bounds__(128) k_cg_digits(Args a) {
+  __shared__ uint64_t fixed[64];
+  const int64_t w = blockIdx.x, j = w * 64 + threadIdx.x;
+  const int e = fixed_exponent(wave_fixed<true>(a.mx, 2 * a.wpr));
+  if (threadIdx.x < 64) fixed[threadIdx.x] = to_fixed(j < a.M ? a.r[j] : 0.0, e);
+  __syncthreads();
+  store_digits(fixed + 32 * (threadIdx.x >> 6), threadIdx.x & 63, 2 * w + (threadIdx.x >> 6), a.rdig);
+  if (w == 0 && threadIdx.x == 0) a.ex[0] = e;
 }
 
-// Stopping test of iteration t, taken identically by every wave of pass A
-// from the partial sums of gamma_t; `writer` records the stop.
-__device__ __forceinline__ bool cg_stop(const Args& a, int64_t t, bool writer) {
-  const double g = wave_fixed_sum(a.rr + (t % 3) * a.nbc, a.nbc);
+// Stopping test of iteration t on g = gamma_t, by one thread; records the stop.
+__device__ __forceinline__ void cg_stop(const Args& a, int64_t t, double g) {
   const double g0 = t == 0 ? g : a.st->rr0;
   const bool bad = !(g == g) || g > 1e300;
   const bool conv = !bad && g <= a.tol2 * g0;
   if (conv || bad || t >= a.maxit) {
-    if (writer) {
-      a.st->done = 1;
-      a.st->iters = static_cast<int32_t>(t);
-      a.st->status = conv ? 0 : (bad ? 2 : 1);
-      __hip_atomic_store(a.host_flag + 1, static_cast<int32_t>(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      __hip_atomic_store(a.host_flag, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-    return true;
+    a.st->done = 1;
+    a.st->iters = static_cast<int32_t>(t);
+    a.st->status = conv ? 0 : (bad ? 2 : 1);
+    __hip_atomic_store(a.host_flag + 1, static_cast<int32_t>(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(a.host_flag, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  } else if (t == 0) {
+    a.st->rr0 = g;
   }
-  if (t == 0 && writer) a.st->rr0 = g;
-  return false;
 }
 
-// Sum of the entries of v selected by n indices, by one wavefront: lane l
-// takes indices l, l + 64, ... four at a time (their loads issued together),
-// then a fixed butterfly; every lane gets the same bits.
-__device__ __forceinline__ double wave_gather_sum(const int32_t* __restrict__ idx, int64_t n,
-                                                  const double* __restrict__ v) {
-  const int lane = threadIdx.x & 63;
-  double s4[4] = {0.0, 0.0, 0.0, 0.0};
-  int64_t e = lane;
-  for (; e + 192 < n; e += 256) {
-    const int32_t j0 = idx[e], j1 = idx[e + 64], j2 = idx[e + 128], j3 = idx[e + 192];
-    s4[0] += v[j0];
-    s4[1] += v[j1];
-    s4[2] += v[j2];
-    s4[3] += v[j3];
-  }
-  for (int q = 0; e < n; e += 64, ++q) s4[q] += v[idx[e]];
-  return wave_sum_d((s4[0] + s4[1]) + (s4[2] + s4[3]));
-}
-
-// Pass A.  Workgroup y * nxa + x (y < npc): upart[y, b] = sum over the words
-// of player chunk y of the bits of bit row b times r; the workgroup builds
-// the chunk's nibble tables of r in LDS (r is padded with zeros to whole
-// words), then each wave takes PW blocks of 64 rows (lane = row),
-// reads their row-blocked words, 512 contiguous bytes per word, and sums
-// table entries.  Workgroup
-// nxa * npc + x (x < nsa): the sparse rows x * kWaves + wave, + nsa * kWaves,
-// ...: u_b = sum of r over the row's players, with the workgroup's partial
-// |u|^2 and |m|.u in uu[2 x], uu[2 x + 1].  Both kinds take the stopping
-// test first.
-template <int PW>
-__global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))) k_cg_pass_a(GroupArgs g) {
-  __shared__ double tab[kTabA * 256];   // the sparse rows' workgroups: kWaves block sums
+// Tiles of 16 rows (pass A) or players (pass B) per workgroup.  Per group of
+// 256 entries a wavefront loads 512 bytes of bits per tile and 3 KiB of
+// digits, through a path of 64 bytes per clock and CU that bounds the loop:
+// more tiles use each digit operand more often, fewer give more workgroups.
+// The launch takes the number (4 or 6) that leaves the busiest CU the least
+// to load (18,001 players, pass B: 4 tiles are 282 workgroups, two on 26 of
+// the 256 CUs; 6 tiles 188).  2 tiles were slower throughout, 8 need more
+// registers than three workgroups per CU leave.  The results do not depend on it.
+// Pass A.  Workgroup x < nxa: u = R r of bit rows 16 TW x .., the digits of
+// their u, partial |u|^2 and |m|.u per 32 rows; workgroup 0 also takes the
+// stopping test (the others' results are not read after a stop).  Workgroup
+// nxa + x: u_b of the 64 sparse rows of block x, lane = row, the wavefronts
+// sharing the entries of their lists; the block's partial sums.
+template <int TW>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6))) k_cg_pass_a(GroupArgs g) {
+  __shared__ alignas(16) float buf[kWaves * TW * 256];
+  __shared__ uint64_t fixed[16 * TW];
+  __shared__ double red[2 * kWaves];
+  __shared__ double gamma;
   int64_t bid;
   const int m = member_of(g, bid);
   const Args& a = g.a[m];
   const int64_t t = g.t[m];
   if (a.st->done) return;
-  const uint64_t* __restrict__ blocked = a.blocked;
-  const double* __restrict__ r = a.r;
-  double* __restrict__ upart = a.upart;
-  // one flat grid per member: nxa x npc bit-row workgroups, then nsa sparse-row ones
-  const int64_t pc = bid < a.nxa * a.npc ? bid / a.nxa : a.npc;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool writer = bid == 0 && threadIdx.x == 0;
-  if (pc == a.npc) {                  // sparse rows
-    if (cg_stop(a, t, false)) return;
-    const int64_t x = bid - a.nxa * a.npc;
-    double uu = 0.0, su = 0.0;
-    for (int64_t it = x * kWaves + wave; it < a.nsi; it += a.nsa * kWaves) {
-      const int64_t info = a.sitem[it];
-      const int lg = static_cast<int>(info & 0xff);
-      const int64_t b = (info >> 8) + (lane >> lg);   // this lane group's row
-      const int64_t e0 = a.csr_ptr[b], e1 = a.csr_ptr[b + 1];
-      double v;
-      if (lg == 6) {
-        v = wave_gather_sum(a.csr_idx + e0, e1 - e0, r);
-      } else {
-        // at most four entries per lane (the block's rows have at most 4 L
-        // players), their loads issued together
-        const int L = 1 << lg;
-        const int64_t e = e0 + (lane & (L - 1));
-        const double v0 = e < e1 ? r[a.csr_idx[e]] : 0.0;
-        const double v1 = e + L < e1 ? r[a.csr_idx[e + L]] : 0.0;
-        const double v2 = e + 2 * L < e1 ? r[a.csr_idx[e + 2 * L]] : 0.0;
-        const double v3 = e + 3 * L < e1 ? r[a.csr_idx[e + 3 * L]] : 0.0;
-        v = (v0 + v1) + (v2 + v3);
-        for (int off = L >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off);
-      }
-      if ((lane & ((1 << lg) - 1)) == 0) {
-        a.u[b] = v;
-        uu += v * v;
-        su += static_cast<double>(a.sz[b]) * v;
-      }
-    }
-    const double s1 = block_sum_d(uu, tab);
-    const double s2 = block_sum_d(su, tab);
-    if (threadIdx.x == 0) {
-      a.usp[2 * x] = s1;
-      a.usp[2 * x + 1] = s2;
-    }
-    return;
-  }
-  // the wavefront's row blocks: rb, rb + kWaves, ... (PW of them)
-  const int64_t rb = a.rbd0 + (bid % a.nxa) * (kWaves * PW) + wave;
-  const int64_t w0 = pc * a.pwords;
-  const int64_t w1 = w0 + a.pwords < a.wpr ? w0 + a.pwords : a.wpr;
-  const int64_t nw = w1 - w0;
-  // the tables do not depend on the stopping test: built first, so that the
-  // test's reads overlap them
-  build_tables(r + w0 * 64, nw * 16, tab);
-  if (cg_stop(a, t, writer)) return;   // the same outcome in every wave
-  __syncthreads();
-#pragma unroll 1
-  for (int q = 0; q < PW; ++q) {
-    const int64_t rq = rb + q * kWaves;
-    if (rq >= a.nrb) break;
-    const uint64_t* src = blocked + (rq * a.wpr + w0) * 64 + lane;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    nibble_dots<kTabA>(src, 64, static_cast<int>(nw), src[0], reinterpret_cast<const char*>(tab), acc);
-    const int64_t row = rq * 64 + lane;
-    if (row < a.kr) upart[pc * a.kr + row] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  }
-}
-
-// v0 + x[0] + x[stride] + ... + x[(n - 1) stride], added in that order, with
-// eight loads in flight ahead of their adds.
-__device__ __forceinline__ double chunk_sum(const double* __restrict__ x, int64_t stride, int64_t n,
-                                            double v0 = 0.0) {
-  double v = v0;
-  int64_t c = 0;
-  for (; c + 8 <= n; c += 8) {
-    double t[8];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t nx = std::max<int64_t>((4 * a.nbits + TW - 1) / TW, 1);
+  if (bid >= nx) {                  // sparse rows
+    const int64_t x = bid - nx;
+    const int64_t e0 = a.ell_ptr[x];
+    const int n = static_cast<int>(a.ell_ptr[x + 1] - e0);   // entries per row
+    const int i1 = n * (wave + 1) / kWaves;
+    const int32_t* __restrict__ idx = a.ell_idx + e0 * 64 + lane;
+    const double* __restrict__ r = a.r;
+    const double size = static_cast<double>(a.sz[x * 64 + lane]);
+    double v = 0.0;
+    for (int i = n * wave / kWaves; i < i1; i += 8) {
+      int32_t p[8];
+      double e[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) t[q] = x[(c + q) * stride];
+      for (int k = 0; k < 8; ++k) p[k] = i + k < i1 ? idx[(i + k) * 64] : static_cast<int32_t>(a.M);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v += t[q];
-  }
-  for (; c < n; ++c) v += x[c * stride];
-  return v;
-}
-
-// u of the bit rows (the sum of their pass-A chunks, one lane per row) with
-// partial |u|^2 and |m|.u in uu[2 (1 + x)], uu[2 (1 + x) + 1]; the last
-// workgroup adds pass A's sparse-row partials into uu[0], uu[1] (fixed order).
-__global__ void __launch_bounds__(256) k_cg_rows(GroupArgs g) {
-  __shared__ double red[4];
-  int64_t bid;
-  const Args& a = g.a[member_of(g, bid)];
-  if (a.st->done) return;
-  if (bid == a.nbu - 1) {
-    const int wv = threadIdx.x >> 6;
-    if (wv < 2) {
-      const double v = a.nsa > 0 ? wave_fixed_sum(a.usp + wv, a.nsa, 2) : 0.0;
-      if ((threadIdx.x & 63) == 0) a.uu[wv] = v;
+      for (int k = 0; k < 8; ++k) e[k] = r[p[k]];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v += e[k];
     }
-    return;
-  }
-  const int64_t b = a.rs + bid * 256 + threadIdx.x;
-  double uu = 0.0, su = 0.0;
-  if (b < a.kr) {
-    const double v = chunk_sum(a.upart + b, a.kr, a.npc);
-    a.u[b] = v;
-    uu = v * v;
-    su = static_cast<double>(a.sz[b]) * v;
-  }
-  const double s1 = block_sum_d(uu, red);
-  const double s2 = block_sum_d(su, red);
-  if (threadIdx.x == 0) {
-    a.uu[2 * (1 + bid)] = s1;
-    a.uu[2 * (1 + bid) + 1] = s2;
-  }
-}
-
-// Pass B.  Workgroup c * nxb + x (c < nrcd): qpart[c, j] = sum over the row
-// blocks of chunk c of the bits of player j times u; the workgroup builds
-// the chunk's nibble tables of u in LDS (u is padded with zeros to whole row
-// blocks), then each wave takes PW words of 64 players (lane =
-// player), reads the bit-transposed words T[rb, j] and sums table entries.  Workgroup
-// nxb * nrcd + x (x < nsb): groups of 64 / L players (x * kWaves + wave, +
-// nsb * kWaves, ...): qs[j] = sum of u over the sparse rows holding player j.
-template <int PW>
-__global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(8))) k_cg_pass_b(GroupArgs g) {
-  __shared__ double tab[kTabB * 256];
-  int64_t bid;
-  const Args& a = g.a[member_of(g, bid)];
-  if (a.st->done) return;
-  const uint64_t* __restrict__ T = a.T;
-  const double* __restrict__ u = a.u;
-  double* __restrict__ qpart = a.qpart;
-  // one flat grid per member: nxb x nrcd bit-row workgroups, then nsb sparse-row ones
-  const int64_t c = bid < a.nxb * a.nrcd ? bid / a.nxb : a.nrcd;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (c == a.nrcd) {                  // sparse rows: 64 / L players per wavefront
-    const int64_t x = bid - a.nxb * a.nrcd;
-    const int lg = a.lgb, L = 1 << lg;
-    const int64_t nit = (a.M + (64 >> lg) - 1) >> (6 - lg);
-    for (int64_t it = x * kWaves + wave; it < nit; it += a.nsb * kWaves) {
-      const int64_t j = (it << (6 - lg)) + (lane >> lg);
-      double v;
-      if (lg == 6) {
-        const int64_t e0 = a.csc_ptr[j];
-        v = wave_gather_sum(a.csc_row + e0, a.csc_ptr[j + 1] - e0, u);
-      } else {
-        const bool ok = j < a.M;
-        const int64_t e1 = ok ? a.csc_ptr[j + 1] : 0;
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-        for (int64_t e = (ok ? a.csc_ptr[j] : 0) + (lane & (L - 1)); e < e1; e += 4 * L) {
-          s0 += u[a.csc_row[e]];
-          if (e + L < e1) s1 += u[a.csc_row[e + L]];
-          if (e + 2 * L < e1) s2 += u[a.csc_row[e + 2 * L]];
-          if (e + 3 * L < e1) s3 += u[a.csc_row[e + 3 * L]];
-        }
-        v = (s0 + s1) + (s2 + s3);
-        for (int off = L >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    double* part = reinterpret_cast<double*>(buf);
+    part[wave * 64 + lane] = v;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) v += part[w * 64 + lane];
+      a.us[x * 64 + lane] = v;
+      const double s1 = wave_sum_d(v * v), s2 = wave_sum_d(size * v);
+      if (lane == 0) {
+        a.uu[2 * (2 * a.nbits + x)] = s1;
+        a.uu[2 * (2 * a.nbits + x) + 1] = s2;
       }
-      if ((lane & (L - 1)) == 0 && j < a.M) a.qs[j] = v;
     }
     return;
   }
-  // the wavefront's player words: gw, gw + kWaves, ... (PW of them)
-  const int64_t gw = (bid % a.nxb) * (kWaves * PW) + wave;
-  const int64_t b0 = a.rbd0 + c * a.rbc;
-  const int64_t b1 = b0 + a.rbc < a.nrb ? b0 + a.rbc : a.nrb;
-  const int64_t nb = b1 - b0;
-  build_tables(u + b0 * 64, nb * 16, tab);
+  BitProducts<TW> bp;
+  if (a.nbits > 0) {
+    bp.set(a.blocked + a.rbd0 * a.wpr * 64, 0, bid * TW, 4 * a.nbits, a.wpr, a.wpr, a.rdig);
+    bp.start(wave);
+  }
+  // this lane's row in wavefronts 0 .. TW - 1
+  const int i = 16 * wave + 4 * (lane >> 4) + (lane & 3);
+  const int64_t b = (a.rbd0 * 4 + bid * TW) * 16 + i;
+  const bool mine = wave < TW && (lane & 15) < 4;
+  const double size = mine && b < a.kr ? static_cast<double>(a.sz[b]) : 0.0;
+  const int er = a.ex[t & 1];
+  if (wave == kWaves - 1) {
+    const double v = wave_fixed(a.rr + (t % 3) * 2 * a.wpr, 2 * a.wpr);
+    if (lane == 0) {
+      gamma = v;
+      if (bid == 0) cg_stop(a, t, v);
+    }
+  }
+  if (a.nbits == 0) return;
+  double row[4];
+  bp.run(wave, er, buf, row);
+  // |u_b| <= sqrt(M) |r| (Cauchy-Schwarz) gives the digits of u their exponent
+  const int eu = fixed_exponent(1.0000001 * __builtin_sqrt(static_cast<double>(a.M) * gamma));
+  if (wave < TW) {
+    // rows beyond kr have no bits (zero), those beyond the last block belong to none
+    const double v = mine && bid * TW + wave < 4 * a.nbits ? pick_row(row, lane) : 0.0;
+    if (mine) fixed[i] = to_fixed(v, eu);
+    const double s1 = wave_sum_d(v * v), s2 = wave_sum_d(size * v);
+    if (lane == 0) {
+      red[wave] = s1;
+      red[kWaves + wave] = s2;
+    }
+  }
   __syncthreads();
-#pragma unroll 1
-  for (int q = 0; q < PW; ++q) {
-    const int64_t gq = gw + q * kWaves;
-    if (gq >= a.wpr) break;
-    const int64_t j = gq * 64 + lane;
-    const bool valid = j < a.M;
-    const uint64_t* col = T + b0 * a.M + (valid ? j : 0);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    // a lane beyond M reads player 0's words and discards its sums
-    nibble_dots<kTabB>(col, a.M, static_cast<int>(nb), col[0], reinterpret_cast<const char*>(tab), acc);
-    if (valid) qpart[c * a.M + j] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  if (tid < 32 * TW) {
+    const int64_t u = bid * (TW / 2) + wave;
+    if (u < 2 * a.nbits) {
+      store_digits(fixed + 32 * wave, lane, u, a.udig);
+      if (lane == 0) {
+        a.uu[2 * u] = red[2 * wave] + red[2 * wave + 1];
+        a.uu[2 * u + 1] = red[kWaves + 2 * wave] + red[kWaves + 2 * wave + 1];
+      }
+    }
+  }
+  if (bid == 0 && tid == 0) a.ex[2] = eu;
+}
+
+// Pass B.  Workgroup x: players 16 TW x .. (see the recurrences above).
+template <int TW>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_cg_pass_b(GroupArgs g) {
+  __shared__ alignas(16) float buf[kWaves * TW * 256];
+  __shared__ double sparse[16 * TW];
+  __shared__ uint64_t fixed[16 * TW];
+  __shared__ double sums[6];
+  __shared__ double red[3][kWaves];
+  int64_t bid;
+  const int m = member_of(g, bid);
+  const Args& a = g.a[m];
+  const int64_t t = g.t[m];
+  if (a.st->done) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  BitProducts<TW> bp;
+  if (a.nbits > 0) {
+    bp.set(a.T, a.rbd0, bid * TW, 4 * a.wpr, a.nrb, a.nbits, a.udig);
+    bp.start(wave);
+  }
+  // this lane's player in wavefronts 0 .. TW - 1
+  const int i = 16 * wave + 4 * (lane >> 4) + (lane & 3);
+  const int64_t j = bid * (16 * TW) + i;
+  const bool mine = wave < TW && (lane & 15) < 4 && j < a.M;
+  double rj = 0.0, pj = 0.0, sj = 0.0, xj = 0.0;
+  if (mine) {
+    rj = a.r[j];
+    pj = a.p[j];
+    sj = a.s[j];
+    xj = a.x[j];
+  }
+  // the sparse rows' lists of this thread's players
+  constexpr int kLists = (TW + 3) / 4;
+  int64_t le0[kLists], le1[kLists];
+#pragma unroll
+  for (int h = 0; h < kLists; ++h) {
+    const int ps = 64 * h + (tid >> 3);
+    const int64_t js = bid * (16 * TW) + ps;
+    const bool any = a.rs > 0 && js < a.M && ps < 16 * TW;
+    le0[h] = any ? a.csc_ptr[js] + (tid & 7) : 0;
+    le1[h] = any ? a.csc_ptr[js + 1] : 0;
+  }
+  const int eu = a.ex[2];
+  const double before = t > 0 ? a.hist[(t + 1) & 1] : 1.0;   // the step before this one
+  // the scalars' partial sums, one wavefront each: gamma, the gamma before,
+  // |u|^2, |m|.u, largest |r| and |s|
+  if (wave < 6) {
+    const int64_t n = 2 * a.wpr;   // units of 32 players
+    double v;
+    if (wave == 0) v = wave_fixed(a.rr + (t % 3) * n, n);
+    else if (wave == 1) v = t > 0 ? wave_fixed(a.rr + ((t + 2) % 3) * n, n) : 1.0;
+    else if (wave < 4) v = wave_fixed(a.uu + (wave - 2), 2 * a.nbits + a.rbd0, 2);
+    else v = wave_fixed<true>(a.mx + ((t & 1) * 2 + wave - 4) * n, n);
+    if (lane == 0) sums[wave] = v;
+  }
+  // sparse rows: eight lanes per player, eight entries of each lane in flight
+#pragma unroll
+  for (int h = 0; h < kLists; ++h) {
+    double v = 0.0;
+    for (int64_t e = le0[h]; e < le1[h]; e += 64) {
+      int32_t p[8];
+      double u[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) p[k] = e + 8 * k < le1[h] ? a.csc_row[e + 8 * k] : -1;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) u[k] = p[k] >= 0 ? a.us[p[k]] : 0.0;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v += u[k];
+    }
+    v += row_move<0xB1>(v);
+    v += row_move<0x4E>(v);
+    v += row_move<0x141>(v);
+    if ((tid & 7) == 0 && 64 * h + (tid >> 3) < 16 * TW) sparse[64 * h + (tid >> 3)] = v;
+  }
+  double row[4] = {};
+  if (a.nbits > 0) {
+    bp.run(wave, eu, buf, row);
+  } else {
+    __syncthreads();
+  }
+  const double gamma = sums[0], uu = sums[2];
+  double beta = 0.0, den = a.alpha * gamma + a.wr2 * uu;
+  if (t > 0) {
+    beta = gamma / sums[1];
+    den -= beta * gamma / before;
+  }
+  const double step = gamma / den;
+  const double mq = sums[3] / static_cast<double>(a.M);
+  if (!(den > 0.0 && step < 1e300 && beta == beta)) {   // identical in every workgroup
+    if (bid == 0 && tid == 0) {
+      a.st->done = 1;
+      a.st->iters = static_cast<int32_t>(t);
+      a.st->status = 2;
+      __hip_atomic_store(a.host_flag + 1, static_cast<int32_t>(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(a.host_flag, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    return;
+  }
+  // |(R^T u)_j| <= sqrt(kr) |u| bounds the new s and r, and so gives the
+  // digits of r their exponent
+  const double bw = a.alpha * sums[4] + a.wr2 * (__builtin_sqrt(static_cast<double>(a.kr) * uu) + __builtin_fabs(mq));
+  const int e = fixed_exponent(1.0000001 * (sums[4] + step * (bw + beta * sums[5])));
+  if (wave < TW) {
+    double rn = 0.0, sn = 0.0;
+    if (mine) {
+      const double wj = a.alpha * rj + a.wr2 * ((sparse[i] + pick_row(row, lane)) - mq);
+      const double pn = rj + beta * pj;
+      sn = wj + beta * sj;
+      rn = rj - step * sn;
+      a.p[j] = pn;
+      a.s[j] = sn;
+      a.x[j] = xj + step * pn;
+      a.r[j] = rn;
+    }
+    if ((lane & 15) < 4) fixed[i] = to_fixed(rn, e);
+    const double r2 = wave_sum_d(rn * rn), rm = wave_max_d(__builtin_fabs(rn)), sm = wave_max_d(__builtin_fabs(sn));
+    if (lane == 0) {
+      red[0][wave] = r2;
+      red[1][wave] = rm;
+      red[2][wave] = sm;
+    }
+  }
+  __syncthreads();
+  if (tid < 32 * TW) {
+    const int64_t u = bid * (TW / 2) + wave, n = 2 * a.wpr;
+    if (u < n) {
+      store_digits(fixed + 32 * wave, lane, u, a.rdig);
+      if (lane == 0) {
+        a.rr[((t + 1) % 3) * n + u] = red[0][2 * wave] + red[0][2 * wave + 1];
+        double* mx = a.mx + ((t + 1) & 1) * 2 * n;
+        mx[u] = fmax(red[1][2 * wave], red[1][2 * wave + 1]);
+        mx[n + u] = fmax(red[2][2 * wave], red[2][2 * wave + 1]);
+      }
+    }
+  }
+  if (bid == 0 && tid == 0) {
+    a.hist[t & 1] = step;
+    a.ex[(t + 1) & 1] = e;
   }
 }
+
+// The instance of a pass for `tiles` tiles per workgroup (4 or 6).
+using PassFn = void (*)(GroupArgs);
+PassFn pass_a(int tiles) { return tiles == 4 ? k_cg_pass_a<4> : k_cg_pass_a<6>; }
+PassFn pass_b(int tiles) { return tiles == 4 ? k_cg_pass_b<4> : k_cg_pass_b<6>; }
 
 // ---- the sparse rows' lists, built once per solve ------------------------------------------
 
-// Exclusive prefix sums of n values by one workgroup of 1024 threads (thread t
-// takes a contiguous run), v[i] -> out[i], total -> out[n].
-template <class T>
-__device__ void block_scan_i64(const T* __restrict__ v, int64_t n, int64_t* __restrict__ out) {
-  __shared__ int64_t part[1024];
-  const int t = threadIdx.x;
-  const int64_t per = (n + 1023) / 1024;
-  const int64_t i0 = t * per, i1 = i0 + per < n ? i0 + per : n;
-  int64_t s = 0;
-  for (int64_t i = i0; i < i1; ++i) s += v[i];
-  part[t] = s;
-  __syncthreads();
-  if (t == 0) {
-    int64_t run = 0;
-    for (int i = 0; i < 1024; ++i) {
-      const int64_t x = part[i];
-      part[i] = run;
-      run += x;
-    }
-    out[n] = run;
+// Inclusive prefix sum of v over the 1024 threads of a workgroup.
+__device__ int64_t block_scan(int64_t v) {
+  __shared__ int64_t part[16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int64_t x = __shfl_up(static_cast<long long>(v), off);
+    if (lane >= off) v += x;
   }
+  if (lane == 63) part[wave] = v;
   __syncthreads();
-  int64_t run = part[t];
-  for (int64_t i = i0; i < i1; ++i) {
-    const int64_t x = v[i];
-    out[i] = run;
-    run += x;
-  }
+  for (int w = 0; w < wave; ++w) v += part[w];
+  return v;
 }
 
-// Row-major lists: csr_ptr = exclusive prefix sums of the sparse rows' sizes.
-__global__ void __launch_bounds__(1024) k_cg_csr_ptr(const int32_t* __restrict__ sz, int64_t rs,
-                                                     int64_t* __restrict__ ptr, int64_t* __restrict__ sitem) {
-  block_scan_i64(sz, rs, ptr);
-  // pass A's work items: block q (rows 64 q .. 64 q + 63, sizes ascending)
-  // gives 2^lg items of 64 / 2^lg rows each, lg from its largest row
-  // (at most 1024 blocks: thread q owns block q; an inclusive scan of the
-  // item counts in LDS, Hillis-Steele)
-  __shared__ int64_t cnt[2][1024];
-  const int64_t nblk = rs / 64;
-  const int q = threadIdx.x;
-  const int lg = q < nblk ? sparse_lanes_log2(sz[64 * q + 63]) : 0;
-  cnt[0][q] = q < nblk ? (int64_t(1) << lg) : 0;
-  __syncthreads();
-  int cur = 0;
-  for (int off = 1; off < 1024; off <<= 1) {
-    cnt[cur ^ 1][q] = cnt[cur][q] + (q >= off ? cnt[cur][q - off] : 0);
-    cur ^= 1;
-    __syncthreads();
-  }
-  if (q < nblk) {
-    const int64_t first = cnt[cur][q] - (int64_t(1) << lg);
-    const int64_t rows = int64_t(64) >> lg;
-    for (int64_t g = 0; g < (int64_t(1) << lg); ++g) sitem[first + g] = ((int64_t(64) * q + g * rows) << 8) | lg;
-  }
+// Row lists: ptr[x] = entries per row of the blocks before x (block x's rows
+// have as many as its last, largest row), at most 1024 blocks.
+__global__ void __launch_bounds__(1024) k_cg_ell_ptr(const int32_t* __restrict__ sz, int64_t nblk,
+                                                     int64_t* __restrict__ ptr) {
+  const int x = threadIdx.x;
+  const int64_t n = x < nblk ? sz[64 * x + 63] : 0;
+  const int64_t end = block_scan(n);
+  if (x == 0) ptr[0] = 0;
+  if (x < nblk) ptr[x + 1] = end;
 }
 
 // The lists are built in kSeg segments at once: of the player words for the
@@ -520,9 +735,9 @@ __global__ void __launch_bounds__(1024) k_cg_csr_ptr(const int32_t* __restrict__
 // it; every list comes out in ascending order.
 constexpr int kSeg = 8;
 
-// Row-major lists, counts: wavefront (g, s) reads the words of segment s of its
+// Row lists, counts: wavefront (g, s) reads the words of segment s of its
 // 64 rows from the row-blocked copy (lane = row): cnt[s][b].
-__global__ void __launch_bounds__(64) k_cg_csr_count(const uint64_t* __restrict__ blocked, int64_t wpr, int64_t rs,
+__global__ void __launch_bounds__(64) k_cg_ell_count(const uint64_t* __restrict__ blocked, int64_t wpr, int64_t rs,
                                                      int32_t* __restrict__ cnt) {
   const int64_t g = blockIdx.x;
   const int sg = blockIdx.y;
@@ -535,38 +750,42 @@ __global__ void __launch_bounds__(64) k_cg_csr_count(const uint64_t* __restrict_
   cnt[sg * rs + b] = c;
 }
 
-// Row-major lists, fill: the players of segment s of row b in order.
-__global__ void __launch_bounds__(64) k_cg_csr_fill(const uint64_t* __restrict__ blocked, int64_t wpr, int64_t rs,
+// Row lists, fill: the players of segment s of row b in order; the last
+// segment pads the row with M.
+__global__ void __launch_bounds__(64) k_cg_ell_fill(const uint64_t* __restrict__ blocked, int64_t wpr, int64_t rs,
                                                     const int64_t* __restrict__ ptr, const int32_t* __restrict__ cnt,
-                                                    int64_t nnz, int32_t* __restrict__ idx) {
+                                                    int32_t M, int32_t* __restrict__ idx) {
   const int64_t g = blockIdx.x;
   const int sg = blockIdx.y;
   const int64_t b = g * 64 + threadIdx.x;
   if (b >= rs) return;
-  int64_t pos = ptr[b];
+  int64_t pos = ptr[g];
+  const int64_t end = ptr[g + 1];
   for (int q = 0; q < sg; ++q) pos += cnt[q * rs + b];
-  const int64_t end = ptr[b + 1] < nnz ? ptr[b + 1] : nnz;
   const int64_t w0 = wpr * sg / kSeg, w1 = wpr * (sg + 1) / kSeg;
   const uint64_t* src = blocked + g * wpr * 64 + threadIdx.x;
+  idx += threadIdx.x;
   for (int64_t w = w0; w < w1; ++w) {
     uint64_t word = src[w * 64];
     while (word && pos < end) {
-      idx[pos++] = static_cast<int32_t>(w * 64 + __builtin_ctzll(word));
+      idx[64 * pos++] = static_cast<int32_t>(w * 64 + __builtin_ctzll(word));
       word &= word - 1;
     }
   }
+  if (sg == kSeg - 1)
+    for (; pos < end; ++pos) idx[64 * pos] = M;
 }
 
 // Player-major lists, counts: cnt[s][j] = the sparse rows of segment s (row
 // blocks nrb_s s / kSeg .. of the bit-transposed rows T[rb, j]) holding j.
-__global__ void __launch_bounds__(256) k_cg_csc_count(const uint64_t* __restrict__ T, int64_t M, int64_t nrb_s,
+__global__ void __launch_bounds__(256) k_cg_csc_count(const uint64_t* __restrict__ T, int64_t M, int64_t nrb, int64_t nrb_s,
                                                       int32_t* __restrict__ cnt) {
   const int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int sg = blockIdx.y;
   if (j >= M) return;
   const int64_t r0 = nrb_s * sg / kSeg, r1 = nrb_s * (sg + 1) / kSeg;
   int c = 0;
-  for (int64_t rb = r0; rb < r1; ++rb) c += __popcll(T[rb * M + j]);
+  for (int64_t rb = r0; rb < r1; ++rb) c += __popcll(T[((j >> 6) * nrb + rb) * 64 + (j & 63)]);
   cnt[sg * M + j] = c;
 }
 
@@ -582,27 +801,15 @@ __global__ void __launch_bounds__(256) k_cg_csc_total(const int32_t* __restrict_
   ptr[j] = v;
 }
 
+// (in place: each thread reads each of its entries before writing it)
 __global__ void __launch_bounds__(1024) k_cg_csc_scan(int64_t M, int64_t* ptr) {
-  // in place: each thread reads each of its entries before writing it
-  __shared__ int64_t part[1024];
   const int t = threadIdx.x;
   const int64_t per = (M + 1023) / 1024;
   const int64_t i0 = t * per, i1 = i0 + per < M ? i0 + per : M;
   int64_t s = 0;
   for (int64_t i = i0; i < i1; ++i) s += ptr[i];
-  part[t] = s;
-  __syncthreads();
-  if (t == 0) {
-    int64_t run = 0;
-    for (int i = 0; i < 1024; ++i) {
-      const int64_t x = part[i];
-      part[i] = run;
-      run += x;
-    }
-    ptr[M] = run;
-  }
-  __syncthreads();
-  int64_t run = part[t];
+  int64_t run = block_scan(s) - s;
+  if (t == 1023) ptr[M] = run + s;
   for (int64_t i = i0; i < i1; ++i) {
     const int64_t x = ptr[i];
     ptr[i] = run;
@@ -610,7 +817,7 @@ __global__ void __launch_bounds__(1024) k_cg_csc_scan(int64_t M, int64_t* ptr) {
   }
 }
 
-__global__ void __launch_bounds__(256) k_cg_csc_fill(const uint64_t* __restrict__ T, int64_t M, int64_t nrb_s,
+__global__ void __launch_bounds__(256) k_cg_csc_fill(const uint64_t* __restrict__ T, int64_t M, int64_t nrb, int64_t nrb_s,
                                                      const int64_t* __restrict__ ptr, const int32_t* __restrict__ cnt,
                                                      int64_t nnz, int32_t* __restrict__ rows) {
   const int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
@@ -621,7 +828,7 @@ __global__ void __launch_bounds__(256) k_cg_csc_fill(const uint64_t* __restrict_
   const int64_t end = ptr[j + 1] < nnz ? ptr[j + 1] : nnz;
   const int64_t r0 = nrb_s * sg / kSeg, r1 = nrb_s * (sg + 1) / kSeg;
   for (int64_t rb = r0; rb < r1; ++rb) {
-    uint64_t word = T[rb * M + j];
+    uint64_t word = T[((j >> 6) * nrb + rb) * 64 + (j & 63)];
     while (word && pos < end) {
       rows[pos++] = static_cast<int32_t>(rb * 64 + __builtin_ctzll(word));
       word &= word - 1;
@@ -629,80 +836,15 @@ __global__ void __launch_bounds__(256) k_cg_csc_fill(const uint64_t* __restrict_
   }
 }
 
-// Update of iteration t (see the recurrences above); partial gamma_{t+1}.
-__global__ void __launch_bounds__(256) k_cg_update(GroupArgs g) {
-  __shared__ double red[4];
-  __shared__ double coef[3];
-  int64_t bid;
-  const int m = member_of(g, bid);
-  const Args& a = g.a[m];
-  const int64_t t = g.t[m];
-  if (a.st->done) return;
-  const int64_t j = bid * 256 + threadIdx.x;
-  // this thread's vector entries first: their loads overlap the scalar sums
-  double q = 0.0, rj = 0.0, pj = 0.0, sj = 0.0;
-  if (j < a.M) {
-    if (a.has_random) {
-      if (a.rs > 0) q = a.qs[j];
-      q = chunk_sum(a.qpart + j, a.M, a.nrcd, q);
-    }
-    rj = a.r[j];
-    pj = a.p[j];
-    sj = a.s[j];
-  }
-  // the four scalar sums, one per wavefront, side by side
-  __shared__ double sums[4];
-  {
-    const int wv = threadIdx.x >> 6;
-    double v = 0.0;
-    if (wv == 0) v = wave_fixed_sum(a.rr + (t % 3) * a.nbc, a.nbc);
-    else if (wv == 1) v = a.has_random ? wave_fixed_sum(a.uu, a.nbu, 2) : 0.0;
-    else if (wv == 2) v = a.has_random ? wave_fixed_sum(a.uu + 1, a.nbu, 2) : 0.0;
-    else v = t > 0 ? wave_fixed_sum(a.rr + ((t + 2) % 3) * a.nbc, a.nbc) : 1.0;
-    if ((threadIdx.x & 63) == 0) sums[wv] = v;
-  }
+// Sum of v over the 1024 threads of a workgroup, in every thread.
+__device__ __forceinline__ double block_sum_d(double v) {
+  __shared__ double red[16];
+  v = wave_sum_d(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const double g = sums[0], uu = sums[1], su = sums[2], gp = sums[3];
-    const double delta = a.alpha * g + a.wr2 * uu;
-    double beta = 0.0, den = delta;
-    if (t > 0) {
-      beta = g / gp;
-      den = delta - beta * g / a.hist[(t + 1) & 1];
-    }
-    const double step = g / den;
-    const bool ok = den > 0.0 && step == step && step < 1e300 && beta == beta;
-    coef[0] = ok ? step : -1.0;
-    coef[1] = beta;
-    coef[2] = su / static_cast<double>(a.M);
-    if (ok && bid == 0) a.hist[t & 1] = step;
-  }
-  __syncthreads();
-  const double step = coef[0], beta = coef[1], mq = coef[2];
-  if (step < 0.0) {   // identical in every workgroup
-    if (bid == 0 && threadIdx.x == 0) {
-      a.st->done = 1;
-      a.st->iters = static_cast<int32_t>(t);
-      a.st->status = 2;
-      __hip_atomic_store(a.host_flag + 1, static_cast<int32_t>(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-      __hip_atomic_store(a.host_flag, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-    return;
-  }
-  double r2 = 0.0;
-  if (j < a.M) {
-    const double wj = a.alpha * rj + a.wr2 * (q - mq);
-    const double pn = rj + beta * pj;
-    const double sn = wj + beta * sj;
-    a.p[j] = pn;
-    a.s[j] = sn;
-    a.x[j] += step * pn;
-    const double rn = rj - step * sn;
-    a.r[j] = rn;
-    r2 = rn * rn;
-  }
-  const double sb = block_sum_d(r2, red);
-  if (threadIdx.x == 0) a.rr[((t + 1) % 3) * a.nbc + bid] = sb;
+  double s = 0.0;
+  for (int i = 0; i < 16; ++i) s += red[i];
+  return s;
 }
 
 // phi = Delta/M + x - mean(x) (the projection made exact), info from the state.
@@ -710,10 +852,9 @@ __global__ void __launch_bounds__(1024) k_cg_finish(const double* __restrict__ x
                                                     const gnnshap::CgState* __restrict__ st,
                                                     const float* __restrict__ fef, float* __restrict__ phi,
                                                     int32_t* info, int32_t undetermined) {
-  __shared__ double red[16];
   double sm = 0.0;
   for (int64_t j = threadIdx.x; j < M; j += 1024) sm += x[j];
-  const double mean = block_sum_d(sm, red) / static_cast<double>(M);
+  const double mean = block_sum_d(sm) / static_cast<double>(M);
   const double base = (static_cast<double>(fef[1]) - static_cast<double>(fef[0])) / static_cast<double>(M);
   for (int64_t j = threadIdx.x; j < M; j += 1024) phi[j] = static_cast<float>(base + (x[j] - mean));
   if (threadIdx.x == 0) *info = (st->status == 0 && !undetermined) ? 0 : static_cast<int32_t>(M + 1);
@@ -812,31 +953,12 @@ gnnshap::CgShape gnnshap::cg_shape(int64_t M, int64_t wpr, int64_t kr, int64_t r
       for (int64_t r = from; r < classes[i].row_begin + classes[i].row_count; ++r) sz.push_back(classes[i].size);
     }
     s.rs = (std::min<int64_t>(static_cast<int64_t>(sz.size()), kr) / 64) * 64;
-    if (s.rs > 64 * 1024) s.rs = 64 * 1024;   // the item table's scan holds 1024 blocks
+    if (s.rs > 64 * 1024) s.rs = 64 * 1024;   // the row lists' scan holds 1024 blocks
     for (int64_t b = 0; b < s.rs; ++b) s.nnz += sz[b];
-    for (int64_t q = 0; q < s.rs / 64; ++q) s.nsi += int64_t(1) << sparse_lanes_log2(sz[64 * q + 63]);
+    for (int64_t q = 0; q < s.rs / 64; ++q) s.nell += 64 * static_cast<int64_t>(sz[64 * q + 63]);
   }
   s.rbd0 = s.rs / 64;
-  const int64_t nrbd = std::max<int64_t>(s.nrb - s.rbd0, 1);
-  // pass A: at least kFill (row block, player chunk) pairs, chunks of whole
-  // words, at most kTabA words of tables per workgroup
-  const int64_t npc = std::max<int64_t>(ceil_div(wpr, kTabA), std::min(ceil_div(kFill, nrbd), wpr));
-  s.pwords = ceil_div(wpr, npc);
-  s.npc = ceil_div(wpr, s.pwords);
-  // pass B: at least kFill (player word, row chunk) pairs, chunks of whole
-  // row blocks, at most kTabB row blocks of tables per workgroup
-  const int64_t nrc = std::max<int64_t>(ceil_div(nrbd, kTabB), std::min(ceil_div(kFill, wpr), nrbd));
-  s.rbc = ceil_div(nrbd, nrc);
-  s.nrc = ceil_div(nrbd, s.rbc);
-  // workgroups of the sparse rows in pass A (rows) and pass B (players), at
-  // most 2048 each (each wave loops), and of the bit rows in the row pass
-  s.nsa = s.rs > 0 ? std::min<int64_t>(ceil_div(s.nsi, kWaves), 2048) : 0;
-  // pass B: lanes per player list from the mean list length (longer lists loop)
-  s.lgb = sparse_lanes_log2(ceil_div(s.nnz, M));
-  s.nsb = s.rs > 0 ? std::min<int64_t>(ceil_div(ceil_div(M, int64_t(64) >> s.lgb), kWaves), 2048) : 0;
-  s.nrcd = s.rbd0 < s.nrb ? s.nrc : 0;
-  s.nbu = 1 + ceil_div(kr - s.rs > 0 ? kr - s.rs : 1, 256);
-  s.nbc = ceil_div(wpr * 64, 256);
+  s.nbits = s.nrb - s.rbd0;
   return s;
 }
 
@@ -844,25 +966,24 @@ gnnshap::CgWs gnnshap::cg_carve(Carver& c, const CgShape& sh) {
   CgWs w;
   const int64_t kr = sh.kr > 0 ? sh.kr : 1;
   w.x = c.take<double>(sh.M);
-  w.r = c.take<double>(sh.wpr * 64);
+  w.r = c.take<double>(sh.M + 1);
   w.p = c.take<double>(sh.M);
   w.s = c.take<double>(sh.M);
-  w.upart = c.take<double>(sh.npc * kr);
-  w.u = c.take<double>((sh.nrb > 0 ? sh.nrb : 1) * 64);
-  w.qpart = c.take<double>(sh.nrc * sh.M);
-  w.uu = c.take<double>(2 * sh.nbu);
-  w.usp = c.take<double>(2 * (sh.nsa > 0 ? sh.nsa : 1));
-  w.rr = c.take<double>(3 * sh.nbc);
+  w.us = c.take<double>(sh.rs > 0 ? sh.rs : 1);
+  w.rdig = c.take<char>(digit_bytes(sh.wpr));
+  w.udig = c.take<char>(std::max<int64_t>(digit_bytes(sh.nbits), 1));
+  w.uu = c.take<double>(2 * std::max<int64_t>(2 * sh.nbits + sh.rbd0, 1));
+  w.rr = c.take<double>(3 * 2 * sh.wpr);
+  w.mx = c.take<double>(4 * 2 * sh.wpr);
   w.hist = c.take<double>(2);
+  w.ex = c.take<int32_t>(3);
   w.sz = c.take<int32_t>(kr);
   w.blocked = c.take<uint64_t>((sh.nrb > 0 ? sh.nrb : 1) * sh.wpr * 64);
   w.st = c.take<CgState>(1);
-  w.csr_ptr = c.take<int64_t>(sh.rs + 1);
-  w.csr_idx = c.take<int32_t>(sh.nnz > 0 ? sh.nnz : 1);
+  w.ell_ptr = c.take<int64_t>(sh.rbd0 + 1);
+  w.ell_idx = c.take<int32_t>(sh.nell > 0 ? sh.nell : 1);
   w.csc_ptr = c.take<int64_t>(sh.M + 1);
   w.csc_row = c.take<int32_t>(sh.nnz > 0 ? sh.nnz : 1);
-  w.qs = c.take<double>(sh.M);
-  w.sitem = c.take<int64_t>(sh.nsi > 0 ? sh.nsi : 1);
   w.segcnt = c.take<int32_t>(kSeg * std::max<int64_t>(std::max<int64_t>(sh.rs, sh.M), 1));
   return w;
 }
@@ -876,20 +997,7 @@ struct Member {
   gnnshap::CgWs w;
   HostFlag* hf = nullptr;
   int64_t t = 0;
-  uint32_t ga = 0, gb = 0, g_rows = 0, g_upd = 0;
 };
-
-// pw row blocks (pass A) and player words (pass B) per wavefront: the
-// passes' grids follow; the sums, and so the results, do not depend on pw.
-void set_per_wave(Member& m, int pw) {
-  Args& a = m.a;
-  const gnnshap::CgShape& sh = m.sh;
-  a.pw = pw;
-  a.nxa = gnnshap::ceil_div(std::max<int64_t>(sh.nrb - sh.rbd0, 1), kWaves * pw);
-  a.nxb = gnnshap::ceil_div(sh.wpr, kWaves * pw);
-  m.ga = static_cast<uint32_t>(a.nxa * sh.npc + sh.nsa);
-  m.gb = static_cast<uint32_t>(a.nxb * sh.nrcd + sh.nsb);
-}
 
 struct gnnshap::CgGroup::State {
   std::vector<Member> mem;
@@ -932,46 +1040,31 @@ int gnnshap::CgGroup::add(const CgProblem& pr, const CgShape& sh, const CgWs& w)
   a.wpr = sh.wpr;
   a.kr = sh.kr;
   a.nrb = sh.nrb;
-  a.npc = sh.npc;
-  a.pwords = sh.pwords;
-  a.nrc = sh.nrc;
-  a.rbc = sh.rbc;
-  a.nbu = sh.nbu;
-  a.nbc = sh.nbc;
   a.alpha = pr.alpha;
   a.wr2 = sh.kr > 0 ? 2.0 * pr.wr : 0.0;
   a.tol2 = kTol * kTol;
   a.maxit = kMaxIt;
-  a.has_random = sh.kr > 0 ? 1 : 0;
   a.x = w.x;
   a.r = w.r;
   a.p = w.p;
   a.s = w.s;
-  a.upart = w.upart;
-  a.u = w.u;
-  a.qpart = w.qpart;
+  a.us = w.us;
+  a.rdig = w.rdig;
+  a.udig = w.udig;
   a.uu = w.uu;
-  a.usp = w.usp;
   a.rr = w.rr;
+  a.mx = w.mx;
   a.hist = w.hist;
+  a.ex = w.ex;
   a.st = w.st;
   a.rs = sh.rs;
   a.rbd0 = sh.rbd0;
-  a.nsa = sh.nsa;
-  a.nsi = sh.nsi;
-  a.lgb = sh.lgb;
-  a.sitem = w.sitem;
-  a.nsb = sh.nsb;
-  a.nrcd = sh.nrcd;
-  set_per_wave(m, 1);
-  a.csr_ptr = w.csr_ptr;
-  a.csr_idx = w.csr_idx;
+  a.nbits = sh.nbits;
+  a.ell_ptr = w.ell_ptr;
+  a.ell_idx = w.ell_idx;
   a.csc_ptr = w.csc_ptr;
   a.csc_row = w.csc_row;
-  a.qs = w.qs;
   a.host_flag = hf->dev;
-  m.g_rows = static_cast<uint32_t>(sh.nbu);
-  m.g_upd = static_cast<uint32_t>(sh.nbc);
   // no kernel of an earlier solve that used this flag writes it any more:
   // a solve stops writing it at its stopping iteration, which had completed
   // before the flag was released
@@ -979,29 +1072,31 @@ int gnnshap::CgGroup::add(const CgProblem& pr, const CgShape& sh, const CgWs& w)
   __atomic_store_n(hf->host + 1, -1, __ATOMIC_RELEASE);
   {
     GS_TIMED("k_cg_init", s);
-    k_cg_init<<<static_cast<unsigned>(sh.nbc), 256, 0, s>>>(a, pr.dv, pr.bsum, pr.nb, pr.classes, pr.ncls, pr.rb0,
-                                                            w.sz);
+    k_cg_init<<<static_cast<unsigned>(ceil_div(sh.wpr, 4)), 256, 0, s>>>(a, pr.dv, pr.bsum, pr.nb, pr.classes,
+                                                                         pr.ncls, pr.rb0, w.sz);
+    GS_LAUNCHED();
+    k_cg_digits<<<static_cast<unsigned>(sh.wpr), 128, 0, s>>>(a);
   }
   GS_LAUNCHED();
   if (sh.rs > 0) {
-    // the sparse rows' lists (row sizes from k_cg_init); qs serves as the
-    // count scratch here, it is written before the iterations read it
+    // the sparse rows' lists (row sizes from k_cg_init)
     const int64_t nrb_s = sh.rs / 64;
     const dim3 gr(static_cast<unsigned>(nrb_s), kSeg), gp(static_cast<unsigned>(ceil_div(sh.M, 256)), kSeg);
     GS_TIMED("k_cg_sparse_build", s);
-    k_cg_csr_ptr<<<1, 1024, 0, s>>>(w.sz, sh.rs, w.csr_ptr, w.sitem);
+    k_cg_ell_ptr<<<1, 1024, 0, s>>>(w.sz, nrb_s, w.ell_ptr);
     GS_LAUNCHED();
-    k_cg_csr_count<<<gr, 64, 0, s>>>(pr.blocked, sh.wpr, sh.rs, w.segcnt);
+    k_cg_ell_count<<<gr, 64, 0, s>>>(pr.blocked, sh.wpr, sh.rs, w.segcnt);
     GS_LAUNCHED();
-    k_cg_csr_fill<<<gr, 64, 0, s>>>(pr.blocked, sh.wpr, sh.rs, w.csr_ptr, w.segcnt, sh.nnz, w.csr_idx);
+    k_cg_ell_fill<<<gr, 64, 0, s>>>(pr.blocked, sh.wpr, sh.rs, w.ell_ptr, w.segcnt, static_cast<int32_t>(sh.M),
+                                    w.ell_idx);
     GS_LAUNCHED();
-    k_cg_csc_count<<<gp, 256, 0, s>>>(pr.T, sh.M, nrb_s, w.segcnt);
+    k_cg_csc_count<<<gp, 256, 0, s>>>(pr.T, sh.M, sh.nrb, nrb_s, w.segcnt);
     GS_LAUNCHED();
     k_cg_csc_total<<<static_cast<unsigned>(ceil_div(sh.M, 256)), 256, 0, s>>>(w.segcnt, sh.M, w.csc_ptr);
     GS_LAUNCHED();
     k_cg_csc_scan<<<1, 1024, 0, s>>>(sh.M, w.csc_ptr);
     GS_LAUNCHED();
-    k_cg_csc_fill<<<gp, 256, 0, s>>>(pr.T, sh.M, nrb_s, w.csc_ptr, w.segcnt, sh.nnz, w.csc_row);
+    k_cg_csc_fill<<<gp, 256, 0, s>>>(pr.T, sh.M, sh.nrb, nrb_s, w.csc_ptr, w.segcnt, sh.nnz, w.csc_row);
     GS_LAUNCHED();
   }
   S.mem.push_back(m);
@@ -1031,6 +1126,40 @@ uint32_t fill_group(GroupArgs& g, const std::vector<Member>& mem, int64_t dt, Ta
   }
   g.blk[g.n] = total;
   return total;
+}
+
+}  // namespace
+
+namespace {
+
+// Workgroups of `tiles` tiles each: of pass A's bit rows (at least one, which
+// takes the stopping test) and of pass B.
+int64_t blocks_a(const gnnshap::CgShape& sh, int tiles) {
+  return std::max<int64_t>(gnnshap::ceil_div(4 * sh.nbits, tiles), 1);
+}
+int64_t blocks_b(const gnnshap::CgShape& sh, int tiles) { return gnnshap::ceil_div(4 * sh.wpr, tiles); }
+
+// Tiles per workgroup of a pass over the members: the number that leaves the
+// busiest of 256 CUs the least to load (see the passes), taking the
+// workgroups as spread evenly.
+template <class Blocks, class Groups>
+int choose_tiles(const std::vector<Member>& mem, Blocks blocks, Groups groups) {
+  int best = 4;
+  double least = 0.0;
+  for (int tiles = 4; tiles <= 6; tiles += 2) {
+    double count = 0.0, work = 0.0;
+    for (const Member& m : mem) {
+      const double n = static_cast<double>(blocks(m.sh, tiles));
+      count += n;
+      work += n * static_cast<double>(groups(m.sh)) * (8 * tiles + 48);   // clocks of 64 bytes
+    }
+    const double busiest = std::ceil(count / 256.0) * (work / count);
+    if (tiles == 4 || busiest < least) {
+      best = tiles;
+      least = busiest;
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -1071,49 +1200,24 @@ int gnnshap::CgGroup::step() {
     }
     if (S.mem.empty()) return GNNSHAP_OK;
   }
-  // a system alone fills the GPU better with one row block (player word)
-  // per wavefront, several systems leave fewer, longer wavefronts
-  const int pw = S.mem.size() >= 2 ? kPerWaveGroup : 1;
-  for (Member& m : S.mem)
-    if (m.a.pw != pw) set_per_wave(m, pw);
   GroupArgs g;
+  const int ta = choose_tiles(S.mem, blocks_a, [](const CgShape& sh) { return ceil_div(sh.wpr, 4); });
+  const int tb = choose_tiles(S.mem, blocks_b, [](const CgShape& sh) { return ceil_div(sh.nbits, 4) + 1; });
   for (int64_t dt = 0; dt < kChunk; ++dt) {
     uint32_t n = fill_group(g, S.mem, dt, [](const Member&, int64_t t) { return t <= kMaxIt; },
-                            [](const Member& m) { return m.ga; });
+                            [ta](const Member& m) { return static_cast<uint32_t>(blocks_a(m.sh, ta) + m.sh.rbd0); });
     if (g.n == 0) break;
     {
       GS_TIMED("k_cg_pass_a", s);
-      if (pw == 1)
-        k_cg_pass_a<1><<<n, kWaves * 64, 0, s>>>(g);
-      else
-        k_cg_pass_a<kPerWaveGroup><<<n, kWaves * 64, 0, s>>>(g);
+      pass_a(ta)<<<n, kThreads, 0, s>>>(g);
     }
     GS_LAUNCHED();
-    n = fill_group(g, S.mem, dt, [](const Member& m, int64_t t) { return t < kMaxIt && m.sh.kr > 0; },
-                   [](const Member& m) { return m.g_rows; });
+    n = fill_group(g, S.mem, dt, [](const Member&, int64_t t) { return t < kMaxIt; },
+                   [tb](const Member& m) { return static_cast<uint32_t>(blocks_b(m.sh, tb)); });
     if (g.n > 0) {
-      {
-        GS_TIMED("k_cg_rows", s);
-        k_cg_rows<<<n, 256, 0, s>>>(g);
-      }
-      GS_LAUNCHED();
-      n = fill_group(g, S.mem, dt, [](const Member& m, int64_t t) { return t < kMaxIt && m.sh.kr > 0; },
-                     [](const Member& m) { return m.gb; });
       {
         GS_TIMED("k_cg_pass_b", s);
-        if (pw == 1)
-          k_cg_pass_b<1><<<n, kWaves * 64, 0, s>>>(g);
-        else
-          k_cg_pass_b<kPerWaveGroup><<<n, kWaves * 64, 0, s>>>(g);
-      }
-      GS_LAUNCHED();
-    }
-    n = fill_group(g, S.mem, dt, [](const Member&, int64_t t) { return t < kMaxIt; },
-                   [](const Member& m) { return m.g_upd; });
-    if (g.n > 0) {
-      {
-        GS_TIMED("k_cg_update", s);
-        k_cg_update<<<n, 256, 0, s>>>(g);
+        pass_b(tb)<<<n, kThreads, 0, s>>>(g);
       }
       GS_LAUNCHED();
     }

@@ -19,23 +19,6 @@ constexpr int64_t kTabWords = 16;    // nibble tables per workgroup: 16 words (3
 // tables of a workgroup are one static LDS array, word w's 16 tables at
 // byte 2048 w.
 //
-// ntab tables of v (4 entries each) into tab, consecutive threads on
-// consecutive entries, so the writes of a wavefront cover 512 contiguous
-// bytes (no two lanes in one bank).  Entry n of table q is
-// ((v[4q] [n & 1] + v[4q + 1] [n & 2]) + v[4q + 2] [n & 4]) + v[4q + 3] [n & 8],
-// an absent term adding 0.0 (exact).
-__device__ __forceinline__ void build_tables(const double* __restrict__ v, int64_t ntab, double* tab) {
-  for (int64_t e = threadIdx.x; e < ntab * 16; e += blockDim.x) {
-    const double* v4 = v + (e >> 4) * 4;
-    const int n = static_cast<int>(e & 15);
-    const double a0 = (n & 1) ? v4[0] : 0.0;
-    const double a1 = (n & 2) ? v4[1] : 0.0;
-    const double a2 = (n & 4) ? v4[2] : 0.0;
-    const double a3 = (n & 8) ? v4[3] : 0.0;
-    tab[e] = ((a0 + a1) + a2) + a3;
-  }
-}
-
 // acc[0..3] += sum over the set bits b of word of v[b], from the word's 16
 // tables at byte 2048 W of `tabs` (W a constant, so that the table offsets
 // are immediates of the LDS reads).  Each 32-bit half is masked into two
@@ -74,7 +57,11 @@ __device__ __forceinline__ void nibble_dots(const uint64_t* __restrict__ src, in
   }
 }
 
-// build_tables for a vector of n valid entries (entries from n on read as 0).
+// ntab tables (4 entries each) of a vector of n valid entries (entries from n
+// on read as 0) into tab, consecutive threads on consecutive entries, so the
+// writes of a wavefront cover 512 contiguous bytes (no two lanes in one bank).
+// Entry k of table q is ((v[4q] [k & 1] + v[4q + 1] [k & 2]) + v[4q + 2] [k & 4])
+// + v[4q + 3] [k & 8], an absent term adding 0.0 (exact).
 __device__ __forceinline__ void build_tables_bounded(const double* __restrict__ v, int64_t n, int64_t ntab,
                                                      double* tab) {
   for (int64_t e = threadIdx.x; e < ntab * 16; e += blockDim.x) {

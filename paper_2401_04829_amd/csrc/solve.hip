@@ -118,7 +118,8 @@ Ws carve(gnnshap::Carver& c, const gnnshap_sample_plan* p, const gnnshap_class* 
   const int64_t kr = half - p->random_begin;
   const int64_t nrb = gnnshap::ceil_div(kr, 64);
   w.classes = c.take<gnnshap_class>(p->num_classes > 0 ? p->num_classes : 1);
-  w.T = c.take<uint64_t>((nrb > 0 ? nrb : 1) * M);
+  // the iterative solver's T holds whole blocks of 64 players, block after block
+  w.T = c.take<uint64_t>((nrb > 0 ? nrb : 1) * (iterative(p) ? p->words_per_row * 64 : M));
   if (iterative(p)) {
     w.G = nullptr;
     w.usum = nullptr;
@@ -165,10 +166,10 @@ __device__ __forceinline__ uint64_t transpose_stage(uint64_t x, int lane, uint64
   return (lane & S) ? (((p >> S) & m) | (x & ~m)) : ((x & m) | ((p & m) << S));
 }
 
-// T[rb, j]: transpose 64 rows x 64 players, lane = row in, lane = player out,
-// in six exchange stages (blocks of 32, 16, ..., 1 bits).  One wave per (rb, word).
+// T[rb, j] (row stride ld): transpose 64 rows x 64 players, lane = row in,
+// lane = player out, in six exchange stages (blocks of 32, 16, ..., 1 bits).  One wave per (rb, word).
 __device__ __forceinline__ void transpose_body(const uint64_t* __restrict__ masks, int64_t wpr, int64_t row0,
-                                               int64_t nrows, int64_t M, uint64_t* __restrict__ T, int64_t rb,
+                                               int64_t nrows, int64_t ld, uint64_t* __restrict__ T, int64_t rb,
                                                int64_t w) {
   const int lane = threadIdx.x & 63;
   const int64_t r = rb * 64 + lane;
@@ -180,7 +181,7 @@ __device__ __forceinline__ void transpose_body(const uint64_t* __restrict__ mask
   x = transpose_stage<2>(x, lane, 0x3333333333333333ull);
   x = transpose_stage<1>(x, lane, 0x5555555555555555ull);
   const int64_t j = w * 64 + lane;
-  if (j < M) T[rb * M + j] = x;
+  if (j < ld) T[rb * ld + j] = x;
 }
 
 __global__ void __launch_bounds__(64) k_transpose(const uint64_t* __restrict__ masks, int64_t wpr, int64_t row0,
@@ -196,7 +197,7 @@ __global__ void __launch_bounds__(64) k_transpose(const uint64_t* __restrict__ m
 // rows (whole cache lines per workgroup) and write 8 x 512 contiguous bytes
 // of each copy.
 __global__ void __launch_bounds__(512) k_transpose_blocked(const uint64_t* __restrict__ masks, int64_t wpr,
-                                                           int64_t row0, int64_t nrows, int64_t M,
+                                                           int64_t row0, int64_t nrows,
                                                            uint64_t* __restrict__ T, uint64_t* __restrict__ B) {
   const int64_t rb = blockIdx.x;
   const int64_t w = static_cast<int64_t>(blockIdx.y) * 8 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -204,7 +205,8 @@ __global__ void __launch_bounds__(512) k_transpose_blocked(const uint64_t* __res
   const int lane = threadIdx.x & 63;
   const int64_t r = rb * 64 + lane;
   B[(rb * wpr + w) * 64 + lane] = r < nrows ? masks[(row0 + r) * wpr + w] : 0;
-  transpose_body(masks, wpr, row0, nrows, M, T, rb, w);
+  // (a 64-player T of its own per word column: row stride 64, no other word)
+  transpose_body(masks + w, wpr, row0, nrows, 64, T + w * gridDim.x * 64, rb, 0);
 }
 
 // Counts C[i, j] = sum_rb popcount(T[rb, i] & T[rb, j]) for 64x64 tiles with J >= I,
@@ -542,7 +544,8 @@ __global__ void __launch_bounds__(256) k_rhs_part(const uint64_t* __restrict__ m
 
 // dv[j] = sum over chunks of part[., j] (fixed order); bsum[block] = sum of its dv.
 // The random rows' part of the right-hand side from their bit-transposed
-// copy T (row block rb, player j: bit b = random row 64 rb + b):
+// copy T (row block rb, player j at T[(j / 64 nrb + rb) 64 + j % 64]: bit b =
+// random row 64 rb + b):
 // part[c][j] = sum over the kTabWords row blocks of chunk c of dzr[64 rb + b]
 // over the set bits of T[rb][j], by nibble tables of dzr in LDS (entries from
 // kr on are 0).  Workgroup c nxb + x; wavefront w takes player word 8 x + w,
@@ -563,9 +566,9 @@ __global__ void __launch_bounds__(512) k_rhs_rand(const uint64_t* __restrict__ T
   if (gw >= wpr) return;
   const int64_t j = gw * 64 + lane;
   const bool valid = j < M;
-  const uint64_t* col = T + b0 * M + (valid ? j : 0);
+  const uint64_t* col = T + (gw * nrb + b0) * 64 + lane;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  gnnshap::nibble_dots<gnnshap::kTabWords>(col, M, static_cast<int>(nb), col[0], reinterpret_cast<const char*>(tab), acc);
+  gnnshap::nibble_dots<gnnshap::kTabWords>(col, 64, static_cast<int>(nb), col[0], reinterpret_cast<const char*>(tab), acc);
   if (valid) part[c * M + j] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
@@ -2140,7 +2143,7 @@ int gnnshap::solve_wls_start(const gnnshap_sample_plan* plan, const gnnshap_clas
       GS_TIMED("k_transpose", s);
       k_transpose_blocked<<<dim3(static_cast<unsigned>(gnnshap::ceil_div(kr, 64)),
                                  static_cast<unsigned>(gnnshap::ceil_div(wpr, 8))),
-                            512, 0, s>>>(masks, wpr, rb0, kr, M, w.T, w.cg.blocked);
+                            512, 0, s>>>(masks, wpr, rb0, kr, w.T, w.cg.blocked);
     }
     GS_LAUNCHED();
     // the right-hand side: the enumerated rows from the row-major masks, the

@@ -1,0 +1,73 @@
+"""The iterative solver's products on the matrix cores at the edges of their
+tiles: players and bit rows around 16, 32, 64 and the 64- and 96-wide
+workgroups, with and without sparse rows, and more rows than one fp32
+accumulation segment holds."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sampler
+from paper_2401_04829_amd import _lib as L
+from tests.gpu_util import require_gpu, sample_on_gpu
+from tests.test_gpu_iterative import _game, _oracle_rows, _solve
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    return require_gpu()
+
+
+@pytest.mark.parametrize("M,p", [(2, 2), (15, 400), (16, 130), (17, 4000), (63, 1000), (64, 1026), (65, 1100),
+                                 (95, 1500), (97, 1600), (128, 3000), (129, 2050), (257, 5000), (769, 4200),
+                                 (1537, 9000)])
+def test_products_at_tile_edges(dev, M, p):
+    """phi against the exact solution of the projected normal equations on
+    the oracle's rows.  Bound: the iteration stops at |A psi - b| <= 1e-6 |b|,
+    so |psi - psi*|_2 <= 1e-6 |b| / lambda_min (A on 1-perp), plus the fp32
+    rounding of phi and of f(full) - f(empty)."""
+    print("iterative tiles", M, p, flush=True)
+    plan, classes, masks, _ = sample_on_gpu(M, p, 5, 6)
+    plan.iterative_threshold = 1
+    mb, w = _oracle_rows(plan, masks, 5, 6)
+    v, f0, f1 = _game(M, mb, 3 * M)
+    yv = v(mb).astype(np.float32)
+    fef = np.array([f0, f1], np.float32)
+    phi, info = _solve(dev, plan, classes, masks, torch.tensor(yv, device=dev), torch.tensor(fef, device=dev))
+    delta = float(fef[1]) - float(fef[0])
+    P = mb - mb.mean(1, keepdims=True)
+    A = (P * w[:, None]).T @ P
+    b = P.T @ (w * (yv.astype(np.float64) - float(fef[0]) - delta / M * mb.sum(1)))
+    lam = np.linalg.eigvalsh(A + A.trace() / M * np.full((M, M), 1.0 / M))[0]
+    if info != 0:      # fewer random rows than unknowns: reported, as documented
+        assert info == M + 1 and plan.random_begin == 0 and plan.num_rows // 2 < M - 1
+        return
+    ref = delta / M + np.linalg.lstsq(A + A.trace() / M * np.full((M, M), 1.0 / M), b, rcond=None)[0]
+    bound = 1e-6 * np.linalg.norm(b) / lam + 1e-6 * np.linalg.norm(ref)
+    assert np.linalg.norm(phi - ref) <= bound, (np.linalg.norm(phi - ref), bound)
+
+
+def test_more_rows_than_one_accumulation_segment(dev):
+    """More than 4096 x 8 groups of 256 random rows: the digit sums are
+    emptied between segments.  Against the factored solver on the same rows
+    (exact counts), within the iteration's 1e-6 and the factorisation's fp32."""
+    M, p = 64, 18_400_000
+    print("iterative segments", M, p, flush=True)
+    plan, classes, masks, _ = sample_on_gpu(M, p, 7, 8)
+    kr = plan.num_rows // 2 - plan.random_begin
+    assert kr > 4096 * 8 * 256
+    g = torch.Generator(device=dev)
+    g.manual_seed(9)
+    a = torch.randn(M, generator=g, device=dev)
+    at = torch.arange(64, device=dev)
+    t = torch.cat([((m[:, :1] >> at) & 1).float() @ a for m in masks.split(1 << 20)])
+    y = t + torch.tanh(t)
+    f1 = float(a.sum() + torch.tanh(a.sum()))
+    fef = torch.tensor([0.0, f1], device=dev)
+    want, info = _solve(dev, plan, classes, masks, y, fef)
+    assert info == 0
+    plan.iterative_threshold = 1
+    got, info = _solve(dev, plan, classes, masks, y, fef)
+    assert info == 0
+    assert np.abs(got - want).max() <= 1e-4 * np.abs(want).max()
