@@ -486,8 +486,8 @@ int gnnshap_gat_explain_batch_workspace(const gnnshap_subgraph* sgs, const gnnsh
                                         const gnnshap_gat* m, size_t* bytes);
 
 /* gnnshap_explain_batch for the two-layer GAT (App. E): sampling, the
- * coalition values of gnnshap_gat_eval_coalitions for every target (one
- * launch sequence per target, in the batch's order) and the least squares,
+ * coalition values of gnnshap_gat_eval_coalitions (each step one launch for
+ * all targets) and the least squares,
  * with the same arguments, outputs, layout, streams and blocking as
  * gnnshap_explain_batch (m->XW1 replaces X).  Every output equals, bit for
  * bit, what the single-target calls give. */

@@ -68,6 +68,53 @@ int launch_eval_batch(const EvalJob* jobs, int64_t n, const EvalModel& md, int64
                       int64_t max_n1, int64_t max_wpr, int64_t max_k, int64_t rows_jobs, size_t rows_lds,
                       hipStream_t s);
 
+// ---- evaluation (two-layer GAT) -----------------------------------------------------------
+// A target's subgraph, the model and the workspace arrays on the device.
+struct GatDev {
+  // subgraph
+  const int32_t* gid;
+  const int32_t* dst_ptr;
+  const int32_t* esrc;
+  int64_t n_nodes, n1, M, indeg_v;
+  // model
+  int32_t H, F, nf, C;
+  const float* XW1;
+  const float* att_src1;
+  const float* att_dst1;
+  const float* b1;
+  const float* W2;
+  const float* att_src2;
+  const float* att_dst2;
+  const float* b2;
+  float slope;
+  // workspace
+  float* z1;     // n_nodes x nf
+  float* ss1;    // n_nodes x H
+  float* sd1;    // n1 x H
+  float* w;      // M x H
+  float* wself;  // n1 x H
+  float* u2s;    // nf
+  float* u2d;    // nf
+  int32_t* cls;  // explained class
+};
+struct GatJob {
+  GatDev g;
+  const uint64_t* masks;
+  int64_t k, wpr;
+  float* fef;
+  float* y;
+  int32_t* class_out;
+  float* scratch;      // 2 C: f(empty), then f(E_c) of every class
+  int32_t target_class;
+};
+// Checks the arguments of gnnshap_gat_eval_coalitions and fills the target's job.
+int gat_fill_job(const gnnshap_subgraph* sg, const gnnshap_gat* m, int32_t target_class, const uint64_t* masks,
+                 int64_t k, int64_t words_per_row, float* y, float* f_empty_full, int32_t* class_out, void* ws,
+                 size_t ws_bytes, GatJob* job);
+// The coalition values of n targets of one model (max_*: the largest of the jobs).
+int launch_gat_batch(const GatJob* jobs, int64_t n, const gnnshap_gat* m, int64_t max_nodes, int64_t max_ndst,
+                     int64_t max_k, hipStream_t s);
+
 // ---- least squares (one-workgroup systems) -----------------------------------------------
 struct SolveJob {
   const uint64_t* masks;

@@ -267,16 +267,18 @@ struct BatchWs {
   gnnshap::EvalJob* eval;
   gnnshap::SolveJob* solve;
   gnnshap::MbJob* mb;
+  gnnshap::GatJob* gat;
   std::vector<char*> eval_slice, solve_slice;
 };
 
-BatchWs carve(gnnshap::Carver& c, const Layout& L) {
+BatchWs carve(gnnshap::Carver& c, const Layout& L, Model m) {
   BatchWs b;
   b.classes = c.take<gnnshap_class>(L.classes);
   b.sample = c.take<gnnshap::SampleJob>(L.n);
   b.eval = c.take<gnnshap::EvalJob>(L.n);
   b.solve = c.take<gnnshap::SolveJob>(L.n);
   b.mb = c.take<gnnshap::MbJob>(L.n);
+  b.gat = c.take<gnnshap::GatJob>(m.gat ? L.n : 0);
   b.eval_slice.resize(L.n);
   b.solve_slice.resize(L.n);
   for (int64_t t = 0; t < L.n; ++t) b.eval_slice[t] = c.take<char>(L.eval_bytes[t]);
@@ -311,7 +313,7 @@ int batch_workspace(const gnnshap_subgraph* sgs, const gnnshap_sample_plan* plan
   Layout L;
   if (int st = make_layout(sgs, plans, n, m, &L)) return st;
   gnnshap::Carver c(nullptr);
-  carve(c, L);
+  carve(c, L, m);
   *bytes = c.bytes();
   return GNNSHAP_OK;
 }
@@ -328,10 +330,10 @@ int explain_batch_impl(const gnnshap_subgraph* sgs, const gnnshap_sample_plan* p
   if (!classes || !masks || !weights || !y || !f_empty_full || !phi || !info || !ws)
     return gnnshap::fail(GNNSHAP_EINVAL, "null argument");
   gnnshap::Carver need(nullptr);
-  carve(need, L);
+  carve(need, L, mdl);
   if (ws_bytes < need.bytes()) return gnnshap::fail(GNNSHAP_ECAPACITY, "batch workspace needs %zu bytes", need.bytes());
   gnnshap::Carver cv(ws);
-  const BatchWs b = carve(cv, L);
+  const BatchWs b = carve(cv, L, mdl);
   hipStream_t s = static_cast<hipStream_t>(stream);
   for (int64_t t = 0; t < n; ++t) {
     if (plans[t].num_players > 131072)
@@ -355,11 +357,12 @@ int explain_batch_impl(const gnnshap_subgraph* sgs, const gnnshap_sample_plan* p
   int64_t bound[3];
   split_groups(plans, n, &order, bound);
 
-  // The class tables and the four job tables (in group order) sit at the
+  // The class tables and the job tables (in group order) sit at the
   // front of the workspace; they are assembled in a host image of that range
   // and copied in one transfer before the first launch.
   char* const base = static_cast<char*>(ws);
-  const size_t front = static_cast<size_t>(reinterpret_cast<char*>(b.mb + n) - base);
+  const size_t front = static_cast<size_t>(
+      (mdl.gat ? reinterpret_cast<char*>(b.gat + n) : reinterpret_cast<char*>(b.mb + n)) - base);
   gnnshap::HostStage* stage = gnnshap::host_stage(front, 0);
   if (!stage) return gnnshap::fail(GNNSHAP_EHIP, "page-locked staging allocation failed");
   char* const image = stage->buf;
@@ -370,6 +373,8 @@ int explain_batch_impl(const gnnshap_subgraph* sgs, const gnnshap_sample_plan* p
   gnnshap::EvalJob* ej = reinterpret_cast<gnnshap::EvalJob*>(at(b.eval));
   gnnshap::SolveJob* vj = reinterpret_cast<gnnshap::SolveJob*>(at(b.solve));
   gnnshap::MbJob* mj = reinterpret_cast<gnnshap::MbJob*>(at(b.mb));
+
+  gnnshap::GatJob* gj = mdl.gat ? reinterpret_cast<gnnshap::GatJob*>(at(b.gat)) : nullptr;
 
   struct Group {
     int64_t begin = 0, end = 0;                      // range of order[]
@@ -435,6 +440,16 @@ int explain_batch_impl(const gnnshap_subgraph* sgs, const gnnshap_sample_plan* p
         G.max_ndst = std::max(G.max_ndst, J.n_dst);
         G.max_n1 = std::max(G.max_n1, J.n1);
       }
+    }
+    for (int64_t j = G.begin; j < G.end && gj; ++j) {
+      const int64_t t = order[j];
+      if (int st = gnnshap::gat_fill_job(&sgs[t], mdl.gat, target_class, masks + L.mask_off[t], plans[t].num_rows,
+                                         plans[t].words_per_row, y + L.row_off[t], f_empty_full + 2 * t,
+                                         class_out ? class_out + t : nullptr, b.eval_slice[t], L.eval_bytes[t],
+                                         &gj[j]))
+        return st;
+      G.max_nodes = std::max(G.max_nodes, sgs[t].num_nodes);
+      G.max_ndst = std::max(G.max_ndst, sgs[t].num_dst);
     }
     // 3. least-squares jobs: one-workgroup systems batched, the rest one by one
     G.solve_begin = nv;
@@ -668,6 +683,12 @@ int explain_batch_impl(const gnnshap_subgraph* sgs, const gnnshap_sample_plan* p
         const Group& G = grp[gi];
         if (G.end == G.begin) return GNNSHAP_OK;
         int st_eval = GNNSHAP_EUNSUPPORTED;
+        if (mdl.gat) {
+          if (int st = gnnshap::launch_gat_batch(b.gat + G.begin, G.end - G.begin, mdl.gat, G.max_nodes, G.max_ndst,
+                                                 G.max_k, gs[gi]))
+            return st;
+          st_eval = GNNSHAP_OK;
+        }
         if (G.eval_all) {
           const gnnshap::EvalModel md{model->XW1, model->b ? model->b[0] : nullptr, model->W[1],
                                       model->b ? model->b[1] : nullptr, model->dims[1], model->dims[2], target_class};
@@ -675,27 +696,20 @@ int explain_batch_impl(const gnnshap_subgraph* sgs, const gnnshap_sample_plan* p
                                                G.max_wpr, G.max_k, G.rows_jobs, G.rows_lds, gs[gi]);
           if (st_eval != GNNSHAP_OK && st_eval != GNNSHAP_EUNSUPPORTED) return st_eval;
           gnnshap::clear_error();
-          if (st_eval == GNNSHAP_OK) {
-            GS_HIP(hipEventRecord(ev_pool[G.begin], gs[gi]));
-            for (int64_t j = G.begin; j < G.end; ++j) evaluated[order[j]] = ev_pool[G.begin];
-          }
+        }
+        if (st_eval == GNNSHAP_OK) {
+          GS_HIP(hipEventRecord(ev_pool[G.begin], gs[gi]));
+          for (int64_t j = G.begin; j < G.end; ++j) evaluated[order[j]] = ev_pool[G.begin];
         }
         if (st_eval != GNNSHAP_OK) {
           for (int64_t j = G.begin; j < G.end; ++j) {
             const int64_t t = order[j];
             const gnnshap_sample_plan& p = plans[t];
-            if (model) {
-              if (int st = gnnshap::eval_coalitions_impl(&sgs[t], model, X, target_class, masks + L.mask_off[t],
-                                                         p.num_rows, p.words_per_row, y + L.row_off[t],
-                                                         f_empty_full + 2 * t, class_out ? class_out + t : nullptr,
-                                                         b.eval_slice[t], L.eval_bytes[t], gs[gi], true))
-                return st;
-            } else if (int st = gnnshap_gat_eval_coalitions(&sgs[t], mdl.gat, target_class, masks + L.mask_off[t],
-                                                            p.num_rows, p.words_per_row, y + L.row_off[t],
-                                                            f_empty_full + 2 * t, class_out ? class_out + t : nullptr,
-                                                            b.eval_slice[t], L.eval_bytes[t], gs[gi])) {
+            if (int st = gnnshap::eval_coalitions_impl(&sgs[t], model, X, target_class, masks + L.mask_off[t],
+                                                       p.num_rows, p.words_per_row, y + L.row_off[t],
+                                                       f_empty_full + 2 * t, class_out ? class_out + t : nullptr,
+                                                       b.eval_slice[t], L.eval_bytes[t], gs[gi], true))
               return st;
-            }
             GS_HIP(hipEventRecord(ev_pool[j], gs[gi]));
             evaluated[t] = ev_pool[j];
             if (rest_pos[t] >= 0)

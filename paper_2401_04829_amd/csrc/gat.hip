@@ -23,7 +23,7 @@
 #include <algorithm>
 #include <cmath>
 
-#include "common.h"
+#include "batch.h"
 
 namespace {
 
@@ -31,33 +31,8 @@ constexpr int kGatMaxFeat = 256;              // heads * head_dim
 constexpr int kGatSlots = kGatMaxFeat / 64;   // features per lane
 constexpr int kRowsWaves = 4;                 // coalitions per workgroup of the per-coalition kernel
 
-struct GatDev {
-  // subgraph
-  const int32_t* gid;
-  const int32_t* dst_ptr;
-  const int32_t* esrc;
-  int64_t n_nodes, n1, M, indeg_v;
-  // model
-  int32_t H, F, nf, C;
-  const float* XW1;
-  const float* att_src1;
-  const float* att_dst1;
-  const float* b1;
-  const float* W2;
-  const float* att_src2;
-  const float* att_dst2;
-  const float* b2;
-  float slope;
-  // workspace
-  float* z1;     // n_nodes x nf
-  float* ss1;    // n_nodes x H
-  float* sd1;    // n1 x H
-  float* w;      // M x H
-  float* wself;  // n1 x H
-  float* u2s;    // nf
-  float* u2d;    // nf
-  int32_t* cls;  // explained class
-};
+using gnnshap::GatDev;
+using gnnshap::GatJob;
 
 __device__ __forceinline__ float leaky(float x, float slope) { return x > 0.f ? x : slope * x; }
 __device__ __forceinline__ float elu(float x) { return x > 0.f ? x : expm1f(x); }
@@ -70,7 +45,7 @@ __device__ __forceinline__ float wave_sum_f(float v) {
 
 // z1 rows of the subgraph's nodes and the per-head attention terms s (every
 // node) and d (nodes of H_1).  Grid-stride over (node, feature) and (node, head).
-__global__ void __launch_bounds__(256) k_gat_gather(GatDev g) {
+__device__ __forceinline__ void gather_body(const GatDev& g) {
   const int64_t tid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   for (int64_t i = tid; i < g.n_nodes * g.nf; i += stride) {
@@ -93,7 +68,7 @@ __global__ void __launch_bounds__(256) k_gat_gather(GatDev g) {
 // Unnormalised layer-1 weights of every candidate edge (players into H_1 and
 // the self loops), shifted by each destination's largest logit; the layer-2
 // attention vectors folded through W_2.
-__global__ void __launch_bounds__(256) k_gat_weights(GatDev g) {
+__device__ __forceinline__ void weights_body(const GatDev& g) {
   const int64_t tid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   for (int64_t i = tid; i < g.n1 * g.H; i += stride) {
@@ -101,10 +76,29 @@ __global__ void __launch_bounds__(256) k_gat_weights(GatDev g) {
     const float d = g.sd1[i];
     const float lself = leaky(g.ss1[x * g.H + h] + d, g.slope);
     float m = lself;
-    for (int32_t p = g.dst_ptr[x]; p < g.dst_ptr[x + 1]; ++p)
-      m = fmaxf(m, leaky(g.ss1[static_cast<int64_t>(g.esrc[p]) * g.H + h] + d, g.slope));
-    for (int32_t p = g.dst_ptr[x]; p < g.dst_ptr[x + 1]; ++p)
-      g.w[static_cast<int64_t>(p) * g.H + h] = expf(leaky(g.ss1[static_cast<int64_t>(g.esrc[p]) * g.H + h] + d, g.slope) - m);
+    // eight edges at a time, their loads in flight together
+    const int32_t p0 = g.dst_ptr[x], p1 = g.dst_ptr[x + 1];
+    for (int32_t p = p0; p < p1; p += 8) {
+      int64_t u[8];
+      float l[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) u[q] = g.esrc[p + q < p1 ? p + q : p1 - 1];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) l[q] = g.ss1[u[q] * g.H + h];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) m = fmaxf(m, leaky(l[q] + d, g.slope));
+    }
+    for (int32_t p = p0; p < p1; p += 8) {
+      int64_t u[8];
+      float l[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) u[q] = g.esrc[p + q < p1 ? p + q : p1 - 1];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) l[q] = g.ss1[u[q] * g.H + h];
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (p + q < p1) g.w[static_cast<int64_t>(p + q) * g.H + h] = expf(leaky(l[q] + d, g.slope) - m);
+    }
     g.wself[i] = expf(lself - m);
   }
   for (int64_t f = tid; f < g.nf; f += stride) {
@@ -199,52 +193,268 @@ __device__ float value_at_v(const GatDev& g, int32_t c, Present present) {
   return acc / sum + g.b2[c];
 }
 
-// f(empty) and f(E_c) for every class (one wave per class and end
-// coalition), then the explained class and f_empty_full.  One workgroup.
-__global__ void __launch_bounds__(1024) k_gat_ends(GatDev g, int32_t target_class, float* fef, int32_t* class_out,
-                                                  float* scratch) {
-  const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int64_t t = wv; t < 2 * g.C; t += nw) {
-    const int32_t c = static_cast<int32_t>(t % g.C);
-    const bool full = t >= g.C;
-    const float v = full ? value_at_v(g, c, [](int32_t) { return true; })
-                         : value_at_v(g, c, [](int32_t) { return false; });
-    if ((threadIdx.x & 63) == 0) scratch[t] = v;
+// f(empty) and f(E_c) for every class, then the explained class and
+// f_empty_full.  One workgroup of 16 wavefronts per target: under E_c they
+// share v's in-neighbours, each accumulating its own online softmax of their
+// layer-1 rows; the layer-2 output of class c is then the softmax-weighted
+// row times W_2[:, c] (one row sum instead of one pass over the neighbours
+// per class: 89 us per Cora-shaped target before).
+constexpr int kEndsWaves = 16;
+
+__device__ __forceinline__ void ends_body(const GatJob& J) {
+  __shared__ float rows[kEndsWaves + 1][kGatMaxFeat];   // the wavefronts' sums; the last one: the row under the empty coalition
+  __shared__ float mxs[kEndsWaves], sums[kEndsWaves];
+  const GatDev& g = J.g;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  float o[kGatSlots], acc[kGatSlots];
+  if (wv == 0) {
+    layer1(g, 0, [](int32_t) { return false; }, o);
+#pragma unroll
+    for (int i = 0; i < kGatSlots; ++i)
+      if (lane + 64 * i < g.nf) rows[kEndsWaves][lane + 64 * i] = o[i];
+  }
+  const auto all = [](int32_t) { return true; };
+  layer1(g, 0, all, o);
+  const float sdv = dot_nf(g, o, g.u2d, 1);
+  float mx = -INFINITY, sum = 0.f;
+  if (wv == 0) {
+    mx = leaky(dot_nf(g, o, g.u2s, 1) + sdv, g.slope);
+    sum = 1.f;
+#pragma unroll
+    for (int i = 0; i < kGatSlots; ++i) acc[i] = o[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < kGatSlots; ++i) acc[i] = 0.f;
+  }
+  for (int64_t e = wv; e < g.indeg_v; e += kEndsWaves) {
+    layer1(g, g.esrc[e], all, o);
+    const float lx = leaky(dot_nf(g, o, g.u2s, 1) + sdv, g.slope);
+    const float mn = fmaxf(mx, lx);
+    const float r = mx == mn ? 1.f : expf(mx - mn), wx = lx == mn ? 1.f : expf(lx - mn);
+    sum = sum * r + wx;
+#pragma unroll
+    for (int i = 0; i < kGatSlots; ++i) acc[i] = acc[i] * r + wx * o[i];
+    mx = mn;
+  }
+#pragma unroll
+  for (int i = 0; i < kGatSlots; ++i)
+    if (lane + 64 * i < g.nf) rows[wv][lane + 64 * i] = acc[i];
+  if (lane == 0) {
+    mxs[wv] = mx;
+    sums[wv] = sum;
+  }
+  __syncthreads();
+  float top = mxs[0];
+  for (int w = 1; w < kEndsWaves; ++w) top = fmaxf(top, mxs[w]);
+  float total = 0.f;
+  float scale[kEndsWaves];
+#pragma unroll
+  for (int w = 0; w < kEndsWaves; ++w) {
+    scale[w] = sums[w] > 0.f ? expf(mxs[w] - top) : 0.f;   // (a wavefront without neighbours has no sum)
+    total += sums[w] * scale[w];
+  }
+#pragma unroll
+  for (int i = 0; i < kGatSlots; ++i) {
+    const int f = lane + 64 * i;
+    float v = 0.f;
+    if (f < g.nf) {
+#pragma unroll
+      for (int w = 0; w < kEndsWaves; ++w) v += rows[w][f] * scale[w];
+    }
+    acc[i] = v / total;
+    o[i] = f < g.nf ? rows[kEndsWaves][f] : 0.f;
+  }
+  for (int32_t c = wv; c < g.C; c += kEndsWaves) {
+    const float fe = dot_nf(g, o, g.W2 + c, g.C) + g.b2[c], ff = dot_nf(g, acc, g.W2 + c, g.C) + g.b2[c];
+    if (lane == 0) {
+      J.scratch[c] = fe;
+      J.scratch[g.C + c] = ff;
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    int32_t c = target_class;
+    int32_t c = J.target_class;
     if (c < 0) {
       c = 0;
       for (int32_t i = 1; i < g.C; ++i)
-        if (scratch[g.C + i] > scratch[g.C + c]) c = i;
+        if (J.scratch[g.C + i] > J.scratch[g.C + c]) c = i;
     }
     *g.cls = c;
-    fef[0] = scratch[c];
-    fef[1] = scratch[g.C + c];
-    if (class_out) *class_out = c;
+    J.fef[0] = J.scratch[c];
+    J.fef[1] = J.scratch[g.C + c];
+    if (J.class_out) *J.class_out = c;
   }
 }
 
-// y[b] for coalition b: one wave per coalition.
-__global__ void __launch_bounds__(kRowsWaves * 64) k_gat_rows(GatDev g, const uint64_t* __restrict__ masks,
-                                                              int64_t k, int64_t wpr, const float* __restrict__ fef,
-                                                              float* __restrict__ y) {
-  const int64_t b = static_cast<int64_t>(blockIdx.x) * kRowsWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (b >= k) return;
-  const uint64_t* row = masks + b * wpr;
-  auto present = [row](int32_t p) { return ((row[p >> 6] >> (p & 63)) & 1ull) != 0; };
+// Whether any in-edge of v is in a coalition.
+__device__ __forceinline__ bool reaches_v(const GatDev& g, const uint64_t* row) {
   bool live = false;
   for (int64_t w = 0; w * 64 < g.indeg_v; ++w) {
     const int64_t n = g.indeg_v - w * 64;
-    const uint64_t m = n >= 64 ? ~0ull : ((1ull << n) - 1ull);
-    live |= (row[w] & m) != 0;
+    live |= (row[w] & (n >= 64 ? ~0ull : ((1ull << n) - 1ull))) != 0;
   }
-  float v;
-  if (!live) v = fef[0];   // no in-edge of v: the target alone (Sec. 3.4.1)
-  else v = value_at_v(g, *g.cls, present);
-  if ((threadIdx.x & 63) == 0) y[b] = v;
+  return live;
 }
+
+// y[b] for coalition b: one wave per coalition, features over the lanes (head
+// widths that are no multiple of 16).
+__device__ __forceinline__ void rows_body(const GatJob& J) {
+  const GatDev& g = J.g;
+  const int64_t b = static_cast<int64_t>(blockIdx.x) * kRowsWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (b >= J.k) return;
+  const uint64_t* row = J.masks + b * J.wpr;
+  auto present = [row](int32_t p) { return ((row[p >> 6] >> (p & 63)) & 1ull) != 0; };
+  float v;
+  if (!reaches_v(g, row)) v = J.fef[0];   // no in-edge of v: the target alone (Sec. 3.4.1)
+  else v = value_at_v(g, *g.cls, present);
+  if ((threadIdx.x & 63) == 0) J.y[b] = v;
+}
+
+// y[b] of 64 coalitions per workgroup, one per lane (head widths that are
+// multiples of 16): wavefront w holds features 16 w .. 16 w + 15 of every
+// lane's layer-1 row, which belong to one head.  An edge's weight and source
+// features are the same for all lanes and stay in scalar registers, and its
+// 17 multiply-adds run under the lanes whose coalition holds it, in edge
+// order as above; so 64 coalitions share every load and the loop control,
+// where one wavefront per coalition spent ~15 instructions per edge on one
+// coalition.  Bound by VALU issue, most of it the ELU and the division of
+// the rows.  40 Cora-shaped targets x 10,000 coalitions: 3.2 ms of kernel
+// time one target after the other before, 0.76 ms for the larger group now
+// (0.97 ms with the edges' values in vector registers).
+constexpr int kSlice = 16;
+constexpr int kEdges = 4;
+constexpr int kMaxSlices = kGatMaxFeat / kSlice;
+
+// Arrays that no wavefront of the kernel writes, read at addresses that are
+// the same for all lanes: through the constant address space they are loaded
+// by scalar loads, also behind barriers.
+template <class T>
+using Uniform = const __attribute__((address_space(4))) T*;
+template <class T>
+__device__ __forceinline__ Uniform<T> uniform(const T* p) {
+  return (Uniform<T>)(reinterpret_cast<uintptr_t>(p));
+}
+
+__device__ __forceinline__ void rows_lanes_body(const GatJob& J) {
+  __shared__ float part[2][2][kMaxSlices][64];
+  const GatDev& g = J.g;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), slices = blockDim.x >> 6;
+  const int64_t tile = blockIdx.x;
+  if (tile * 64 >= J.k) return;
+  const int64_t b = tile * 64 + lane;
+  const uint64_t* row = J.masks + (b < J.k ? b : J.k - 1) * J.wpr;
+  const bool live = reaches_v(g, row);
+  const float f_empty = J.fef[0];
+  if (!__any(live)) {
+    if (wave == 0 && b < J.k) J.y[b] = f_empty;
+    return;   // the same outcome in every wavefront
+  }
+  const int32_t c = *g.cls;
+  const int f0 = wave * kSlice, h = f0 / g.F;
+  const auto z1 = uniform(g.z1), w1 = uniform(g.w), wself = uniform(g.wself), b1 = uniform(g.b1), u2s = uniform(g.u2s),
+             u2d = uniform(g.u2d), W2 = uniform(g.W2);
+  const auto esrc = uniform(g.esrc), dst_ptr = uniform(g.dst_ptr);
+  float mx = 0.f, sum = 0.f, acc = 0.f, sdv = 0.f;
+  uint64_t word_e = 0;
+  int buf = 0;   // the sums of one node are written while those of the node before are read
+  for (int64_t i = -1; i < g.indeg_v; ++i) {   // v itself, then its in-neighbours
+    bool on = live;
+    int64_t x = 0;
+    if (i >= 0) {
+      if ((i & 63) == 0) word_e = row[i >> 6];
+      on = live && ((word_e >> (i & 63)) & 1ull);
+      if (!__any(on)) continue;
+      x = esrc[i];
+    }
+    float num[kSlice];
+    float den = wself[x * g.H + h];
+    const auto z = z1 + x * g.nf + f0;
+#pragma unroll
+    for (int q = 0; q < kSlice; ++q) num[q] = den * z[q];
+    const int32_t p0 = dst_ptr[x], p1 = dst_ptr[x + 1];
+    uint64_t word = p0 < p1 ? row[p0 >> 6] : 0;
+    // four edges at a time, so that their (scalar) loads overlap
+    for (int32_t p = p0; p < p1; p += kEdges) {
+      float wp[kEdges];
+      Uniform<float> zu[kEdges];
+#pragma unroll
+      for (int k = 0; k < kEdges; ++k) {
+        const int32_t pk = p + k < p1 ? p + k : p1 - 1;
+        wp[k] = w1[static_cast<int64_t>(pk) * g.H + h];
+        zu[k] = z1 + static_cast<int64_t>(esrc[pk]) * g.nf + f0;
+      }
+#pragma unroll
+      for (int k = 0; k < kEdges; ++k) {
+        if (p + k >= p1) break;
+        if (((p + k) & 63) == 0) word = row[(p + k) >> 6];
+        if (on && ((word >> ((p + k) & 63)) & 1ull)) {
+          den += wp[k];
+#pragma unroll
+          for (int q = 0; q < kSlice; ++q) num[q] += wp[k] * zu[k][q];
+        }
+      }
+    }
+    float sl = 0.f, sy = 0.f, sd = 0.f;
+#pragma unroll
+    for (int q = 0; q < kSlice; ++q) {
+      const int f = f0 + q;
+      const float o = elu(num[q] / den + b1[f]);
+      sl += o * u2s[f];
+      sy += o * W2[static_cast<int64_t>(f) * g.C + c];
+      if (i < 0) sd += o * u2d[f];
+    }
+    buf ^= 1;
+    part[buf][0][wave][lane] = sl;
+    part[buf][1][wave][lane] = sy;
+    __syncthreads();
+    if (wave == 0) {
+      sl = part[buf][0][0][lane];
+      sy = part[buf][1][0][lane];
+      for (int w = 1; w < slices; ++w) {
+        sl += part[buf][0][w][lane];
+        sy += part[buf][1][w][lane];
+      }
+    }
+    if (i < 0) {
+      part[buf ^ 1][0][wave][lane] = sd;
+      __syncthreads();
+      if (wave == 0) {
+        sdv = part[buf ^ 1][0][0][lane];
+        for (int w = 1; w < slices; ++w) sdv += part[buf ^ 1][0][w][lane];
+        mx = leaky(sl + sdv, g.slope);
+        sum = 1.f;
+        acc = sy;
+      }
+      __syncthreads();
+    } else if (wave == 0 && on) {
+      const float lx = leaky(sl + sdv, g.slope);
+      if (lx > mx) {
+        const float r = expf(mx - lx);
+        sum = sum * r + 1.f;
+        acc = acc * r + sy;
+        mx = lx;
+      } else {
+        const float wx = expf(lx - mx);
+        sum += wx;
+        acc += wx * sy;
+      }
+    }
+  }
+  if (wave == 0 && b < J.k) J.y[b] = live ? acc / sum + g.b2[c] : f_empty;
+}
+
+// One target (its job by value) and a batch (job blockIdx.y of a table).
+__global__ void __launch_bounds__(256) k_gat_gather(GatJob J) { gather_body(J.g); }
+__global__ void __launch_bounds__(256) k_gat_gather_batch(const GatJob* __restrict__ jobs) { gather_body(jobs[blockIdx.y].g); }
+__global__ void __launch_bounds__(256) k_gat_weights(GatJob J) { weights_body(J.g); }
+__global__ void __launch_bounds__(256) k_gat_weights_batch(const GatJob* __restrict__ jobs) { weights_body(jobs[blockIdx.y].g); }
+__global__ void __launch_bounds__(kEndsWaves * 64) k_gat_ends(GatJob J) { ends_body(J); }
+__global__ void __launch_bounds__(kEndsWaves * 64) k_gat_ends_batch(const GatJob* __restrict__ jobs) { ends_body(jobs[blockIdx.y]); }
+__global__ void __launch_bounds__(kRowsWaves * 64) k_gat_rows(GatJob J) { rows_body(J); }
+__global__ void __launch_bounds__(kRowsWaves * 64) k_gat_rows_batch(const GatJob* __restrict__ jobs) { rows_body(jobs[blockIdx.y]); }
+__global__ void __launch_bounds__(kMaxSlices * 64) k_gat_rows_lanes(GatJob J) { rows_lanes_body(J); }
+__global__ void __launch_bounds__(kMaxSlices * 64) k_gat_rows_lanes_batch(const GatJob* __restrict__ jobs) { rows_lanes_body(jobs[blockIdx.y]); }
 
 struct GatWs {
   float *z1, *ss1, *sd1, *w, *wself, *u2s, *u2d, *scratch;
@@ -295,12 +505,9 @@ extern "C" int gnnshap_gat_eval_workspace(const gnnshap_subgraph* sg, const gnns
   return GNNSHAP_OK;
 }
 
-extern "C" int gnnshap_gat_eval_coalitions(const gnnshap_subgraph* sg, const gnnshap_gat* m, int32_t target_class,
-                                           const uint64_t* masks, int64_t k, int64_t words_per_row, float* y,
-                                           float* f_empty_full, int32_t* class_out, void* ws, size_t ws_bytes,
-                                           void* stream) {
-  GS_TRY_BEGIN
-  gnnshap::clear_error();
+int gnnshap::gat_fill_job(const gnnshap_subgraph* sg, const gnnshap_gat* m, int32_t target_class,
+                          const uint64_t* masks, int64_t k, int64_t words_per_row, float* y, float* f_empty_full,
+                          int32_t* class_out, void* ws, size_t ws_bytes, GatJob* job) {
   if (int st = gat_check(sg, m)) return st;
   if (!masks || !y || !f_empty_full || !ws || k < 1) return gnnshap::fail(GNNSHAP_EINVAL, "null argument or k < 1");
   if (!sg->node_gid || !sg->dst_ptr || !sg->edge_src) return gnnshap::fail(GNNSHAP_EINVAL, "null subgraph arrays");
@@ -311,10 +518,11 @@ extern "C" int gnnshap_gat_eval_coalitions(const gnnshap_subgraph* sg, const gnn
   gnnshap::Carver need(nullptr);
   gat_carve(need, sg, m);
   if (ws_bytes < need.bytes()) return gnnshap::fail(GNNSHAP_ECAPACITY, "GAT workspace needs %zu bytes", need.bytes());
+  if (!m->b1 || !m->b2) return gnnshap::fail(GNNSHAP_EINVAL, "the GAT needs both biases (zero arrays for none)");
   gnnshap::Carver cv(ws);
   const GatWs w = gat_carve(cv, sg, m);
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  GatDev g{};
+  *job = GatJob{};
+  GatDev& g = job->g;
   g.gid = sg->node_gid;
   g.dst_ptr = sg->dst_ptr;
   g.esrc = sg->edge_src;
@@ -344,20 +552,74 @@ extern "C" int gnnshap_gat_eval_coalitions(const gnnshap_subgraph* sg, const gnn
   g.u2s = w.u2s;
   g.u2d = w.u2d;
   g.cls = w.cls;
-  if (!g.b1 || !g.b2) return gnnshap::fail(GNNSHAP_EINVAL, "the GAT needs both biases (zero arrays for none)");
-  k_gat_gather<<<gnnshap::grid_for(sg->num_nodes * g.nf, 256, 1024), 256, 0, s>>>(g);
+  job->masks = masks;
+  job->k = k;
+  job->wpr = words_per_row;
+  job->fef = f_empty_full;
+  job->y = y;
+  job->class_out = class_out;
+  job->scratch = w.scratch;
+  job->target_class = target_class;
+  return GNNSHAP_OK;
+}
+
+// Head widths that are multiples of 16 take the kernel with one coalition per
+// lane, whose wavefronts hold 16 features of one head each.
+static bool takes_lanes(const gnnshap_gat* m) { return m->head_dim % kSlice == 0; }
+
+int gnnshap::launch_gat_batch(const GatJob* jobs, int64_t n, const gnnshap_gat* m, int64_t max_nodes, int64_t max_ndst,
+                              int64_t max_k, hipStream_t s) {
+  if (n < 1) return GNNSHAP_OK;
+  const unsigned nn = static_cast<unsigned>(n);
+  const int64_t nf = static_cast<int64_t>(m->heads) * m->head_dim;
+  k_gat_gather_batch<<<dim3(grid_for(max_nodes * nf, 256, 1024), nn), 256, 0, s>>>(jobs);
   GS_LAUNCHED();
-  k_gat_weights<<<gnnshap::grid_for(std::max<int64_t>(sg->num_dst * g.H, g.nf), 256, 256), 256, 0, s>>>(g);
+  k_gat_weights_batch<<<dim3(grid_for(std::max<int64_t>(max_ndst * m->heads, nf), 256, 256), nn), 256, 0, s>>>(jobs);
+  GS_LAUNCHED();
+  {
+    GS_TIMED("k_gat_ends_batch", s);
+    k_gat_ends_batch<<<dim3(1, nn), kEndsWaves * 64, 0, s>>>(jobs);
+  }
+  GS_LAUNCHED();
+  {
+    GS_TIMED("k_gat_rows_batch", s);
+    if (takes_lanes(m))
+      k_gat_rows_lanes_batch<<<dim3(static_cast<unsigned>(ceil_div(max_k, 64)), nn),
+                               static_cast<unsigned>(nf / kSlice * 64), 0, s>>>(jobs);
+    else
+      k_gat_rows_batch<<<dim3(static_cast<unsigned>(ceil_div(max_k, kRowsWaves)), nn), kRowsWaves * 64, 0, s>>>(jobs);
+  }
+  GS_LAUNCHED();
+  return GNNSHAP_OK;
+}
+
+extern "C" int gnnshap_gat_eval_coalitions(const gnnshap_subgraph* sg, const gnnshap_gat* m, int32_t target_class,
+                                           const uint64_t* masks, int64_t k, int64_t words_per_row, float* y,
+                                           float* f_empty_full, int32_t* class_out, void* ws, size_t ws_bytes,
+                                           void* stream) {
+  GS_TRY_BEGIN
+  gnnshap::clear_error();
+  GatJob J;
+  if (int st = gnnshap::gat_fill_job(sg, m, target_class, masks, k, words_per_row, y, f_empty_full, class_out, ws,
+                                     ws_bytes, &J))
+    return st;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  k_gat_gather<<<gnnshap::grid_for(sg->num_nodes * J.g.nf, 256, 1024), 256, 0, s>>>(J);
+  GS_LAUNCHED();
+  k_gat_weights<<<gnnshap::grid_for(std::max<int64_t>(sg->num_dst * J.g.H, J.g.nf), 256, 256), 256, 0, s>>>(J);
   GS_LAUNCHED();
   {
     GS_TIMED("k_gat_ends", s);
-    k_gat_ends<<<1, 1024, 0, s>>>(g, target_class, f_empty_full, class_out, w.scratch);
+    k_gat_ends<<<1, kEndsWaves * 64, 0, s>>>(J);
   }
   GS_LAUNCHED();
   {
     GS_TIMED("k_gat_rows", s);
-    k_gat_rows<<<static_cast<unsigned>(gnnshap::ceil_div(k, kRowsWaves)), kRowsWaves * 64, 0, s>>>(
-        g, masks, k, words_per_row, f_empty_full, y);
+    if (takes_lanes(m))
+      k_gat_rows_lanes<<<static_cast<unsigned>(gnnshap::ceil_div(k, 64)), static_cast<unsigned>(J.g.nf / kSlice * 64),
+                         0, s>>>(J);
+    else
+      k_gat_rows<<<static_cast<unsigned>(gnnshap::ceil_div(k, kRowsWaves)), kRowsWaves * 64, 0, s>>>(J);
   }
   GS_LAUNCHED();
   return GNNSHAP_OK;

@@ -162,3 +162,29 @@ def test_gat_batch_equals_single(dev):
     phi_ref = wls.kernel_shap(m, w, game.values(m), f0, f1)
     phi = b.phi.cpu().numpy().astype(np.float64)
     assert np.abs(phi - phi_ref).max() <= 1e-3 * np.abs(phi_ref).max()
+
+
+@pytest.mark.parametrize("heads,F", [(1, 16), (16, 16), (2, 48), (3, 20)])
+def test_gat_lanes_and_batch_at_edges(dev, heads, F):
+    """One coalition per lane (head widths that are multiples of 16) and per
+    wavefront (20): 130 and 6 coalitions (a part of a workgroup), 1 to 256
+    features, a hub with more than 64 in-neighbours, a target with a single
+    one; the batch (targets of unlike sizes in one launch) equals the single
+    calls bit for bit."""
+    rng = np.random.default_rng(heads * 100 + F)
+    hub = np.stack([np.arange(1, 81), np.zeros(80, np.int64)])
+    rest = rng.integers(1, 90, size=(2, 60))
+    e = np.concatenate([hub, rest, [[85], [95]], [[95], [96]]], axis=1)   # 96 <- 95 <- 85
+    indptr, indices = W.in_csr_from_directed(97, e[0], e[1])
+    X = W.gaussian_features(97, 9, 3)
+    P = W.glorot_gat(9, heads, F, 5, 11, bias="random")
+    ex = GatExplainer(indptr, indices, X, P)
+    targets = [0, 96]
+    for p in (130, 6):
+        single = [_check(ex, indptr, indices, X, P, v, p, 3)[0] for v in targets]
+        single = [(r.y.clone(), r.f_empty_full.clone(), r.cls.clone()) for r in single]
+        batch = ex.explain_batch(targets, p, 3)
+        torch.cuda.synchronize()
+        for t in range(len(targets)):
+            for a, b in zip(single[t], (batch[t].y, batch[t].f_empty_full, batch[t].cls)):
+                assert torch.equal(a, b)
