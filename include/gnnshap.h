@@ -435,6 +435,18 @@ int gnnshap_fidelity(const gnnshap_subgraph* sg, const gnnshap_gcn* m, const flo
                      const float* phi, double sparsity, int64_t top_k, float* out, void* ws, size_t ws_bytes,
                      void* stream);
 
+/* Bytes of device workspace for gnnshap_fidelity_batch. */
+int gnnshap_fidelity_batch_workspace(const gnnshap_subgraph* sgs, int64_t n, const gnnshap_gcn* m, size_t* bytes);
+
+/* gnnshap_fidelity for n targets: sgs[t] and phi[t] ([host] arrays; phi[t]
+ * [dev]) are target t's, its three numbers go to out[3 t .. 3 t + 2].  Models
+ * that the batched evaluation takes run one launch per step for all targets,
+ * others target by target.  Every output equals gnnshap_fidelity's bit for
+ * bit.  EINVAL also for n < 1. */
+int gnnshap_fidelity_batch(const gnnshap_subgraph* sgs, const float* const* phi, int64_t n, const gnnshap_gcn* m,
+                           const float* X, int32_t target_class, double sparsity, int64_t top_k, float* out, void* ws,
+                           size_t ws_bytes, void* stream);
+
 /* eq. 7 and eq. 8 over n targets: avg[0] = mean of terms[t * stride],
  * avg[1] = mean of terms[t * stride + 1] (all [dev]; fp64 sums in a fixed
  * order).  EINVAL: n < 1 or stride < 2. */

@@ -101,6 +101,10 @@ _SIGNATURES = {
     "gnnshap_fidelity_workspace": (ctypes.c_int, [_P(gnnshap_subgraph), _P(gnnshap_gcn), _P(ctypes.c_size_t)]),
     "gnnshap_fidelity": (ctypes.c_int, [_P(gnnshap_subgraph), _P(gnnshap_gcn), c_vp, c_i32, c_vp, c_dbl, c_i64,
                                         c_vp, c_vp, ctypes.c_size_t, c_vp]),
+    "gnnshap_fidelity_batch_workspace": (ctypes.c_int, [_P(gnnshap_subgraph), c_i64, _P(gnnshap_gcn),
+                                                        _P(ctypes.c_size_t)]),
+    "gnnshap_fidelity_batch": (ctypes.c_int, [_P(gnnshap_subgraph), _P(c_vp), c_i64, _P(gnnshap_gcn), c_vp, c_i32,
+                                              c_dbl, c_i64, c_vp, c_vp, ctypes.c_size_t, c_vp]),
     "gnnshap_fidelity_average": (ctypes.c_int, [c_vp, c_i64, c_i64, c_vp, c_vp]),
     "gnnshap_fidelity_masks": (ctypes.c_int, [c_vp, c_i64, c_dbl, c_i64, c_vp, c_vp]),
     "gnnshap_gat_eval_workspace": (ctypes.c_int, [_P(gnnshap_subgraph), _P(gnnshap_gat), c_i64,
@@ -356,6 +360,20 @@ def gnnshap_fidelity_workspace(sg, model):
 def gnnshap_fidelity(sg, model, X_ptr, target_class, phi_ptr, sparsity, top_k, out_ptr, ws_ptr, ws_bytes, stream):
     check(load().gnnshap_fidelity(ctypes.byref(sg), ctypes.byref(model), X_ptr, int(target_class), phi_ptr,
                                   float(sparsity), int(top_k), out_ptr, ws_ptr, ws_bytes, stream), "fidelity")
+
+
+def gnnshap_fidelity_batch_workspace(sgs, model):
+    n = ctypes.c_size_t()
+    check(load().gnnshap_fidelity_batch_workspace(sgs, len(sgs), ctypes.byref(model), ctypes.byref(n)),
+          "fidelity_batch_workspace")
+    return n.value
+
+
+def gnnshap_fidelity_batch(sgs, phis, model, X_ptr, target_class, sparsity, top_k, out_ptr, ws_ptr, ws_bytes, stream):
+    """sgs: ctypes array of gnnshap_subgraph; phis: ctypes array of device addresses."""
+    check(load().gnnshap_fidelity_batch(sgs, phis, len(sgs), ctypes.byref(model), X_ptr, int(target_class),
+                                        float(sparsity), int(top_k), out_ptr, ws_ptr, ws_bytes, stream),
+          "fidelity_batch")
 
 
 def gnnshap_gat_eval_workspace(sg, model, k):

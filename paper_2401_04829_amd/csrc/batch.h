@@ -59,6 +59,9 @@ int eval_coalitions_impl(const gnnshap_subgraph* sg, const gnnshap_gcn* m, const
 // Whether one target can go through the batched evaluation, and the bytes of
 // its workspace slice.
 bool eval_batchable(const gnnshap_subgraph* sg, const gnnshap_gcn* m, int64_t k);
+// Whether, besides, the single-target call takes the same kernels (it
+// contracts wide hidden layers on matrix cores), so that both give the same bits.
+bool eval_batch_same(const gnnshap_subgraph* sg, const gnnshap_gcn* m, int64_t k);
 size_t eval_slice_bytes(const gnnshap_subgraph* sg, const gnnshap_gcn* m, int64_t k);
 // Carves job.ctl .. job.Zc1 from a slice.
 void eval_carve_slice(void* base, const gnnshap_subgraph* sg, const gnnshap_gcn* m, int64_t k, EvalJob* job);

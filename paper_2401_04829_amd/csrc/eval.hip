@@ -1824,6 +1824,15 @@ bool gnnshap::eval_batchable(const gnnshap_subgraph* sg, const gnnshap_gcn* m, i
          ends_ok(sh) && fused_l2_ok(sh, k, false);
 }
 
+bool gnnshap::eval_batch_same(const gnnshap_subgraph* sg, const gnnshap_gcn* m, int64_t k) {
+  Shape sh;
+  if (make_shape(sg, m, k, &sh) != GNNSHAP_OK) {
+    clear_error();
+    return false;
+  }
+  return !sh.wide && eval_batchable(sg, m, k);
+}
+
 size_t gnnshap::eval_slice_bytes(const gnnshap_subgraph* sg, const gnnshap_gcn* m, int64_t k) {
   Shape sh;
   if (make_shape(sg, m, k, &sh) != GNNSHAP_OK) return 0;

@@ -298,8 +298,8 @@ class Explainer:
     def fidelity(self, explanations, sparsity=0.3, top_k=10, target_class=-1):
         """Fidelity- and Fidelity+ (eq. 7-8) of explanations whose subgraph
         arrays are still valid (explain()'s until the next extract(), a
-        BatchExplanations' until the next batch): per target
-        gnnshap_fidelity with the explanation's phi (G_S drops the
+        BatchExplanations' until the next batch): gnnshap_fidelity_batch
+        with the explanations' phi (G_S drops the
         floor(sparsity M) least important players by |phi|, G_C minus S the
         top_k most important; Sec. 4.6 uses 0.3 and 10), then
         gnnshap_fidelity_average.  Returns (terms, avg): float32 [n, 3] rows
@@ -310,11 +310,12 @@ class Explainer:
         terms = torch.empty((n, 3), dtype=torch.float32, device=self.device)
         avg = torch.empty(2, dtype=torch.float32, device=self.device)
         s = self.stream()
-        for t, e in enumerate(items):
-            nbytes = L.gnnshap_fidelity_workspace(e.sub.sg, self.model)
-            ws = self.ws_fid.get(nbytes)
-            L.gnnshap_fidelity(e.sub.sg, self.model, _vp(self.X), target_class, _vp(e.phi), sparsity, top_k,
-                               _vp(terms[t]), _vp(ws), ws.numel(), s)
+        if n:
+            sgs = (L.gnnshap_subgraph * n)(*[e.sub.sg for e in items])
+            phis = (ctypes.c_void_p * n)(*[e.phi.data_ptr() for e in items])
+            ws = self.ws_fid.get(L.gnnshap_fidelity_batch_workspace(sgs, self.model))
+            L.gnnshap_fidelity_batch(sgs, phis, self.model, _vp(self.X), target_class, sparsity, top_k, _vp(terms),
+                                     _vp(ws), ws.numel(), s)
         L.gnnshap_fidelity_average(_vp(terms), n, 3, _vp(avg), s)
         return terms, avg
 

@@ -97,3 +97,23 @@ def test_fidelity_limits_exact(dev):
     tg = terms.cpu().numpy()
     assert tg[0, 0] == want and tg[0, 1] == want
     assert tg[0, 2] == np.float32(fef[1])
+
+
+@pytest.mark.parametrize("dims", [[12, 8, 3], [12, 33, 3], [12, 64, 3], [12, 8, 6, 3]])
+def test_fidelity_batch_equals_single_calls(dev, dims):
+    """gnnshap_fidelity_batch (one launch per step; three layers: target by
+    target) against gnnshap_fidelity for targets of unlike sizes, bit for bit."""
+    from paper_2401_04829_amd.explainer import Explainer
+    indptr, indices = W.random_digraph(90, 400, seed=8, symmetric=True)
+    Ws, bs = W.glorot_gcn(dims, 4, bias="random")
+    ex = Explainer(indptr, indices, W.gaussian_features(90, 12, 5), Ws, bs, 2)
+    targets = [int(v) for v in np.argsort(-np.diff(indptr))[[0, 3, 40, 80]]]
+    exps = list(ex.explain_batch(targets, 400, 2))
+    terms, _ = ex.fidelity(exps, 0.4, 5)
+    one = torch.empty(3, device=dev)
+    for t, e in enumerate(exps):
+        ws = torch.empty(L.gnnshap_fidelity_workspace(e.sub.sg, ex.model), dtype=torch.uint8, device=dev)
+        L.gnnshap_fidelity(e.sub.sg, ex.model, _vp(ex.X), -1, _vp(e.phi), 0.4, 5, _vp(one), _vp(ws), ws.numel(),
+                           torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(one, terms[t]), (targets[t], one, terms[t])
