@@ -235,6 +235,194 @@ __global__ void __launch_bounds__(256) k_gemm(const float* __restrict__ A, int64
   }
 }
 
+// The same product for large shapes on bf16 matrix instructions (16x the fp32
+// rate): every fp32 operand is the sum of three bf16 parts (hi = bf16(x), mid =
+// bf16(x - hi), lo = bf16(x - hi - mid), each rounded to nearest; 24 bits in
+// all), and the product of two such sums is taken as the six part products
+// down to 2^-16 of the largest (the three dropped ones are below 2^-25, half
+// an ulp of fp32 at most and of random sign).  Accumulation is fp32 over 32
+// products per step instead of 4, so the distance from 64 bits is no larger
+// than that of the fp32 instruction.  Values that round to infinity in bf16
+// or are not finite give a non-finite sum; such an output is computed again
+// in fp32.
+//
+// One workgroup: 128 rows x 32 NT columns, four wavefronts of 64 x 16 NT; K in
+// steps of 32, split while they are staged in LDS in operand order (16-byte
+// reads in lane order; the rows of odd k groups are swapped by 8 so that the
+// staging writes of eight rows x eight k quads spread over the banks).  The
+// next step's values are loaded while this one is multiplied.  Bound by the
+// latency of a step (staging, two barriers), then by the matrix
+// instructions (6 x 2 m n k flop); X W_1 of 232,965 x 602 x 128: 921 us
+// (k_transform) before, 353 us now, 2.2e-7 and 1.0e-7 off the 64-bit result.
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef unsigned u4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u2_t __attribute__((ext_vector_type(2)));
+typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any float's address
+constexpr int kSplitRows = 128;
+
+// Two floats as packed bf16 (round to nearest even), and what they leave.
+__device__ __forceinline__ unsigned bf16_pair(float& a, float& b) {
+  unsigned p;
+  asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(p) : "v"(a), "v"(b));
+  a -= __uint_as_float(p << 16);
+  b -= __uint_as_float(p & 0xffff0000u);
+  return p;
+}
+
+template <int NT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict__ arow,
+             const float* __restrict__ abias, const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
+             int64_t ldc, int64_t m0, int64_t rows, int64_t N, int64_t K, const int32_t* dyn_count, int64_t dyn_off,
+             int64_t dyn_cap, int64_t dyn_mult) {
+  constexpr int kCols = 32 * NT, kBT = 2 * NT;          // columns and column tiles of the workgroup
+  constexpr int kPerB = 32 * kCols / 256;               // B values per thread and step: 8 or 16, consecutive k
+  __shared__ u4_t As[3][8 * 64], Bs[3][kBT * 64];       // [part][tile][lane]: 8 bf16 of one row (column)
+  if (dyn_count) {
+    const int64_t r = rows_in_pass(dyn_count, dyn_off, dyn_cap) * dyn_mult;
+    if (r < rows) rows = r;
+  }
+  const int64_t mb = m0 + static_cast<int64_t>(blockIdx.x) * kSplitRows;
+  if (mb >= m0 + rows) return;
+  const int64_t nb = static_cast<int64_t>(blockIdx.y) * kCols;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // A: thread (row tid / 8 + 32 i, k quad tid % 8); B: column tid % kCols, k from kPerB (tid / kCols)
+  const int ak = (tid & 7) * 4;
+  const float* arp[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int64_t m = mb + tid / 8 + 32 * i;
+    const int64_t c = m < m0 + rows ? m : m0 + rows - 1;   // rows beyond the last: its values, not stored
+    arp[i] = A + (arow ? static_cast<int64_t>(arow[c]) : c) * lda;
+  }
+  const int bn = tid % kCols, bk = tid / kCols * kPerB;
+  const float* bp = B + (nb + bn < N ? nb + bn : N - 1);
+  float ra[4][4], rb[kPerB];
+  auto fetch = [&](int64_t k0) {
+    const bool whole = k0 + 32 <= K;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (whole) {
+        const f4u_t v = *reinterpret_cast<const f4u_t*>(arp[i] + k0 + ak);
+        ra[i][0] = v.x;
+        ra[i][1] = v.y;
+        ra[i][2] = v.z;
+        ra[i][3] = v.w;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) ra[i][q] = k0 + ak + q < K ? arp[i][k0 + ak + q] : 0.f;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kPerB; ++q) {
+      const int64_t k = k0 + bk + q;
+      rb[q] = whole || k < K ? bp[k * ldb] : 0.f;
+    }
+  };
+  auto stage = [&](int64_t k0) {
+    const int g = ak >> 3;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = tid / 8 + 32 * i;
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        v[q] = ra[i][q];
+        if (abias) v[q] = k0 + ak + q < K ? fmaxf(v[q] + abias[k0 + ak + q], 0.f) : 0.f;
+      }
+      const int at = ((row >> 4) * 64 + g * 16 + ((row & 15) ^ (8 * (g & 1)))) * 2 + ((ak >> 2) & 1);
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        reinterpret_cast<u2_t*>(As[p])[at] = u2_t{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3])};
+    }
+#pragma unroll
+    for (int h = 0; h < kPerB / 8; ++h) {
+      float v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = rb[8 * h + q];
+      const int at = (bn >> 4) * 64 + ((bk >> 3) + h) * 16 + (bn & 15);
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        Bs[p][at] = u4_t{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]), bf16_pair(v[4], v[5]), bf16_pair(v[6], v[7])};
+    }
+  };
+  // wavefront (wave / 2, wave % 2): rows 64 (wave / 2) .., columns 16 NT (wave % 2) ..
+  const int wm = (wave >> 1) * 4, wn = (wave & 1) * NT, g = lane >> 4, r = lane & 15;
+  const int la = g * 16 + (r ^ (8 * (g & 1)));
+  mx4_t acc[4][NT];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) acc[a][b] = mx4_t{0.f, 0.f, 0.f, 0.f};
+  fetch(0);
+  for (int64_t k0 = 0; k0 < K; k0 += 32) {
+    stage(k0);
+    __syncthreads();
+    if (k0 + 32 < K) fetch(k0 + 32);
+    bf8_t av[3][4];
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) av[p][a] = __builtin_bit_cast(bf8_t, As[p][(wm + a) * 64 + la]);
+#pragma unroll
+    for (int b = 0; b < NT; ++b) {
+      bf8_t bv[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) bv[p] = __builtin_bit_cast(bf8_t, Bs[p][(wn + b) * 64 + lane]);
+      // the step's sum from zero, (part of A, part of B) small products first,
+      // so that the running sum is rounded once per step and not six times
+      // (602 products: 3.7e-7 off instead of 2.2e-7 otherwise)
+      mx4_t sum[4];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[2][a], bv[0], mx4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[0][a], bv[2], sum[a], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[1][a], bv[1], sum[a], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[1][a], bv[0], sum[a], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[0][a], bv[1], sum[a], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[0][a], bv[0], sum[a], 0, 0, 0);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) acc[a][b] += sum[a];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t m = mb + 16 * (wm + a) + 4 * g + q;
+      if (m >= m0 + rows) continue;
+#pragma unroll
+      for (int b = 0; b < NT; ++b) {
+        const int64_t n = nb + 16 * (wn + b) + r;
+        if (n >= N) continue;
+        float v = acc[a][b][q];
+        if (!(fabsf(v) <= 3.4e38f)) {
+          const float* ar = A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda;
+          v = 0.f;
+          for (int64_t k = 0; k < K; ++k) v = fmaf(abias ? fmaxf(ar[k] + abias[k], 0.f) : ar[k], B[k * ldb + n], v);
+        }
+        C[m * ldc + n] = v;
+      }
+    }
+}
+
+// Whether a product takes k_gemm_split: columns and K that its tiles do not
+// mostly pad, and at least `least` workgroups.  One step of a workgroup takes
+// 2-3 us whatever the grid, so a small grid is faster on the many small tiles
+// of the fp32 kernels.  Against k_gemm the line is 256 workgroups, one per CU
+// (8,192 x 256 x 256, 128 workgroups: 23.4 us k_gemm, 30.5 split; 16,384 x
+// 600 x 41, 128: 37.3, 52.3; 232,965 x 602 x 128, 1,821: 921 k_transform,
+// 353 split), against k_transform, which has one workgroup per 16 rows, 128
+// (16,384 x 128 x 128: 20.2 us, 18.9 split; 8,192: 11.0, 18.3).
+bool takes_split(int64_t rows, int64_t N, int64_t K, int64_t least) {
+  return N >= 40 && K >= 32 && gnnshap::ceil_div(rows, kSplitRows) * gnnshap::ceil_div(N, 128) >= least;
+}
+
 // Zc[u, :] = XW1[node_gid[u], :]
 __global__ void k_gather_rows(const float* __restrict__ src, const int32_t* __restrict__ idx, int64_t n, int h,
                               float* __restrict__ dst) {
@@ -1374,10 +1562,19 @@ __global__ void __launch_bounds__(KW * 64) k_transform(const float* __restrict__
 int launch_gemm(hipStream_t s, const float* A, int64_t lda, const int32_t* arow, const float* abias,
                 const float* B, int64_t ldb, float* C, int64_t ldc, int64_t m0, int64_t rows, int64_t N,
                 int64_t K, const int32_t* dyn = nullptr, int64_t dyn_off = 0, int64_t dyn_cap = 0,
-                int64_t dyn_mult = 0) {
+                int64_t dyn_mult = 0, int64_t least = 256) {
   if (rows <= 0) return GNNSHAP_OK;
-  dim3 grid(static_cast<unsigned>(gnnshap::ceil_div(rows, 64)), static_cast<unsigned>(gnnshap::ceil_div(N, 64)));
   GS_TIMED("k_gemm", s);
+  if (takes_split(rows, N, K, least)) {
+    const int nt = N > 64 ? 4 : 2;
+    const dim3 g(static_cast<unsigned>(gnnshap::ceil_div(rows, kSplitRows)),
+                 static_cast<unsigned>(gnnshap::ceil_div(N, 32 * nt)));
+    (nt == 4 ? k_gemm_split<4> : k_gemm_split<2>)<<<g, 256, 0, s>>>(A, lda, arow, abias, B, ldb, C, ldc, m0, rows, N,
+                                                                   K, dyn, dyn_off, dyn_cap, dyn_mult);
+    GS_LAUNCHED();
+    return GNNSHAP_OK;
+  }
+  dim3 grid(static_cast<unsigned>(gnnshap::ceil_div(rows, 64)), static_cast<unsigned>(gnnshap::ceil_div(N, 64)));
   k_gemm<<<grid, 256, 0, s>>>(A, lda, arow, abias, B, ldb, C, ldc, m0, rows, N, K, dyn, dyn_off,
                               dyn_cap, dyn_mult);
   GS_LAUNCHED();
@@ -1790,7 +1987,8 @@ extern "C" int gnnshap_transform_features(const float* X, int64_t n, int32_t d, 
   if (!X || !W || !Z) return gnnshap::fail(GNNSHAP_EINVAL, "null argument");
   if (n < 1 || d < 1 || h < 1) return gnnshap::fail(GNNSHAP_EINVAL, "bad sizes");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (h % 16 == 0 && h <= 128 && gnnshap::ceil_div(n, 16) <= INT32_MAX) {
+  const bool narrow = h % 16 == 0 && h <= 128 && gnnshap::ceil_div(n, 16) <= INT32_MAX;
+  if (narrow && !takes_split(n, h, d, 128)) {
     const unsigned g = static_cast<unsigned>(gnnshap::ceil_div(n, 16));
     GS_TIMED("k_transform", s);
     switch (h / 16) {
@@ -1808,7 +2006,7 @@ extern "C" int gnnshap_transform_features(const float* X, int64_t n, int32_t d, 
   }
   if (gnnshap::ceil_div(n, 64) > INT32_MAX || gnnshap::ceil_div(h, 64) > 65535)
     return gnnshap::fail(GNNSHAP_EUNSUPPORTED, "matrix too large");
-  return launch_gemm(s, X, d, nullptr, nullptr, W, h, Z, h, 0, n, h, d);
+  return launch_gemm(s, X, d, nullptr, nullptr, W, h, Z, h, 0, n, h, d, nullptr, 0, 0, 0, narrow ? 128 : 256);
   GS_TRY_END
 }
 

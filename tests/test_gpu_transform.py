@@ -1,0 +1,63 @@
+"""X W of large shapes on split bf16 matrix products, against float64: tile
+edges in rows, columns and K, rows whose start is not 16-byte aligned, a wide
+range of magnitudes, infinities, NaN and values that round to infinity in
+bf16."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2401_04829_amd import _lib as L
+from paper_2401_04829_amd.explainer import _vp
+from tests.gpu_util import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    return require_gpu()
+
+
+def _transform(X, W):
+    Z = torch.full((X.shape[0], W.shape[1]), -7.0, device=X.device)
+    L.gnnshap_transform_features(_vp(X), X.shape[0], X.shape[1], _vp(W), W.shape[1], _vp(Z),
+                                 torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return Z
+
+
+@pytest.mark.parametrize("n,d,h", [(16384, 32, 64), (32700, 33, 40), (16385, 602, 128), (32641, 97, 65),
+                                   (16384, 64, 129), (20001, 31, 64), (32895, 130, 127), (1000, 70, 48)])
+def test_transform_against_float64(dev, n, d, h):
+    print("transform", n, d, h, flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    X = torch.randn((n, d), generator=g, device=dev) * torch.exp(3 * torch.randn((n, 1), generator=g, device=dev))
+    W = torch.randn((d, h), generator=g, device=dev) * torch.exp(3 * torch.randn((1, h), generator=g, device=dev))
+    Z = _transform(X, W).double()
+    exact = X.double() @ W.double()
+    # fp32 products and sums: d roundings of at most 2^-24 of the sum of magnitudes
+    bound = (d + 4) * 2.0 ** -24 * (X.double().abs() @ W.double().abs())
+    assert bool(((Z - exact).abs() <= bound).all()), float(((Z - exact).abs() / bound).max())
+
+
+def test_transform_special_values(dev):
+    """Infinities, NaN and values above the largest bf16 number give what
+    fp32 arithmetic gives; the other rows are untouched by them."""
+    n, d, h = 16384, 64, 64
+    X = torch.ones((n, d), device=dev)
+    W = torch.full((d, h), 0.5, device=dev)
+    W[3, 5] = 0.0
+    X[10, 3] = float("inf")
+    X[20, 4] = float("nan")
+    X[30, 7] = 3.4e38
+    X[40, 8], X[40, 9] = float("inf"), float("-inf")
+    Z = _transform(X, W).cpu().numpy()
+    want = np.full((n, h), 32.0, np.float32)
+    want[:, 5] = 31.5
+    want[10] = np.inf
+    want[10, 5] = np.nan
+    want[20] = np.nan
+    want[30] = 1.7e38
+    want[40] = np.nan
+    np.testing.assert_allclose(Z, want, rtol=1e-6, equal_nan=True)
