@@ -49,6 +49,7 @@ namespace {
 
 typedef float mx4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;                      // wavefronts per workgroup
 constexpr int kWaveRows = 64;                  // coalitions per wavefront (four tiles of 16)
@@ -250,7 +251,7 @@ __global__ void __launch_bounds__(kBlockRows, 2) k_wide_l1(
   const int fb = blockIdx.y;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, rl = lane & 15, g = lane >> 4;
   const int64_t c0 = cb * kBlockRows + wave * kWaveRows;
-  if (c0 >= nloc) return;                        // no barrier in this kernel
+  const bool active = c0 < nloc;                 // (a wavefront without rows only stages operands)
   const int e0 = dst_ptr[x], e1 = dst_ptr[x + 1];
   const int u0 = seg[x], nu = seg[x + 1] - u0;
   const int ft0 = fb * kTiles;
@@ -271,23 +272,32 @@ __global__ void __launch_bounds__(kBlockRows, 2) k_wide_l1(
 #pragma unroll
     for (int ft = 0; ft < kTiles; ++ft) D[ct][ft] = mx4_t{0.f, 0.f, 0.f, 0.f};
 
-  // A operands of unit q: lane's three parts for each of the kTiles feature
-  // tiles; the next unit's are loaded while this one is multiplied
+  // A operands of a unit (three parts of kTiles feature tiles, 12 KiB): the
+  // same for the four wavefronts, so they are staged in LDS once per workgroup
+  // (each wavefront loading them for itself kept the CU's 64 B/clk load path
+  // as busy as the matrix cores).  Two buffers: the next unit's operands are
+  // in registers, the one after it is being loaded, while this one is multiplied.
+  // (every load is of a valid unit and tile: the tiles beyond nt repeat a
+  // valid one, whose products are not used)
+  constexpr int kOps = kTiles * kParts * 64, kLoads = kOps / kBlockRows;
+  __shared__ u4_t As[2][kOps];
   const int64_t ustride = static_cast<int64_t>(ntot) * kParts * 64;
-  const uint4* zp = Zop + static_cast<int64_t>(u0) * ustride + static_cast<int64_t>(ft0) * kParts * 64 + lane;
-  // (every load is of a valid unit and tile: the last unit's successor and
-  // the tiles beyond nt repeat a valid one, whose products are not used)
-  uint4 a[kTiles][kParts], an[kTiles][kParts];
-  if (nu > 0) {
+  const u4_t* zp[kLoads];
+  u4_t an[kLoads];
 #pragma unroll
-    for (int ft = 0; ft < kTiles; ++ft)
-#pragma unroll
-      for (int p = 0; p < kParts; ++p) a[ft][p] = zp[((ft < nt ? ft : nt - 1) * kParts + p) * 64];
+  for (int i = 0; i < kLoads; ++i) {
+    const int o = static_cast<int>(threadIdx.x) + kBlockRows * i, ft = o / (kParts * 64);
+    zp[i] = reinterpret_cast<const u4_t*>(Zop) + static_cast<int64_t>(u0) * ustride +
+            static_cast<int64_t>(ft0 + (ft < nt ? ft : nt - 1)) * kParts * 64 + o % (kParts * 64);
+    if (nu > 0) {
+      As[0][o] = zp[i][0];
+      an[i] = zp[i][(nu > 1 ? 1 : 0) * ustride];
+    }
   }
   // the mask bits of 64 players (units q, q + 1) of each of the lane's rows;
   // the window of the next two units is loaded while these are multiplied
   auto window = [&](int q, int ct) -> uint64_t {
-    if (!valid[ct] || q >= nu) return 0;
+    if (!valid[ct] || q >= nu) return 0;   // (no lane of an idle wavefront is valid)
     const int64_t pb = e0 + static_cast<int64_t>(kUnit) * q;
     const int64_t wa = pb >> 6;
     const int sh = static_cast<int>(pb & 63);
@@ -307,13 +317,19 @@ __global__ void __launch_bounds__(kBlockRows, 2) k_wide_l1(
         wnext[ct] = window(q + 2, ct);
       }
     }
-    const int64_t qn = q + 1 < nu ? q + 1 : q;
+    __syncthreads();   // unit q is staged; buffer (q + 1) & 1 was read before the barrier of unit q - 1
+    if (q + 1 < nu) {
 #pragma unroll
-    for (int ft = 0; ft < kTiles; ++ft)
+      for (int i = 0; i < kLoads; ++i) As[(q + 1) & 1][threadIdx.x + kBlockRows * i] = an[i];
+      const int64_t qn = q + 2 < nu ? q + 2 : q + 1;
 #pragma unroll
-      for (int p = 0; p < kParts; ++p) an[ft][p] = zp[qn * ustride + ((ft < nt ? ft : nt - 1) * kParts + p) * 64];
+      for (int i = 0; i < kLoads; ++i) an[i] = zp[i][qn * ustride];
+    }
+    if (!active) continue;
+    const u4_t* a = As[q & 1] + lane;
     // B: the lane's eight players 8 g .. 8 g + 7 of the unit for row 16 ct +
     // rl, as eight bf16 of 0.0 or 1.0 (0x3F80), two per dword
+    bf8_t bv[4];
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
       const uint32_t byte = static_cast<uint32_t>(win[ct] >> (32 * (q & 1) + 8 * g)) & 0xffu;
@@ -321,20 +337,20 @@ __global__ void __launch_bounds__(kBlockRows, 2) k_wide_l1(
 #pragma unroll
       for (int t = 0; t < 4; ++t)
         bw[t] = (((byte >> (2 * t)) & 1u) | (((byte >> (2 * t + 1)) & 1u) << 16)) * 0x3F80u;
-      const bf8_t bv = __builtin_bit_cast(bf8_t, make_uint4(bw[0], bw[1], bw[2], bw[3]));
-      // (tiles beyond nt multiply a repeated valid tile; the epilogue skips them)
-#pragma unroll
-      for (int ft = 0; ft < kTiles; ++ft)
-#pragma unroll
-        for (int p = 0; p < kParts; ++p)
-          D[ct][ft] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8_t, a[ft][p]), bv, D[ct][ft],
-                                                              0, 0, 0);
+      bv[ct] = __builtin_bit_cast(bf8_t, make_uint4(bw[0], bw[1], bw[2], bw[3]));
     }
+    // (tiles beyond nt multiply a repeated valid tile; the epilogue skips them)
 #pragma unroll
     for (int ft = 0; ft < kTiles; ++ft)
 #pragma unroll
-      for (int p = 0; p < kParts; ++p) a[ft][p] = an[ft][p];
+      for (int p = 0; p < kParts; ++p) {
+        const bf8_t av = __builtin_bit_cast(bf8_t, a[(ft * kParts + p) * 64]);
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct)
+          D[ct][ft] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[ct], D[ct][ft], 0, 0, 0);
+      }
   }
+  if (!active) return;
 
   // epilogue: the players whose source is in H_1, self loop, bias, ReLU and
   // (kProj, kProjRows) the explained class's column of the next weight
@@ -362,7 +378,53 @@ __global__ void __launch_bounds__(kBlockRows, 2) k_wide_l1(
     for (int ct = 0; ct < 4; ++ct)
       P[ct][ft] = mx4_t{s4.x - D[ct][ft][0], s4.y - D[ct][ft][1], s4.z - D[ct][ft][2], s4.w - D[ct][ft][3]};
   }
-  for (int sp = sp0; sp < sp1; ++sp) {
+  if (MODE != kProjRows) {
+    // constant input rows: (features x players) x (players x coalitions) on
+    // fp32 MFMA 16x16x4, four players per step.  Lane (rl, g) gives player
+    // sp + g's feature rl of each tile and its coefficient in coalition rl of
+    // each row tile (0 when the coalition does not hold it), so a coefficient
+    // is computed by one lane and not by four, and the multiply-adds run at
+    // twice the VALU rate.  With ~40 such players per node this loop took
+    // longer than the contraction above.
+    int e_n = sp0 < sp1 ? spec_e[min(sp0 + g, sp1 - 1)] : 0;
+    int32_t u_n = sp0 < sp1 ? edge_src[e_n] : 0;
+    for (int sp = sp0; sp < sp1; sp += 4) {
+      const bool in = sp + g < sp1;
+      const int e = e_n;
+      const int32_t u = u_n;
+      float zu[kTiles];
+#pragma unroll
+      for (int ft = 0; ft < kTiles; ++ft)
+        zu[ft] = Zc[static_cast<int64_t>(u) * h + 16 * (ft0 + (ft < nt ? ft : nt - 1)) + rl];
+      const int nuu = PAIRS ? dst_ptr[u + 1] - dst_ptr[u] : 0;
+      uint64_t mw[4];
+      int du[4];
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) {
+        mw[ct] = mrr[ct][e >> 6];
+        du[ct] = dgr[ct][u];
+      }
+      e_n = spec_e[min(sp + 4 + g, sp1 - 1)];
+      u_n = edge_src[e_n];
+      float cw[4], cp[4];
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) {
+        const bool bit = (mw[ct] >> (e & 63)) & 1;
+        cw[ct] = in && bit ? __builtin_amdgcn_rsqf(1.0f + static_cast<float>(du[ct])) : 0.f;
+        cp[ct] = PAIRS && in && !bit ? __builtin_amdgcn_rsqf(1.0f + static_cast<float>(nuu - du[ct])) : 0.f;
+      }
+#pragma unroll
+      for (int ft = 0; ft < kTiles; ++ft) {
+        if (ft >= nt) continue;
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) {
+          D[ct][ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(zu[ft], cw[ct], D[ct][ft], 0, 0, 0);
+          if (PAIRS) P[ct][ft] = __builtin_amdgcn_mfma_f32_16x16x4f32(zu[ft], cp[ct], P[ct][ft], 0, 0, 0);
+        }
+      }
+    }
+  }
+  for (int sp = sp0; MODE == kProjRows && sp < sp1; ++sp) {
     const int e = spec_e[sp];
     const int32_t u = edge_src[e];
     const int nuu = PAIRS ? dst_ptr[u + 1] - dst_ptr[u] : 0;
@@ -378,41 +440,24 @@ __global__ void __launch_bounds__(kBlockRows, 2) k_wide_l1(
     for (int ft = 0; ft < kTiles; ++ft) {
       if (ft >= nt) continue;
       const int f = 16 * (ft0 + ft) + 4 * g;
-      if (MODE != kProjRows) {
-        const float4 zu = *reinterpret_cast<const float4*>(Zc + static_cast<int64_t>(u) * h + f);
+      // the source's row under the coalition that holds the player (the
+      // row itself, or with pairs its complement): one load, no branch, so
+      // the loads of the four row tiles go out together; the other
+      // coefficient is 0 and adds nothing
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-          D[ct][ft][0] = fmaf(cw[ct], zu.x, D[ct][ft][0]);
-          D[ct][ft][1] = fmaf(cw[ct], zu.y, D[ct][ft][1]);
-          D[ct][ft][2] = fmaf(cw[ct], zu.z, D[ct][ft][2]);
-          D[ct][ft][3] = fmaf(cw[ct], zu.w, D[ct][ft][3]);
-          if (PAIRS) {
-            P[ct][ft][0] = fmaf(cp[ct], zu.x, P[ct][ft][0]);
-            P[ct][ft][1] = fmaf(cp[ct], zu.y, P[ct][ft][1]);
-            P[ct][ft][2] = fmaf(cp[ct], zu.z, P[ct][ft][2]);
-            P[ct][ft][3] = fmaf(cp[ct], zu.w, P[ct][ft][3]);
-          }
-        }
-      } else {
-        // the source's row under the coalition that holds the player (the
-        // row itself, or with pairs its complement): one load, no branch, so
-        // the loads of the four row tiles go out together; the other
-        // coefficient is 0 and adds nothing
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-          const bool own = !PAIRS || cw[ct] != 0.f;
-          const float4 zu =
-              *reinterpret_cast<const float4*>(Zrow + ((own ? lr[ct] : lr[ct] + nloc) * n1 + u) * h + f);
-          D[ct][ft][0] = fmaf(cw[ct], zu.x, D[ct][ft][0]);
-          D[ct][ft][1] = fmaf(cw[ct], zu.y, D[ct][ft][1]);
-          D[ct][ft][2] = fmaf(cw[ct], zu.z, D[ct][ft][2]);
-          D[ct][ft][3] = fmaf(cw[ct], zu.w, D[ct][ft][3]);
-          if (PAIRS) {
-            P[ct][ft][0] = fmaf(cp[ct], zu.x, P[ct][ft][0]);
-            P[ct][ft][1] = fmaf(cp[ct], zu.y, P[ct][ft][1]);
-            P[ct][ft][2] = fmaf(cp[ct], zu.z, P[ct][ft][2]);
-            P[ct][ft][3] = fmaf(cp[ct], zu.w, P[ct][ft][3]);
-          }
+      for (int ct = 0; ct < 4; ++ct) {
+        const bool own = !PAIRS || cw[ct] != 0.f;
+        const float4 zu =
+            *reinterpret_cast<const float4*>(Zrow + ((own ? lr[ct] : lr[ct] + nloc) * n1 + u) * h + f);
+        D[ct][ft][0] = fmaf(cw[ct], zu.x, D[ct][ft][0]);
+        D[ct][ft][1] = fmaf(cw[ct], zu.y, D[ct][ft][1]);
+        D[ct][ft][2] = fmaf(cw[ct], zu.z, D[ct][ft][2]);
+        D[ct][ft][3] = fmaf(cw[ct], zu.w, D[ct][ft][3]);
+        if (PAIRS) {
+          P[ct][ft][0] = fmaf(cp[ct], zu.x, P[ct][ft][0]);
+          P[ct][ft][1] = fmaf(cp[ct], zu.y, P[ct][ft][1]);
+          P[ct][ft][2] = fmaf(cp[ct], zu.z, P[ct][ft][2]);
+          P[ct][ft][3] = fmaf(cp[ct], zu.w, P[ct][ft][3]);
         }
       }
     }
