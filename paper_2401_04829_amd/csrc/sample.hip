@@ -5,7 +5,7 @@
 // Enumerated classes unrank their lexicographic index; random classes run
 // Floyd's algorithm on Philox4x32-10 draws, 64 steps at a time: every lane
 // takes one step, lanes whose draw cannot interact with an earlier step of
-// the same chunk decide at once, the others are replayed in step order, so
+// the same chunk decide at once, the others are resolved in step order, so
 // the result is exactly the sequential algorithm's.  Each Philox call gives
 // the draws of four consecutive steps, so the words of 256 steps are made by
 // one call per lane and staged in LDS.
@@ -18,7 +18,7 @@
 namespace {
 
 static_assert(sizeof(gnnshap_class) == 32, "class record layout");
-constexpr int64_t kMaxPlayers = 131072;  // 3 bitsets of M bits in 48 KiB of LDS
+constexpr int64_t kMaxPlayers = 131072;  // the row's bitset in 16 KiB of LDS
 
 struct Ws {
   gnnshap_class* classes;
@@ -95,6 +95,59 @@ __device__ __forceinline__ void set_bit(uint32_t* bs, int64_t j) { bs[j >> 5] |=
 
 constexpr int64_t kMaxComb = 64;   // enumerated subsets stepped incrementally up to this size
 
+// Steps lane = 0 .. min(63, left - 1) of Floyd's algorithm, step `lane` with
+// draw u of [0, j], j = j0 + lane: t = the drawn player, or j if t is in the
+// set.  S holds the set before these steps, which has no player >= j0.
+//
+// A draw t < j0 is in the set before the steps or not, whatever the steps do:
+// one read and one or of S, which the LDS runs in this order, tell both that
+// and whether another lane drew the same t (then all but the first of them
+// take their j).  The players from j0 on are the 64 bits of `hi` in scalar
+// registers: a step takes its own j, or its draw is one of an earlier step's j
+// and is resolved in step order (the steps of one row meet rarely: 64 draws
+// among 20 000 players about once in 7 chunks).
+//
+// What bounds a row is this chain of dependent LDS round trips, so a chunk
+// has one with a wait and one without: 100 000 rows of 18 001 players take
+// 557 us at twelve row pairs per wavefront, where two more bitsets (draws
+// seen once, twice), five waits per chunk and a replay through LDS by lane 0
+// took 870 us; 157 us at one pair per wavefront.
+__device__ __forceinline__ void floyd_steps(uint32_t* S, uint32_t u, int j0, int left, int lane) {
+  const bool act = lane < left;
+  const int t = static_cast<int>((static_cast<uint64_t>(u) * static_cast<uint32_t>(j0 + lane + 1)) >> 32);
+  const int p = t - j0;                  // [-j0, lane]
+  const uint32_t bit = 1u << (t & 31);
+  bool in = false, dup = false;
+  if (act && p < 0) {
+    const uint32_t before = __hip_atomic_load(&S[t >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint32_t old = __hip_atomic_fetch_or(&S[t >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    in = (before & bit) != 0;
+    dup = !in && (old & bit) != 0;
+  }
+  uint64_t hi = __ballot(in || (act && p == lane));
+  uint64_t todo = __ballot(dup);
+  while (todo) {                         // all lanes of the same draw but the first take their j
+    const int l = __builtin_ctzll(todo);
+    const int tl = __builtin_amdgcn_readlane(t, l);
+    uint64_t same = __ballot(act && t == tl);
+    todo &= ~same;
+    same &= same - 1;
+    hi |= same;
+  }
+  todo = __ballot(act && p >= 0 && p < lane);
+  while (todo) {                         // draws of earlier steps' j, in step order
+    const int l = __builtin_ctzll(todo);
+    todo &= todo - 1;
+    const int pl = __builtin_amdgcn_readlane(p, l);
+    hi |= uint64_t(1) << (((hi >> pl) & 1) ? l : pl);
+  }
+  const int sh = j0 & 31;
+  const uint32_t part = lane == 0 ? static_cast<uint32_t>(hi << sh)
+                      : lane == 1 ? static_cast<uint32_t>((hi << sh) >> 32)
+                      : lane == 2 && sh ? static_cast<uint32_t>(hi >> (64 - sh)) : 0;
+  if (part) __hip_atomic_fetch_or(&S[(j0 >> 5) + lane], part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Rows [r_begin, min(r_end, half)) of one job; one wavefront.  The class of
 // the first row is found by binary search, later rows advance through the
 // class table (rows are grouped by class).
@@ -107,13 +160,8 @@ __device__ __forceinline__ void sample_rows(const gnnshap::SampleJob& J, int64_t
   extern __shared__ uint32_t lds[];
   const int64_t nw = 2 * wpr;           // 32-bit words per bitset
   uint32_t* S = lds;                    // the row being built
-  uint32_t* D1 = S + nw;                // draws seen once in the current chunk
-  uint32_t* D2 = D1 + nw;               // draws seen twice or more
   const int lane = threadIdx.x;
-  for (int64_t w = lane; w < nw; w += 64) {
-    D1[w] = 0;
-    D2[w] = 0;
-  }
+  for (int64_t w = lane; w < nw; w += 64) S[w] = 0;
   if (r_end > half) r_end = half;
   int64_t lo = 0, hi = ncls - 1;        // last class starting at or before row r_begin
   while (lo < hi) {
@@ -136,7 +184,6 @@ __device__ __forceinline__ void sample_rows(const gnnshap::SampleJob& J, int64_t
     const int full = cur.full;
     const int64_t rank = i - cur.row_begin;
     const float wt = static_cast<float>(cur.weight);
-    for (int64_t w = lane; w < nw; w += 64) S[w] = 0;
     __syncthreads();
     if (full) {
       if (lane == 0) {
@@ -171,69 +218,37 @@ __device__ __forceinline__ void sample_rows(const gnnshap::SampleJob& J, int64_t
         comb_rank = rank;
       }
     } else {
-      for (int64_t base = 0; base < c; base += 64) {
-        if ((base & 255) == 0) {
-          // the draws of steps base .. base + 255: lane l evaluates counter
-          // base/4 + l, whose four words are the draws of steps base + 4l + 0..3
-          if (base + 4 * lane < c) {
-            uint32_t c0 = static_cast<uint32_t>((base >> 2) + lane), c1 = static_cast<uint32_t>(i), c2 = st_lo,
-                     c3 = st_hi;
-            philox4x32_10(c0, c1, c2, c3, seed_lo, seed_hi);
-            draws[4 * lane] = c0;
-            draws[4 * lane + 1] = c1;
-            draws[4 * lane + 2] = c2;
-            draws[4 * lane + 3] = c3;
-          }
-          __syncthreads();
-        }
-        const int64_t s = base + lane;
-        const bool act = s < c;
-        const int64_t j = M - c + s;
-        uint32_t t = 0;
-        if (act) {
-          const uint32_t u = draws[s & 255];
-          t = static_cast<uint32_t>((static_cast<uint64_t>(u) * static_cast<uint64_t>(j + 1)) >> 32);
-        }
-        const int64_t wd = t >> 5;
-        const uint32_t bit = 1u << (t & 31);
-        if (act) {
-          const uint32_t old = atomicOr(&D1[wd], bit);
-          if (old & bit) atomicOr(&D2[wd], bit);
+      const int cc = static_cast<int>(c), mc = static_cast<int>(M - c);
+      for (int base = 0; base < cc; base += 256) {
+        // the draws of steps base .. base + 255: lane l evaluates counter
+        // base/4 + l, whose four words are the draws of steps base + 4l + 0..3
+        if (base + 4 * lane < cc) {
+          uint32_t c0 = static_cast<uint32_t>((base >> 2) + lane), c1 = static_cast<uint32_t>(i), c2 = st_lo,
+                   c3 = st_hi;
+          philox4x32_10(c0, c1, c2, c3, seed_lo, seed_hi);
+          draws[4 * lane] = c0;
+          draws[4 * lane + 1] = c1;
+          draws[4 * lane + 2] = c2;
+          draws[4 * lane + 3] = c3;
         }
         __syncthreads();
-        const bool dup = act && (D2[wd] & bit);
-        const bool hits_j = act && static_cast<int64_t>(t) >= M - c + base && static_cast<int64_t>(t) < j;
-        const bool dirty = dup || hits_j;
-        const bool in = act && !dirty && (S[wd] & bit);
+        uint32_t u[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = draws[64 * q + lane];
         __syncthreads();
-        if (act && !dirty) {
-          const int64_t ins = in ? j : static_cast<int64_t>(t);
-          atomicOr(&S[ins >> 5], 1u << (ins & 31));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int b0 = base + 64 * q;
+          if (b0 < cc) floyd_steps(S, u[q], mc + b0, cc - b0, lane);
         }
-        __syncthreads();
-        uint64_t todo = __ballot(dirty);
-        while (todo) {                     // replay the interacting steps in order
-          const int l = __ffsll(static_cast<long long>(todo)) - 1;
-          todo &= todo - 1;
-          const uint32_t tl = __shfl(t, l);
-          if (lane == 0) {
-            const int64_t jl = M - c + base + l;
-            const bool inl = S[tl >> 5] & (1u << (tl & 31));
-            set_bit(S, inl ? jl : static_cast<int64_t>(tl));
-          }
-          __syncthreads();
-        }
-        if (act) {
-          D1[wd] = 0;
-          D2[wd] = 0;
-        }
-        __syncthreads();
       }
     }
     __syncthreads();
     const uint64_t tail = (M & 63) ? ((uint64_t(1) << (M & 63)) - 1) : ~uint64_t(0);
     for (int64_t w = lane; w < wpr; w += 64) {
       const uint64_t word = static_cast<uint64_t>(S[2 * w]) | (static_cast<uint64_t>(S[2 * w + 1]) << 32);
+      S[2 * w] = 0;                      // for the next row
+      S[2 * w + 1] = 0;
       const uint64_t valid = (w == wpr - 1) ? tail : ~uint64_t(0);
       masks[i * wpr + w] = word;
       masks[(i + half) * wpr + w] = ~word & valid;
@@ -322,12 +337,15 @@ __device__ __forceinline__ void sample_lane_rows(const gnnshap::SampleJob& J, in
   J.weights[i + half] = wt;
 }
 
-// Consecutive representative rows per wavefront: enough workgroups to fill
-// the GPU several times over, at most kRowsPerBlock rows each.
+// Consecutive representative rows per wavefront, at most kRowsPerBlock.  A
+// row is one chain of LDS round trips, hidden by other wavefronts only, so
+// rows are stacked no earlier than the grid is several times the 8192
+// wavefront slots: 50 000 rows of 18 001 players take 557 us at twelve per
+// wavefront, 226 us at three, 157 us at one.
 constexpr int64_t kRowsPerBlock = 16;
 
 int64_t rows_per_block(int64_t half) {
-  int64_t r = half / 4096;
+  int64_t r = half / 32768;
   return r < 1 ? 1 : (r > kRowsPerBlock ? kRowsPerBlock : r);
 }
 
@@ -424,7 +442,7 @@ int sample_launch(const gnnshap_sample_plan* plan, const gnnshap_class* classes,
     GS_LAUNCHED();
     return GNNSHAP_OK;
   }
-  const size_t lds = static_cast<size_t>(3 * 2 * wpr) * sizeof(uint32_t);
+  const size_t lds = static_cast<size_t>(2 * wpr) * sizeof(uint32_t);
   const int64_t rpb = rows_per_block(half);
   const int64_t nblk = gnnshap::ceil_div(half, rpb);
   if (nblk > INT32_MAX) return gnnshap::fail(GNNSHAP_EUNSUPPORTED, "too many rows");
@@ -501,7 +519,7 @@ int64_t gnnshap::plan_sample_batch(SampleJob* jobs, int64_t n) {
 int gnnshap::launch_sample_batch(const SampleJob* jobs, int64_t n, int64_t blocks, int64_t max_wpr, hipStream_t s) {
   if (n < 1) return GNNSHAP_OK;
   if (blocks > INT32_MAX) return fail(GNNSHAP_EUNSUPPORTED, "too many rows");
-  const size_t lds = std::max(static_cast<size_t>(3 * 2 * max_wpr) * sizeof(uint32_t),
+  const size_t lds = std::max(static_cast<size_t>(2 * max_wpr) * sizeof(uint32_t),
                               lane_lds_bytes(std::min<int64_t>(max_wpr, kLaneMaxPlayers / 64)));
   GS_TIMED("k_sample_batch", s);
   k_sample_batch<<<static_cast<unsigned>(blocks), 64, lds, s>>>(jobs, n);
