@@ -117,3 +117,27 @@ def test_fidelity_batch_equals_single_calls(dev, dims):
                            torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         assert torch.equal(one, terms[t]), (targets[t], one, terms[t])
+
+
+def test_fidelity_captured_in_a_graph(dev):
+    """Explainer.fidelity recorded in a graph and replayed on new phi, with
+    eager calls on other targets between the replays (they use the host
+    staging buffers again): every replay equals the eager result bit for bit."""
+    cfg = W.make_config("cora")
+    ex = explainer_for(cfg)
+    exps = list(ex.explain_batch(cfg["targets"][:4], cfg["p"], cfg["seed"]))
+    saved = [e.phi.clone() for e in exps]
+    ex.fidelity(exps, 0.3, 4)                     # the workspace exists before the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        terms, avg = ex.fidelity(exps, 0.3, 4)
+    for i in range(5):
+        for e, p in zip(exps, saved):
+            e.phi.copy_(torch.roll(p, i))
+        for _ in range(3):
+            want, want_avg = ex.fidelity(exps, 0.3, 4)
+            ex.fidelity(exps[1:], 0.3, 4)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(terms, want) and torch.equal(avg, want_avg), i
