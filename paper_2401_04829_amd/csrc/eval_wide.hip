@@ -237,6 +237,9 @@ enum : int { kProj = 0, kFull = 1, kProjRows = 2 };
 // 4 g .. + 3 of pass row c0 + 16 ct + r.  The row's complement (pairs) is
 // row + khalf; per-row arrays of the pass (Hout, Zrow: [pass row][x][f])
 // hold the complement of pass row i at i + nloc.
+// Bound by bf16 MFMA and the loads of its operands: with the operands staged
+// in LDS once per workgroup and the H_1 players on fp32 MFMA, 1378 -> 1178 us
+// per Reddit-shaped target (2.56e11 useful flop: 217 TFLOP/s).
 template <bool PAIRS, int MODE>
 __global__ void __launch_bounds__(kBlockRows, 2) k_wide_l1(
     const uint64_t* __restrict__ masks, int64_t wpr, int64_t r0, int64_t nloc, int64_t khalf, int64_t cblocks,
