@@ -26,8 +26,8 @@
 // (0001 = 0.5, 0010 = 1.0; e2m1), so v_mfma_f32_16x16x128_f8f6f4 contracts
 // 16 bit rows x 128 entries with the 16 digits in one instruction: every
 // product is a whole number of eighths and every sum stays below 2^24 of
-// them, so fp32 accumulation loses nothing (segments of kSegGroups groups
-// keep it so for any number of rows).  The digit sums are combined in fp64.
+// them, so fp32 accumulation loses nothing (segments of kSegGroups groups per
+// wavefront keep it so for any number of rows).  The digit sums are combined in fp64.
 // What rounds is the integer (2^-62 of the bound, which is within a factor
 // of 2^10 of the largest entry) and the last 16-term fp64 combination, less
 // than the thousands of fp64 additions of a direct sum; and the result does
@@ -87,7 +87,9 @@ constexpr int64_t kMaxIt = 4000;
 constexpr int64_t kChunk = 8;        // iterations queued between stopping checks
 constexpr int kWaves = 8;            // waves per workgroup of both passes
 constexpr int kThreads = kWaves * 64;
-constexpr int kSegGroups = 4096;     // K groups (256 entries) a wavefront accumulates in fp32: 2^20 x 15 < 2^24
+constexpr int kSegGroups = 512;      // K groups (256 entries) a wavefront accumulates in fp32 before an fp64 sum
+// a segment's sum over its wavefronts, in eighths, is exact in fp32
+static_assert(int64_t(kSegGroups) * kWaves * 256 * 15 < (int64_t(1) << 24));
 constexpr int64_t kSparseDiv = 128;   // sparse rows: coalition size at most M / kSparseDiv
 constexpr int kFixedBits = 62;        // |fixed-point entries| stay below 2^62
 constexpr uint64_t kSign = uint64_t(1) << 63;
@@ -479,6 +481,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6
   const int m = member_of(g, bid);
   const Args& a = g.a[m];
   const int64_t t = g.t[m];
+  // workgroup 0 may set this while others start: a wavefront that sees it ends
+  // (barriers wait for the wavefronts that are left), the rest computes values
+  // that nobody reads
   if (a.st->done) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
