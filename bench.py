@@ -201,7 +201,7 @@ def cpu_baseline(cfg, seconds):
 # = 78.6 TFLOP/s; 32-bit integer VALU ops at the same issue rate: 39.3 Tops/s.
 HBM_PEAK_GBS = 8000.0
 VALU_FP32_TFLOPS = 78.6
-VALU_INT_TOPS = 39.3
+MFMA_FP4_TFLOPS = 10000.0
 MFMA_FP32_TFLOPS = 157.3
 MFMA_BF16_TFLOPS = 2500.0
 
@@ -226,8 +226,8 @@ def work_model(kernel, results, dims, solves):
                    fp64 vectors of M read and written)
     k_solve_mid / k_solve_one_batch (one-workgroup solves)
                    M^3/6 (Cholesky) + 2 M^2 (two triangular solves) MACs, 2 flop each
-    k_gram         K_R M(M+1)/2 pair counts over the random rows, 1 popcount-AND
-                   per 64 rows and pair
+    k_gram         K_R M(M+1)/2 pair counts over the random rows, 2 flop each (fp4
+                   matrix instructions, exact)
     k_sample       k x ceil(M/64) x 8 bytes of masks + 4 k bytes of weights written
     k_rhs_part, k_rhs_tile
                    (k/2) x ceil(M/64) x 8 bytes of masks + 4 k bytes of y read
@@ -262,7 +262,7 @@ def work_model(kernel, results, dims, solves):
             tot += 2.0 * ((k / 2.0) * M * h + k * n1 * h)
         elif base == "k_gram":
             if not batched or path in (1, 2):
-                tot += (kr / 64.0) * M * (M + 1) / 2.0
+                tot += 2.0 * kr * M * (M + 1) / 2.0
         elif base == "k_sample":
             tot += k * wpr * 8.0 + 4.0 * k
         elif base in ("k_rhs_part", "k_rhs_tile"):
@@ -271,7 +271,7 @@ def work_model(kernel, results, dims, solves):
     if base in ("k_sample", "k_rhs_part", "k_rhs_tile"):
         return tot, "GB/s", "hbm", HBM_PEAK_GBS
     if base == "k_gram":
-        return tot, "Tops/s", "alu", VALU_INT_TOPS
+        return tot, "TFLOP/s", "mfma", MFMA_FP4_TFLOPS
     if base == "k_wide_l1":
         return tot, "TFLOP/s", "mfma", MFMA_BF16_TFLOPS
     if base == "k_eval_rows_mx":

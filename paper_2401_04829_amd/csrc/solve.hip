@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(512) k_transpose_blocked(const uint64_t* __res
 }
 
 // Counts C[i, j] = sum_rb popcount(T[rb, i] & T[rb, j]) for 64x64 tiles with J >= I,
-// stored in both halves (row stride ld).
+// stored in both halves (row stride ld): gram_body.
 // Row sums of a 64 x 64 count tile (I, J) held 4 x 4 per thread (thread
 // (ty, tx) = (tid / 16, tid % 16) holds rows ty + 16 q and columns tx + 16 r,
 // q, r < 4, so that a wavefront's LDS reads of the tile's words fall on
@@ -246,80 +246,52 @@ __device__ __forceinline__ void tile_row_sums(const int (&acc)[4][4], int64_t M,
   }
 }
 
-// usum: NULL, or row sums to add the tile's sums to (tile_row_sums).
-__device__ __forceinline__ void gram_body(const uint64_t* __restrict__ T, int64_t nrb, int64_t M, int64_t ld,
-                                          int32_t* __restrict__ C, int64_t I, int64_t J,
-                                          int64_t* __restrict__ usum = nullptr) {
-  if (J < I) return;
-  __shared__ uint64_t Ti[16][64];
-  __shared__ uint64_t Tj[16][64];
-  const int tid = threadIdx.x;
-  const int ty = tid / 16, tx = tid % 16;
-  int acc[4][4] = {};
-  // the next stage's words are fetched while the current stage is counted
-  uint64_t ni[4], nj[4];
-  auto fetch = [&](int64_t k0) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = tid + q * 256;
-      const int kk = idx / 64, c = idx % 64;
-      const int64_t i = I * 64 + c, j = J * 64 + c;
-      const bool kin = k0 + kk < nrb;
-      ni[q] = (kin && i < M) ? T[(k0 + kk) * M + i] : 0;
-      nj[q] = (kin && j < M) ? T[(k0 + kk) * M + j] : 0;
-    }
-  };
-  fetch(0);
-  for (int64_t k0 = 0; k0 < nrb; k0 += 16) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = tid + q * 256;
-      Ti[idx / 64][idx % 64] = ni[q];
-      Tj[idx / 64][idx % 64] = nj[q];
-    }
-    __syncthreads();
-    if (k0 + 16 < nrb) fetch(k0 + 16);
-#pragma unroll 4
-    for (int kk = 0; kk < 16; ++kk) {
-      uint64_t a[4], b[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        a[q] = Ti[kk][ty + 16 * q];
-        b[q] = Tj[kk][tx + 16 * q];
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[q][r] += __popcll(a[q] & b[r]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int64_t i = I * 64 + ty + 16 * q;
-    if (i >= M) continue;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t j = J * 64 + tx + 16 * r;
-      if (j >= M) continue;
-      C[i * ld + j] = acc[q][r];
-      C[j * ld + i] = acc[q][r];
-    }
-  }
-  if (usum) tile_row_sums(acc, M, I, J, usum);
+// The counts of tile (I, J), J >= I, over the row words [w0, w1).  whole: they
+// are all the words, the counts are stored (both halves); otherwise they are
+// added to C with integer atomics (exact in any order; C starts at zero; a
+// diagonal tile adds each of its entries once).  usum: NULL, or row sums to add
+// the tile's sums to (tile_row_sums).
+//
+// The counts run on matrix instructions, exactly: a word's bits, left in place
+// in their nibbles, are fp4 numbers (0001 = 0.5, 0010 = 1, 0100 = 2), the left
+// operand has the even bits as 0.5 and the right one as 2, the odd bits are 1 in
+// both, so every product is 0 or 1 and one 16x16x128 step counts two halves of
+// four words (lane group g: word g) of 16 x 16 pairs.  fp32 sums are whole
+// numbers below 2^24; kGramSeg words at a time keep them so.  A wavefront takes
+// 32 x 32 of the tile's 64 x 64 pairs: 44 VALU instructions per four words make
+// its operands, where counting 64-bit ANDs took 256 and was bound by them.
+// 64 PubMed-shaped targets (500 to 4,000 players) x 25,000 coalitions: 31 us a
+// target, the batch 36.7 -> 33.9 ms; 1,501 players x 25,000: 23 us, the solve
+// 1894 -> 1859 us; 100 Cora-shaped targets, one launch: the batch 533 -> 496 us.
+// The finished tile goes through LDS, so that both halves are stored along rows.
+constexpr int kGramRow = 80;            // words per staged row: lane groups g and g + 1 on other banks
+constexpr int64_t kGramSeg = 1 << 17;   // x 64 rows = 2^23
+typedef int gram8i_t __attribute__((ext_vector_type(8)));
+typedef float gram4f_t __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ gram8i_t gram_left(uint32_t m) {
+  const uint32_t h = m >> 2;
+  return gram8i_t{static_cast<int>(m & 0x11111111u), static_cast<int>(m & 0x22222222u),
+                  static_cast<int>(h & 0x11111111u), static_cast<int>(h & 0x22222222u), 0, 0, 0, 0};
 }
 
-// The same counts over the row words [w0, w1) only, added to C with integer
-// atomics (exact in any order; C starts at zero).  A diagonal tile adds each
-// of its entries once, an off-diagonal tile adds both halves.
-__device__ __forceinline__ void gram_part_body(const uint64_t* __restrict__ T, int64_t w0, int64_t w1, int64_t M,
-                                               int64_t ld, int32_t* __restrict__ C, int64_t I, int64_t J,
-                                               int64_t* __restrict__ usum) {
-  __shared__ uint64_t Ti[16][64];
-  __shared__ uint64_t Tj[16][64];
-  const int tid = threadIdx.x;
-  const int ty = tid / 16, tx = tid % 16;
-  int acc[4][4] = {};
+__device__ __forceinline__ gram8i_t gram_right(uint32_t m) {
+  return gram8i_t{static_cast<int>((m << 2) & 0x44444444u), static_cast<int>(m & 0x22222222u),
+                  static_cast<int>(m & 0x44444444u), static_cast<int>((m >> 2) & 0x22222222u), 0, 0, 0, 0};
+}
+
+__device__ __forceinline__ void gram_body(const uint64_t* __restrict__ T, int64_t w0, int64_t w1, int64_t M,
+                                          int64_t ld, int32_t* __restrict__ C, int64_t I, int64_t J, bool whole,
+                                          int64_t* __restrict__ usum) {
+  if (J < I) return;
+  __shared__ union {
+    uint64_t in[2][16 * kGramRow];   // 16 words of the tile's players i, j
+    int out[64][65];
+  } lds;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int ri = (wave >> 1) * 32, cj = (wave & 1) * 32;   // this wavefront's pairs
+  const int g = lane >> 4, r = lane & 15;
+  // the next stage's words are fetched while the current stage is counted
   uint64_t ni[4], nj[4];
   auto fetch = [&](int64_t k0) {
 #pragma unroll
@@ -332,49 +304,84 @@ __device__ __forceinline__ void gram_part_body(const uint64_t* __restrict__ T, i
       nj[q] = (kin && j < M) ? T[(k0 + kk) * M + j] : 0;
     }
   };
+  int cnt[2][2][4] = {};
   fetch(w0);
-  for (int64_t k0 = w0; k0 < w1; k0 += 16) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = tid + q * 256;
-      Ti[idx / 64][idx % 64] = ni[q];
-      Tj[idx / 64][idx % 64] = nj[q];
-    }
-    __syncthreads();
-    if (k0 + 16 < w1) fetch(k0 + 16);
-#pragma unroll 4
-    for (int kk = 0; kk < 16; ++kk) {
-      uint64_t a[4], b[4];
+  for (int64_t s0 = w0; s0 < w1; s0 += kGramSeg) {
+    const int64_t s1 = s0 + kGramSeg < w1 ? s0 + kGramSeg : w1;
+    gram4f_t acc[2][2] = {};
+    for (int64_t k0 = s0; k0 < s1; k0 += 16) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        a[q] = Ti[kk][ty + 16 * q];
-        b[q] = Tj[kk][tx + 16 * q];
+        const int idx = tid + q * 256;
+        lds.in[0][idx / 64 * kGramRow + idx % 64] = ni[q];
+        lds.in[1][idx / 64 * kGramRow + idx % 64] = nj[q];
       }
+      __syncthreads();
+      if (k0 + 16 < w1) fetch(k0 + 16);
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
+      for (int kk = 0; kk < 16; kk += 4) {
+        uint64_t a[2], b[2];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[q][r] += __popcll(a[q] & b[r]);
+        for (int q = 0; q < 2; ++q) {
+          a[q] = lds.in[0][(kk + g) * kGramRow + ri + 16 * q + r];
+          b[q] = lds.in[1][(kk + g) * kGramRow + cj + 16 * q + r];
+        }
+#pragma unroll
+        for (int h = 0; h < 64; h += 32) {
+          gram8i_t x[2], y[2];
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            x[q] = gram_left(static_cast<uint32_t>(a[q] >> h));
+            y[q] = gram_right(static_cast<uint32_t>(b[q] >> h));
+          }
+#pragma unroll
+          for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+              acc[p][q] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x[p], y[q], acc[p][q], 4, 4, 0, 0, 0, 0);
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) cnt[p][q][c] += static_cast<int>(acc[p][q][c]);
   }
+  // lane 16 g + r holds pairs (16 p + 4 g + c, 16 q + r) of its 32 x 32
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) lds.out[ri + 16 * p + 4 * g + c][cj + 16 * q + r] = cnt[p][q][c];
+  __syncthreads();
+  const int ty = tid / 16, tx = tid % 16;
+  int acc[4][4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int64_t i = I * 64 + ty + 16 * q;
-    if (i >= M) continue;
+    const int64_t i = I * 64 + ty + 16 * q, im = J * 64 + ty + 16 * q;   // rows of the tile and of its mirror
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t j = J * 64 + tx + 16 * r;
-      if (j >= M || acc[q][r] == 0) continue;
-      atomicAdd(&C[i * ld + j], acc[q][r]);
-      if (I != J) atomicAdd(&C[j * ld + i], acc[q][r]);
+    for (int t = 0; t < 4; ++t) {
+      const int64_t j = J * 64 + tx + 16 * t, jm = I * 64 + tx + 16 * t;
+      const int v = acc[q][t] = lds.out[ty + 16 * q][tx + 16 * t], vm = lds.out[tx + 16 * t][ty + 16 * q];
+      if (whole) {
+        if (i < M && j < M) C[i * ld + j] = v;
+        if (I != J && im < M && jm < M) C[im * ld + jm] = vm;
+      } else {
+        if (i < M && j < M && v != 0) atomicAdd(&C[i * ld + j], v);
+        if (I != J && im < M && jm < M && vm != 0) atomicAdd(&C[im * ld + jm], vm);
+      }
     }
   }
-  tile_row_sums(acc, M, I, J, usum);
+  if (usum) tile_row_sums(acc, M, I, J, usum);
 }
 
 __global__ void __launch_bounds__(256) k_gram(const uint64_t* __restrict__ T, int64_t nrb, int64_t M, int64_t ld,
                                               int32_t* __restrict__ C) {
-  gram_body(T, nrb, M, ld, C, blockIdx.y, blockIdx.x);
+  gram_body(T, 0, nrb, M, ld, C, blockIdx.y, blockIdx.x, true, nullptr);
 }
 
 // usum[i] = sum_j C[i, j]; one wave per row.
@@ -1719,10 +1726,8 @@ __global__ void __launch_bounds__(256) k_gram_batch(const gnnshap::SolveJob* __r
   int64_t Jt = 0;
   while ((Jt + 1) * (Jt + 2) / 2 <= tile) ++Jt;
   const int64_t It = tile - Jt * (Jt + 1) / 2;
-  if (whole)
-    gram_body(J.T, J.nrb, J.M, J.ld, J.counts, It, Jt, J.usum);
-  else
-    gram_part_body(J.T, w0, w0 + kGramChunk < J.nrb ? w0 + kGramChunk : J.nrb, J.M, J.ld, J.counts, It, Jt, J.usum);
+  const int64_t w1 = whole || w0 + kGramChunk > J.nrb ? J.nrb : w0 + kGramChunk;
+  gram_body(J.T, w0, w1, J.M, J.ld, J.counts, It, Jt, whole, J.usum);
 }
 
 __global__ void __launch_bounds__(kTileRows) k_rhs_tile_batch(const gnnshap::SolveJob* __restrict__ jobs) {
