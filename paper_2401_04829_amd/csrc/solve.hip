@@ -1305,22 +1305,27 @@ __global__ void __launch_bounds__(kMidThreads) k_solve_mid(float* G, int64_t ld,
 
 // ---- multi-block path: MFMA GEMM ---------------------------------------------------------
 
-constexpr int kGT = 128;        // output tile edge
 constexpr int kGK = 32;         // K chunk staged in LDS
 constexpr int kGP = kGK + 4;    // LDS row pitch (floats)
 
-// C = beta C + alpha A B^T over 128x128 tiles, fp32 MFMA 32x32x2; rows of A and
+// C = beta C + alpha A B^T over tiles of 64 XR x 64 XC, fp32 MFMA 32x32x2; rows of A and
 // B are K contiguous floats (K a multiple of 32; lda, ldb multiples of 4 and
-// 16-byte aligned bases).  Four wavefronts own 64x64 quadrants; lane half h
-// feeds k in [16h, 16h+16) of each chunk.  kLower: blockIdx.x enumerates the
+// 16-byte aligned bases).  Four wavefronts own the tile's quadrants; lane half h
+// feeds k in [16h, 16h+16) of each chunk, so an element's sum does not depend on
+// the tile.  kLower (XR = XC): blockIdx.x enumerates the
 // tiles with J <= I (diagonal tiles written whole).  A may alias C when one
 // tile column covers all of n (the tile reads its rows before writing them).
-template <bool kLower>
+// The K loop is short (kPB), so latency bounds a tile: C is read before it and
+// the next chunk under the current one's products.  1,501 players: trailing
+// update 36 -> 7.5 us (C's loads waited for the stores before them), panel
+// 19 -> 9.8 us (64 rows per workgroup); 24 PubMed-shaped systems 118 -> 96 us
+// and 21.6 -> 15.6 us, where the trailing matrices' traffic bounds the former.
+template <bool kLower, int XR, int XC>
 __device__ __forceinline__ void k_gemm_nt_body(const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                                int64_t ldc, int64_t m, int64_t n, int64_t K, float alpha,
                                                float beta, int64_t tiles_n, int64_t bx) {
-  __shared__ __align__(16) float As[kGT * kGP];
-  __shared__ __align__(16) float Bs[kGT * kGP];
+  __shared__ __align__(16) float As[64 * XR * kGP];
+  __shared__ __align__(16) float Bs[64 * XC * kGP];
   const int64_t t = bx;
   int64_t I, J;
   if (kLower) {
@@ -1334,63 +1339,91 @@ __device__ __forceinline__ void k_gemm_nt_body(const float* A, int64_t lda, cons
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1, h = lane >> 5, rl = lane & 31;
-  const int64_t i0 = I * kGT, j0 = J * kGT;
-  f32x16 acc[2][2];
+  const int64_t i0 = I * 64 * XR, j0 = J * 64 * XC;
+  f32x4 va[2 * XR], vb[2 * XC];
+  auto fetch = [&](int64_t p0) {   // thread: row tid / 8 + 32 q, floats 4 (tid % 8) ..
+    const int r = tid >> 3, c4 = (tid & 7) << 2;
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+    for (int q = 0; q < 2 * XR; ++q) {
+      va[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (i0 + r + 32 * q < m) va[q] = *reinterpret_cast<const f32x4*>(A + (i0 + r + 32 * q) * lda + p0 + c4);
+    }
 #pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = f32x16{};
+    for (int q = 0; q < 2 * XC; ++q) {
+      vb[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (j0 + r + 32 * q < n) vb[q] = *reinterpret_cast<const f32x4*>(B + (j0 + r + 32 * q) * ldb + p0 + c4);
+    }
+  };
+  fetch(0);
+  const int64_t crow = i0 + wr * 32 * XR + 4 * h, ccol = j0 + wc * 32 * XC + rl;
+  float cv[XR][XC][16];
+  if (beta != 0.f) {
+#pragma unroll
+    for (int x = 0; x < XR; ++x)
+#pragma unroll
+      for (int y = 0; y < XC; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int64_t row = crow + x * 32 + 8 * (r >> 2) + (r & 3), col = ccol + y * 32;
+          cv[x][y][r] = row < m && col < n ? C[row * ldc + col] : 0.f;
+        }
+  }
+  f32x16 acc[XR][XC];
+#pragma unroll
+  for (int x = 0; x < XR; ++x)
+#pragma unroll
+    for (int y = 0; y < XC; ++y) acc[x][y] = f32x16{};
   for (int64_t p0 = 0; p0 < K; p0 += kGK) {
+    {
+      const int r = tid >> 3, c4 = (tid & 7) << 2;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = tid + q * 256;
-      const int r = idx >> 3, c4 = (idx & 7) << 2;
-      f32x4 va = {0.f, 0.f, 0.f, 0.f}, vb = {0.f, 0.f, 0.f, 0.f};
-      if (i0 + r < m) va = *reinterpret_cast<const f32x4*>(A + (i0 + r) * lda + p0 + c4);
-      if (j0 + r < n) vb = *reinterpret_cast<const f32x4*>(B + (j0 + r) * ldb + p0 + c4);
-      *reinterpret_cast<f32x4*>(As + r * kGP + c4) = va;
-      *reinterpret_cast<f32x4*>(Bs + r * kGP + c4) = vb;
+      for (int q = 0; q < 2 * XR; ++q) *reinterpret_cast<f32x4*>(As + (r + 32 * q) * kGP + c4) = va[q];
+#pragma unroll
+      for (int q = 0; q < 2 * XC; ++q) *reinterpret_cast<f32x4*>(Bs + (r + 32 * q) * kGP + c4) = vb[q];
     }
     __syncthreads();
+    if (p0 + kGK < K) fetch(p0 + kGK);
 #pragma unroll
     for (int kk = 0; kk < 16; kk += 4) {
-      f32x4 a[2], b[2];
+      f32x4 a[XR], b[XC];
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        a[s] = *reinterpret_cast<const f32x4*>(As + (wr * 64 + s * 32 + rl) * kGP + h * 16 + kk);
-        b[s] = *reinterpret_cast<const f32x4*>(Bs + (wc * 64 + s * 32 + rl) * kGP + h * 16 + kk);
-      }
+      for (int x = 0; x < XR; ++x)
+        a[x] = *reinterpret_cast<const f32x4*>(As + (wr * 32 * XR + x * 32 + rl) * kGP + h * 16 + kk);
+#pragma unroll
+      for (int y = 0; y < XC; ++y)
+        b[y] = *reinterpret_cast<const f32x4*>(Bs + (wc * 32 * XC + y * 32 + rl) * kGP + h * 16 + kk);
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < XR; ++x)
 #pragma unroll
-          for (int y = 0; y < 2; ++y)
+          for (int y = 0; y < XC; ++y)
             acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x][e], b[y][e], acc[x][y], 0, 0, 0);
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+  for (int x = 0; x < XR; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y) {
-      const int64_t col = j0 + wc * 64 + y * 32 + rl;
+    for (int y = 0; y < XC; ++y)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int64_t row = i0 + wr * 64 + x * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (row < m && col < n) {
-          float* c = C + row * ldc + col;
-          *c = beta == 0.f ? alpha * acc[x][y][r] : beta * *c + alpha * acc[x][y][r];
-        }
+        const int64_t row = crow + x * 32 + 8 * (r >> 2) + (r & 3), col = ccol + y * 32;
+        if (row < m && col < n)
+          C[row * ldc + col] = beta == 0.f ? alpha * acc[x][y][r] : beta * cv[x][y][r] + alpha * acc[x][y][r];
       }
-    }
 }
 
-template <bool kLower>
+// Edge (in 64s) of the trailing update's tiles, for the tiles of 128 that a
+// launch would have: below one workgroup per CU, tiles of 64 give four times as
+// many workgroups of a quarter of the work each.
+int syrk_edge(int64_t tiles) { return tiles < 256 ? 1 : 2; }
+
+template <bool kLower, int XR, int XC>
 __global__ void __launch_bounds__(256) k_gemm_nt(const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                                  int64_t ldc, int64_t m, int64_t n, int64_t K, float alpha,
                                                  float beta, int64_t tiles_n) {
-  k_gemm_nt_body<kLower>(A, lda, B, ldb, C, ldc, m, n, K, alpha, beta, tiles_n, blockIdx.x);
+  k_gemm_nt_body<kLower, XR, XC>(A, lda, B, ldb, C, ldc, m, n, K, alpha, beta, tiles_n, blockIdx.x);
 }
 
 // ---- multi-block path: triangular solves ------------------------------------------------
@@ -1621,21 +1654,22 @@ __global__ void __launch_bounds__(256) k_trsm_mb(const gnnshap::MbJob* __restric
   const int64_t r0 = o + kPB;
   if (r0 >= J.M) return;
   const int64_t rows = J.M - r0;
-  if (static_cast<int64_t>(blockIdx.x) >= (rows + kGT - 1) / kGT) return;
+  if (static_cast<int64_t>(blockIdx.x) >= (rows + 63) / 64) return;
   float* panel = J.G + r0 * J.ld + o;
-  k_gemm_nt_body<false>(panel, J.ld, J.Winv, kPB, panel, J.ld, rows, kPB, kPB, 1.f, 0.f, 1, blockIdx.x);
+  k_gemm_nt_body<false, 1, 2>(panel, J.ld, J.Winv, kPB, panel, J.ld, rows, kPB, kPB, 1.f, 0.f, 1, blockIdx.x);
 }
 
-// trailing lower triangle -= panel panel^T
+// trailing lower triangle -= panel panel^T, in tiles of 64 X
+template <int X>
 __global__ void __launch_bounds__(256) k_syrk_mb(const gnnshap::MbJob* __restrict__ jobs, int64_t o) {
   const gnnshap::MbJob J = jobs[blockIdx.y];
   const int64_t r0 = o + kPB;
   if (r0 >= J.M) return;
   const int64_t rows = J.M - r0;
-  const int64_t tr = (rows + kGT - 1) / kGT;
+  const int64_t tr = (rows + 64 * X - 1) / (64 * X);
   if (static_cast<int64_t>(blockIdx.x) >= tr * (tr + 1) / 2) return;
   const float* panel = J.G + r0 * J.ld + o;
-  k_gemm_nt_body<true>(panel, J.ld, panel, J.ld, J.G + r0 * J.ld + r0, J.ld, rows, rows, kPB, -1.f, 1.f, 0,
+  k_gemm_nt_body<true, X, X>(panel, J.ld, panel, J.ld, J.G + r0 * J.ld + r0, J.ld, rows, rows, kPB, -1.f, 1.f, 0,
                        blockIdx.x);
 }
 
@@ -2337,18 +2371,20 @@ int gnnshap::solve_wls_start(const gnnshap_sample_plan* plan, const gnnshap_clas
     const int64_t r0 = o + kPB;
     if (r0 >= M) break;
     const int64_t rows = M - r0;
-    const int64_t tr = gnnshap::ceil_div(rows, kGT);
     float* panel = w.G + r0 * ld + o;
     {
       GS_TIMED("k_trsm", s);   // panel <- panel L_jj^-T = panel Winv^T
-      k_gemm_nt<false><<<static_cast<unsigned>(tr), 256, 0, s>>>(panel, ld, w.Winv, kPB, panel, ld, rows, kPB, kPB,
-                                                                  1.f, 0.f, 1);
+      k_gemm_nt<false, 1, 2><<<static_cast<unsigned>(gnnshap::ceil_div(rows, 64)), 256, 0, s>>>(
+          panel, ld, w.Winv, kPB, panel, ld, rows, kPB, kPB, 1.f, 0.f, 1);
     }
     GS_LAUNCHED();
     {
       GS_TIMED("k_syrk", s);   // trailing lower triangle -= panel panel^T
-      k_gemm_nt<true><<<static_cast<unsigned>(tr * (tr + 1) / 2), 256, 0, s>>>(panel, ld, panel, ld, w.G + r0 * ld + r0,
-                                                                                ld, rows, rows, kPB, -1.f, 1.f, 0);
+      const int64_t tr2 = gnnshap::ceil_div(rows, 128);
+      const int edge = syrk_edge(tr2 * (tr2 + 1) / 2);
+      const int64_t tr = gnnshap::ceil_div(rows, 64 * edge);
+      (edge == 1 ? k_gemm_nt<true, 1, 1> : k_gemm_nt<true, 2, 2>)<<<static_cast<unsigned>(tr * (tr + 1) / 2), 256, 0, s>>>(
+          panel, ld, panel, ld, w.G + r0 * ld + r0, ld, rows, rows, kPB, -1.f, 1.f, 0);
     }
     GS_LAUNCHED();
   }
@@ -2497,15 +2533,17 @@ int gnnshap::launch_solve_mb(const MbJob* jobs, int64_t n, int64_t max_M, hipStr
     GS_LAUNCHED();
     const int64_t r0 = o + kPB;
     if (r0 >= max_M) break;
-    const int64_t tr = ceil_div(max_M - r0, kGT);
     {
       GS_TIMED("k_trsm_mb", s);
-      k_trsm_mb<<<dim3(static_cast<unsigned>(tr), nn), 256, 0, s>>>(jobs, o);
+      k_trsm_mb<<<dim3(static_cast<unsigned>(ceil_div(max_M - r0, 64)), nn), 256, 0, s>>>(jobs, o);
     }
     GS_LAUNCHED();
     {
       GS_TIMED("k_syrk_mb", s);
-      k_syrk_mb<<<dim3(static_cast<unsigned>(tr * (tr + 1) / 2), nn), 256, 0, s>>>(jobs, o);
+      const int64_t tr2 = ceil_div(max_M - r0, 128);
+      const int edge = syrk_edge(tr2 * (tr2 + 1) / 2 * n);
+      const int64_t tr = ceil_div(max_M - r0, 64 * edge);
+      (edge == 1 ? k_syrk_mb<1> : k_syrk_mb<2>)<<<dim3(static_cast<unsigned>(tr * (tr + 1) / 2), nn), 256, 0, s>>>(jobs, o);
     }
     GS_LAUNCHED();
   }
