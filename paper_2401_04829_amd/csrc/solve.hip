@@ -711,60 +711,7 @@ __global__ void k_zero_info(int32_t* info) { *info = 0; }
 
 constexpr int kHP = 68;                                  // LDS pitch of a 64x64 block (16-byte rows)
 constexpr int kHB = 64 * kHP;                            // floats per block
-constexpr size_t kPotrfLds = (5 * kHB + 64) * sizeof(float);
-
-// One wavefront: Cholesky of a 64x64 block held row `lane` per lane in a[]
-// (rows past the real block are the identity).  Column k goes through LDS
-// (`col`, 64 floats): every lane reads the pivot and the entries below it as
-// 16-byte broadcasts and applies the rank-1 update to its row.  Entries above
-// the diagonal are left undefined.  The first non-positive pivot (1-based,
-// offset o) goes to *info and is replaced by 1.
-__device__ __forceinline__ void chol_wave(float (&a)[64], float* col, int64_t o, int32_t* info) {
-  const int lane = threadIdx.x & 63;
-  int bad = 0;
-#pragma unroll
-  for (int k = 0; k < 64; ++k) {
-    col[lane] = a[k];
-    __builtin_amdgcn_wave_barrier();
-    const float piv = col[k];
-    const bool ok = piv > 0.f;
-    bad = (bad == 0 && !ok) ? k + 1 : bad;
-    const float rs = 1.0f / sqrtf(ok ? piv : 1.f);
-    a[k] *= rs;                    // L[lane][k] (lane k: sqrt of the pivot)
-    const float t = a[k] * rs;     // L[lane][k] / L[k][k]: L[j][k] = col[j] rs
-#pragma unroll
-    for (int j4 = (k + 1) & ~3; j4 < 64; j4 += 4) {
-      const f32x4 q = *reinterpret_cast<const f32x4*>(col + j4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (j4 + e > k) a[j4 + e] -= t * q[e];
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-  if (bad != 0 && lane == 0) atomicCAS(info, 0, static_cast<int32_t>(o + bad));
-}
-
-// One wavefront: column `lane` of W = L^-1 into w[] from Lt = L^T (pitch kHP)
-// by right-looking forward substitution; row p of Lt is read as 16-byte
-// broadcasts.  Entries above the diagonal come out exactly zero.
-__device__ __forceinline__ void inv_wave(const float* Lt, float (&w)[64]) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int c = 0; c < 64; ++c) w[c] = c == lane ? 1.f : 0.f;
-#pragma unroll
-  for (int p = 0; p < 64; ++p) {
-    const float* row = Lt + p * kHP;
-    w[p] *= 1.0f / row[p];
-    const float u = w[p];
-#pragma unroll
-    for (int j4 = (p + 1) & ~3; j4 < 64; j4 += 4) {
-      const f32x4 q = *reinterpret_cast<const f32x4*>(row + j4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (j4 + e > p) w[j4 + e] -= q[e] * u;
-    }
-  }
-}
+constexpr size_t kPotrfLds = (5 * kHB + 128) * sizeof(float);
 
 // ---- one wavefront: Cholesky factor and its inverse of a 64x64 block -------------------
 //
@@ -941,9 +888,8 @@ __device__ __forceinline__ void chol_inv_rec(float* S, float* Wb, int64_t o, int
 }
 
 // One wavefront: S (64x64, pitch kHP) <- L = chol(S) (zeros above the
-// diagonal) and Wb <- L^-1.  `col` is unused (kept for the callers' layout).
-__device__ __forceinline__ void chol_inv64(float* S, float* Wb, float* col, int64_t o, int32_t* info) {
-  (void)col;
+// diagonal) and Wb <- L^-1.
+__device__ __forceinline__ void chol_inv64(float* S, float* Wb, int64_t o, int32_t* info) {
   chol_inv_rec<64>(S, Wb, o, info);
 }
 
@@ -988,17 +934,23 @@ __device__ __forceinline__ void mm64(const float* X, const float* Y, float* D, f
 //   L11 = chol(A11), W11 = L11^-1, L21 = A21 W11^T, A22 -= L21 L21^T,
 //   L22 = chol(A22), W22 = L22^-1, W21 = -W22 (L21 W11).
 // L goes back to the lower part of G, W = L^-1 (zero above the diagonal) to Winv.
+// The forward substitution rides along: x[o ..] = W rhs[o ..], and the trailing
+// update's launch takes L x off the rows below.  (A kernel of its own per 256
+// rows took 28 us at 1,501 players, most of it one workgroup's reads of the
+// triangle: the solve 1303 -> 1117 us, 64 PubMed-shaped targets 31.2 -> 30.9 ms.)
 __device__ __forceinline__ void k_potrf_body(float* G, int64_t ld, int64_t M, int64_t o, int32_t* info,
-                                             float* __restrict__ Winv) {
+                                             float* __restrict__ Winv, const float* __restrict__ rhs,
+                                             float* __restrict__ x) {
   extern __shared__ __align__(16) unsigned char smem[];
   float* S0 = reinterpret_cast<float*>(smem);  // A11 -> L11, later L21 W11
   float* S1 = S0 + kHB;                        // W11
   float* S2 = S1 + kHB;                        // A21 -> L21, later W21
   float* S3 = S2 + kHB;                        // A22 -> L22
   float* S4 = S3 + kHB;                        // W22
-  float* col = S4 + kHB;
+  float* rv = S4 + kHB;                        // rhs of these rows
   const int tid = threadIdx.x, wave = tid >> 6;
   const int64_t n = M - o < kPB ? M - o : kPB;
+  if (tid < kPB) rv[tid] = tid < n ? rhs[o + tid] : 0.f;
   {
     // all 64 loads of a thread in flight before the LDS stores
     float v[kPB * kPB / 256];
@@ -1018,7 +970,7 @@ __device__ __forceinline__ void k_potrf_body(float* G, int64_t ld, int64_t M, in
     }
   }
   __syncthreads();
-  if (wave == 0) chol_inv64(S0, S1, col, o, info);
+  if (wave == 0) chol_inv64(S0, S1, o, info);
   __syncthreads();
   mm64<true>(S2, S1, S2, 1.f, 0.f);     // L21
   mm64<true>(S2, S2, S3, -1.f, 1.f);    // A22 - L21 L21^T
@@ -1028,9 +980,30 @@ __device__ __forceinline__ void k_potrf_body(float* G, int64_t ld, int64_t M, in
   }
   __syncthreads();
   mm64<false>(S2, S1, S0, 1.f, 0.f);    // L21 W11
-  if (wave == 0) chol_inv64(S3, S4, col, o + 64, info);
+  if (wave == 0) chol_inv64(S3, S4, o + 64, info);
   __syncthreads();
   mm64<false>(S4, S0, S2, -1.f, 0.f);   // W21
+  {   // x: two lanes per row, 16-byte reads in turn
+    const int r = tid >> 1, e = (tid & 1) * 4;
+    const float* lo = r < 64 ? S1 + r * kHP : S2 + (r - 64) * kHP;
+    const float* hi = S4 + (r & 63) * kHP;
+    float acc = 0.f;
+#pragma unroll
+    for (int c = 0; c < 64; c += 8) {
+      const f32x4 w = *reinterpret_cast<const f32x4*>(lo + c + e), v = *reinterpret_cast<const f32x4*>(rv + c + e);
+      acc += (w[0] * v[0] + w[1] * v[1]) + (w[2] * v[2] + w[3] * v[3]);
+    }
+    if (r >= 64) {
+#pragma unroll
+      for (int c = 0; c < 64; c += 8) {
+        const f32x4 w = *reinterpret_cast<const f32x4*>(hi + c + e),
+                    v = *reinterpret_cast<const f32x4*>(rv + 64 + c + e);
+        acc += (w[0] * v[0] + w[1] * v[1]) + (w[2] * v[2] + w[3] * v[3]);
+      }
+    }
+    acc += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(acc), 0xB1, 0xf, 0xf, true));
+    if ((tid & 1) == 0 && r < n) x[o + r] = acc;
+  }
   for (int t = tid; t < 64 * 64; t += 256) {
     const int r = t / 64, c = t % 64;
     if (64 + r < n && 64 + c < n && c <= r) G[(o + 64 + r) * ld + o + 64 + c] = S3[r * kHP + c];
@@ -1045,8 +1018,9 @@ __device__ __forceinline__ void k_potrf_body(float* G, int64_t ld, int64_t M, in
 }
 
 __global__ void __launch_bounds__(256) k_potrf(float* G, int64_t ld, int64_t M, int64_t o, int32_t* info,
-                                               float* __restrict__ Winv) {
-  k_potrf_body(G, ld, M, o, info, Winv);
+                                               float* __restrict__ Winv, const float* __restrict__ rhs,
+                                               float* __restrict__ x) {
+  k_potrf_body(G, ld, M, o, info, Winv, rhs, x);
 }
 
 // ---- one-workgroup path (systems of up to kMidMax players) --------------------------------
@@ -1065,7 +1039,7 @@ __global__ void __launch_bounds__(256) k_potrf(float* G, int64_t ld, int64_t M, 
 
 constexpr int kMidThreads = 256;
 constexpr int kMidBlk = kMidMax / 64;
-constexpr size_t kMidLds = (static_cast<size_t>(1 + kMidBlk) * kHB + 64 + kMidMax + 4 * 64) * sizeof(float);
+constexpr size_t kMidLds = (static_cast<size_t>(1 + kMidBlk) * kHB + kMidMax + 4 * 64) * sizeof(float);
 
 // G: G~ on its lower triangle (row stride ld) on entry, the factor on exit;
 // dvg: the summed right-hand side before centring; Wd: room for the
@@ -1078,8 +1052,7 @@ __device__ __forceinline__ void solve_mid_body(float* G, int64_t ld, int64_t M, 
   float* D0 = reinterpret_cast<float*>(smem);  // diagonal block -> L_pp (and the look-ahead's)
   float* D1 = D0 + kHB;                        // W_pp = L_pp^-1
   float* P = D1 + kHB;                         // blocks below the diagonal block -> L_Ip
-  float* col = P + (kMidBlk - 1) * kHB;        // 64: column broadcasts of the wavefront Cholesky
-  float* rv = col + 64;                        // kMidMax: r, then z, then psi
+  float* rv = P + (kMidBlk - 1) * kHB;         // kMidMax: r, then z, then psi
   float* red8 = rv + kMidMax;                  // NW x 64
   __shared__ double red[NW];
   __shared__ double sc[2];                     // mean of dv, Delta
@@ -1126,7 +1099,7 @@ __device__ __forceinline__ void solve_mid_body(float* G, int64_t ld, int64_t M, 
       }
     }
     __builtin_amdgcn_wave_barrier();
-    chol_inv64(D0, D1, col, o, info);
+    chol_inv64(D0, D1, o, info);
   };
   // one task: trailing quadrant (qr, qc) of tile (I, J) below panel o: A -= L_Io L_Jo^T
   auto trailing = [&](int64_t o, int I, int J, int q) {
@@ -1428,10 +1401,11 @@ __global__ void __launch_bounds__(256) k_gemm_nt(const float* A, int64_t lda, co
 
 // ---- multi-block path: triangular solves ------------------------------------------------
 //
-// Segments [s0, s1) of at most kSeg rows: one workgroup loads the segment's
+// The forward substitution rides along with the factorisation (k_potrf_body,
+// k_syrk_body).  Backward: segments [s0, s1) of at most kSeg rows: one workgroup loads the segment's
 // lower triangle into LDS (packed, row i at i(i+1)/2) and substitutes through
-// it in 64-row blocks (one wavefront per diagonal block); multi-block GEMVs
-// then carry the segment's unknowns to the rows outside it.
+// it in 64-row blocks (one wavefront per diagonal block); a multi-block GEMV
+// then carries the segment's unknowns to the rows before it.
 
 __device__ __forceinline__ int64_t tri(int64_t i, int64_t j) { return ((i * (i + 1)) >> 1) + j; }
 
@@ -1439,8 +1413,8 @@ constexpr size_t kTrsvLds = (kSeg * (kSeg + 1) / 2 + 2 * kSeg) * sizeof(float);
 
 // Packed triangle of rows/cols [s0, s1) and reciprocal pivots: a wavefront takes every sixteenth row, its
 // loads (four of 64 columns per row) all in flight at once.  One workgroup reads the 131 KB triangle: its
-// misses bound the kernel.  Per segment (1,501 players): forward 40 -> 28 us, backward 50 -> 32 us, with four
-// lanes per row in the updates below instead of a wavefront (forward) or a lane (backward).
+// misses bound the kernel.  Per segment (1,501 players): 50 -> 32 us, with four
+// lanes per row in the updates below instead of one.
 __device__ __forceinline__ void load_segment(const float* __restrict__ G, int64_t ld, int64_t s0, int64_t len,
                                              float* Ls, float* rd) {
   constexpr int kRows = kSeg / 16, kCols = kSeg / 64;
@@ -1477,55 +1451,6 @@ __device__ __forceinline__ float quad_sum(float v) {
   return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xf, 0xf, true));
 }
 
-// Forward: x[s0:s1) = L[s0:s1, s0:s1)^-1 rhs[s0:s1) (rhs holds the earlier segments' updates).
-__device__ __forceinline__ void k_trsv_fwd_body(const float* __restrict__ G, int64_t ld, int64_t s0, int64_t s1,
-                                                const float* __restrict__ rhs, float* __restrict__ x) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  float* Ls = reinterpret_cast<float*>(smem);
-  float* rd = Ls + kSeg * (kSeg + 1) / 2;
-  float* v = rd + kSeg;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int64_t len = s1 - s0;
-  for (int64_t t = tid; t < len; t += blockDim.x) v[t] = rhs[s0 + t];
-  load_segment(G, ld, s0, len, Ls, rd);
-  for (int64_t ob = 0; ob < len; ob += kTB) {
-    const int nbe = static_cast<int>(len - ob < kTB ? len - ob : kTB);
-    if (wave == 0) {
-      // b_k is final once the columns before k are applied: x_k = b_k / L_kk
-      const int r = lane < nbe ? lane : 0;
-      float b = lane < nbe ? v[ob + lane] : 0.f;
-      float lr[kTB];
-#pragma unroll
-      for (int c = 0; c < kTB; ++c) lr[c] = (lane < nbe && c < lane) ? Ls[tri(ob + r, ob + c)] : 0.f;
-#pragma unroll
-      for (int k = 0; k < kTB; ++k) {
-        const float rk = k < nbe ? rd[ob + k] : 1.f;
-        b -= lr[k] * (bcast(b, k) * rk);
-      }
-      if (lane < nbe) v[ob + lane] = b * rd[ob + lane];
-    }
-    __syncthreads();
-    // the rows below (the block is whole when there are any): four lanes per row
-    const int i = static_cast<int>(ob) + kTB + (tid >> 2);
-    if (i < len) {
-      const float* row = Ls + (i * (i + 1) >> 1) + ob + (tid & 3);
-      const float* xo = v + ob + (tid & 3);
-      float p = 0.f;
-#pragma unroll
-      for (int c = 0; c < kTB; c += 4) p += row[c] * xo[c];
-      p = quad_sum(p);
-      if ((tid & 3) == 0) v[i] -= p;
-    }
-    __syncthreads();
-  }
-  for (int64_t t = tid; t < len; t += blockDim.x) x[s0 + t] = v[t];
-}
-
-__global__ void __launch_bounds__(1024) k_trsv_fwd(const float* __restrict__ G, int64_t ld, int64_t s0, int64_t s1,
-                                                   const float* __restrict__ rhs, float* __restrict__ x) {
-  k_trsv_fwd_body(G, ld, s0, s1, rhs, x);
-}
-
 // rhs[i] -= L[i, s0:s1) x[s0:s1) for i >= s1; one wavefront per row, four floats per lane.
 __device__ __forceinline__ void k_gemv_fwd_body(const float* __restrict__ G, int64_t ld, int64_t M, int64_t s0,
                                                 int64_t s1, const float* __restrict__ x, float* __restrict__ rhs, int64_t bx) {
@@ -1546,9 +1471,28 @@ __device__ __forceinline__ void k_gemv_fwd_body(const float* __restrict__ G, int
   if (lane == 0) rhs[i] -= acc;
 }
 
-__global__ void __launch_bounds__(256) k_gemv_fwd(const float* __restrict__ G, int64_t ld, int64_t M, int64_t s0,
-                                                  int64_t s1, const float* __restrict__ x, float* __restrict__ rhs) {
-  k_gemv_fwd_body(G, ld, M, s0, s1, x, rhs, blockIdx.x);
+// One step's trailing update: workgroups below `tiles` subtract panel panel^T
+// from the lower triangle in tiles of 64 X, the ones above carry the panel's
+// unknowns to the right-hand side of the rows below (four rows each).
+template <int X>
+__device__ __forceinline__ void k_syrk_body(float* G, int64_t ld, int64_t M, int64_t o, int64_t tiles,
+                                            const float* __restrict__ x, float* __restrict__ rhs) {
+  const int64_t r0 = o + kPB, rows = M - r0;
+  if (rows <= 0) return;
+  if (blockIdx.x >= tiles) {
+    k_gemv_fwd_body(G, ld, M, o, r0, x, rhs, blockIdx.x - tiles);
+    return;
+  }
+  const int64_t tr = (rows + 64 * X - 1) / (64 * X);
+  if (static_cast<int64_t>(blockIdx.x) >= tr * (tr + 1) / 2) return;
+  const float* panel = G + r0 * ld + o;
+  k_gemm_nt_body<true, X, X>(panel, ld, panel, ld, G + r0 * ld + r0, ld, rows, rows, kPB, -1.f, 1.f, 0, blockIdx.x);
+}
+
+template <int X>
+__global__ void __launch_bounds__(256) k_syrk(float* G, int64_t ld, int64_t M, int64_t o, int64_t tiles,
+                                              const float* __restrict__ x, float* __restrict__ rhs) {
+  k_syrk_body<X>(G, ld, M, o, tiles, x, rhs);
 }
 
 // Backward: z[s0:s1) = L[s0:s1, s0:s1)^-T x[s0:s1) into rhs (x holds the later segments' updates).
@@ -1645,7 +1589,7 @@ __global__ void k_finish(const float* __restrict__ z, int64_t M, const double* _
 __global__ void __launch_bounds__(256) k_potrf_mb(const gnnshap::MbJob* __restrict__ jobs, int64_t o) {
   const gnnshap::MbJob J = jobs[blockIdx.y];
   if (o >= J.M) return;
-  k_potrf_body(J.G, J.ld, J.M, o, J.info, J.Winv);
+  k_potrf_body(J.G, J.ld, J.M, o, J.info, J.Winv, J.rhs, J.x);
 }
 
 // panel <- panel W^T (the off-diagonal blocks of the step's 128 columns)
@@ -1659,31 +1603,10 @@ __global__ void __launch_bounds__(256) k_trsm_mb(const gnnshap::MbJob* __restric
   k_gemm_nt_body<false, 1, 2>(panel, J.ld, J.Winv, kPB, panel, J.ld, rows, kPB, kPB, 1.f, 0.f, 1, blockIdx.x);
 }
 
-// trailing lower triangle -= panel panel^T, in tiles of 64 X
 template <int X>
-__global__ void __launch_bounds__(256) k_syrk_mb(const gnnshap::MbJob* __restrict__ jobs, int64_t o) {
+__global__ void __launch_bounds__(256) k_syrk_mb(const gnnshap::MbJob* __restrict__ jobs, int64_t o, int64_t tiles) {
   const gnnshap::MbJob J = jobs[blockIdx.y];
-  const int64_t r0 = o + kPB;
-  if (r0 >= J.M) return;
-  const int64_t rows = J.M - r0;
-  const int64_t tr = (rows + 64 * X - 1) / (64 * X);
-  if (static_cast<int64_t>(blockIdx.x) >= tr * (tr + 1) / 2) return;
-  const float* panel = J.G + r0 * J.ld + o;
-  k_gemm_nt_body<true, X, X>(panel, J.ld, panel, J.ld, J.G + r0 * J.ld + r0, J.ld, rows, rows, kPB, -1.f, 1.f, 0,
-                       blockIdx.x);
-}
-
-__global__ void __launch_bounds__(1024) k_trsv_fwd_mb(const gnnshap::MbJob* __restrict__ jobs, int64_t s0) {
-  const gnnshap::MbJob J = jobs[blockIdx.y];
-  if (s0 >= J.M) return;
-  k_trsv_fwd_body(J.G, J.ld, s0, J.M < s0 + kSeg ? J.M : s0 + kSeg, J.rhs, J.x);
-}
-
-__global__ void __launch_bounds__(256) k_gemv_fwd_mb(const gnnshap::MbJob* __restrict__ jobs, int64_t s0) {
-  const gnnshap::MbJob J = jobs[blockIdx.y];
-  const int64_t s1 = s0 + kSeg;
-  if (s1 >= J.M) return;
-  k_gemv_fwd_body(J.G, J.ld, J.M, s0, s1, J.x, J.rhs, blockIdx.x);
+  k_syrk_body<X>(J.G, J.ld, J.M, o, tiles, J.x, J.rhs);
 }
 
 __global__ void __launch_bounds__(1024) k_trsv_bwd_mb(const gnnshap::MbJob* __restrict__ jobs, int64_t s0) {
@@ -1849,7 +1772,7 @@ __device__ __forceinline__ void pp_factor_diag(float* D, float* W, int64_t M, in
   const int tid = threadIdx.x;
   if (tid < 64 && p * 64 + tid >= M) D[tid * kHP + tid] = 1.f;
   __syncthreads();
-  if ((tid >> 6) == 0) chol_inv64(D, W, nullptr, p * 64, info);
+  if ((tid >> 6) == 0) chol_inv64(D, W, p * 64, info);
   __syncthreads();
 }
 
@@ -2341,9 +2264,8 @@ int gnnshap::solve_wls_start(const gnnshap_sample_plan* plan, const gnnshap_clas
     return GNNSHAP_OK;
   }
 
-  static bool potrf_lds = false, fwd_lds = false, bwd_lds = false;
+  static bool potrf_lds = false, bwd_lds = false;
   if (!allow_lds(reinterpret_cast<const void*>(&k_potrf), kPotrfLds, potrf_lds) ||
-      !allow_lds(reinterpret_cast<const void*>(&k_trsv_fwd), kTrsvLds, fwd_lds) ||
       !allow_lds(reinterpret_cast<const void*>(&k_trsv_bwd), kTrsvLds, bwd_lds))
     return gnnshap::fail(GNNSHAP_EHIP, "device cannot give the solver %zu bytes of LDS", kTrsvLds);
   k_zero_info<<<1, 1, 0, s>>>(info);
@@ -2365,7 +2287,7 @@ int gnnshap::solve_wls_start(const gnnshap_sample_plan* plan, const gnnshap_clas
   for (int64_t o = 0; o < M; o += kPB) {
     {
       GS_TIMED("k_potrf", s);
-      k_potrf<<<1, 256, kPotrfLds, s>>>(w.G, ld, M, o, info, w.Winv);
+      k_potrf<<<1, 256, kPotrfLds, s>>>(w.G, ld, M, o, info, w.Winv, w.rhs, w.x);
     }
     GS_LAUNCHED();
     const int64_t r0 = o + kPB;
@@ -2379,29 +2301,16 @@ int gnnshap::solve_wls_start(const gnnshap_sample_plan* plan, const gnnshap_clas
     }
     GS_LAUNCHED();
     {
-      GS_TIMED("k_syrk", s);   // trailing lower triangle -= panel panel^T
+      GS_TIMED("k_syrk", s);
       const int64_t tr2 = gnnshap::ceil_div(rows, 128);
       const int edge = syrk_edge(tr2 * (tr2 + 1) / 2);
-      const int64_t tr = gnnshap::ceil_div(rows, 64 * edge);
-      (edge == 1 ? k_gemm_nt<true, 1, 1> : k_gemm_nt<true, 2, 2>)<<<static_cast<unsigned>(tr * (tr + 1) / 2), 256, 0, s>>>(
-          panel, ld, panel, ld, w.G + r0 * ld + r0, ld, rows, rows, kPB, -1.f, 1.f, 0);
+      const int64_t tr = gnnshap::ceil_div(rows, 64 * edge), tiles = tr * (tr + 1) / 2;
+      (edge == 1 ? k_syrk<1> : k_syrk<2>)<<<static_cast<unsigned>(tiles + gnnshap::ceil_div(rows, 4)), 256, 0, s>>>(
+          w.G, ld, M, o, tiles, w.x, w.rhs);
     }
     GS_LAUNCHED();
   }
-  // L x = rhs, L^T psi = x (psi into rhs), phi = Delta/M + psi
-  for (int64_t s0 = 0; s0 < M; s0 += kSeg) {
-    const int64_t s1 = std::min(M, s0 + kSeg);
-    {
-      GS_TIMED("k_trsv", s);
-      k_trsv_fwd<<<1, 1024, kTrsvLds, s>>>(w.G, ld, s0, s1, w.rhs, w.x);
-    }
-    GS_LAUNCHED();
-    if (s1 < M) {
-      k_gemv_fwd<<<static_cast<unsigned>(gnnshap::ceil_div((M - s1) * 64, 256)), 256, 0, s>>>(w.G, ld, M, s0, s1, w.x,
-                                                                                             w.rhs);
-      GS_LAUNCHED();
-    }
-  }
+  // L^T psi = x (psi into rhs), phi = Delta/M + psi
   for (int64_t s0 = ((M - 1) / kSeg) * kSeg; s0 >= 0; s0 -= kSeg) {
     const int64_t s1 = std::min(M, s0 + kSeg);
     {
@@ -2519,9 +2428,8 @@ int gnnshap::solve_fill_mb_job(const gnnshap_sample_plan* plan, const gnnshap_cl
 int gnnshap::launch_solve_mb(const MbJob* jobs, int64_t n, int64_t max_M, hipStream_t s) {
   if (n < 1) return GNNSHAP_OK;
   if (n > 65535) return fail(GNNSHAP_EUNSUPPORTED, "at most 65535 multi-block systems per launch");
-  static bool potrf_lds = false, fwd_lds = false, bwd_lds = false;
+  static bool potrf_lds = false, bwd_lds = false;
   if (!allow_lds(reinterpret_cast<const void*>(&k_potrf_mb), kPotrfLds, potrf_lds) ||
-      !allow_lds(reinterpret_cast<const void*>(&k_trsv_fwd_mb), kTrsvLds, fwd_lds) ||
       !allow_lds(reinterpret_cast<const void*>(&k_trsv_bwd_mb), kTrsvLds, bwd_lds))
     return fail(GNNSHAP_EHIP, "device cannot give the solver %zu bytes of LDS", kTrsvLds);
   const unsigned nn = static_cast<unsigned>(n);
@@ -2542,22 +2450,11 @@ int gnnshap::launch_solve_mb(const MbJob* jobs, int64_t n, int64_t max_M, hipStr
       GS_TIMED("k_syrk_mb", s);
       const int64_t tr2 = ceil_div(max_M - r0, 128);
       const int edge = syrk_edge(tr2 * (tr2 + 1) / 2 * n);
-      const int64_t tr = ceil_div(max_M - r0, 64 * edge);
-      (edge == 1 ? k_syrk_mb<1> : k_syrk_mb<2>)<<<dim3(static_cast<unsigned>(tr * (tr + 1) / 2), nn), 256, 0, s>>>(jobs, o);
+      const int64_t tr = ceil_div(max_M - r0, 64 * edge), tiles = tr * (tr + 1) / 2;
+      (edge == 1 ? k_syrk_mb<1> : k_syrk_mb<2>)<<<dim3(static_cast<unsigned>(tiles + ceil_div(max_M - r0, 4)), nn), 256,
+                                                  0, s>>>(jobs, o, tiles);
     }
     GS_LAUNCHED();
-  }
-  for (int64_t s0 = 0; s0 < max_M; s0 += kSeg) {
-    {
-      GS_TIMED("k_trsv_mb", s);
-      k_trsv_fwd_mb<<<dim3(1, nn), 1024, kTrsvLds, s>>>(jobs, s0);
-    }
-    GS_LAUNCHED();
-    const int64_t s1 = std::min(max_M, s0 + kSeg);
-    if (s1 < max_M) {
-      k_gemv_fwd_mb<<<dim3(static_cast<unsigned>(ceil_div((max_M - s1) * 64, 256)), nn), 256, 0, s>>>(jobs, s0);
-      GS_LAUNCHED();
-    }
   }
   for (int64_t s0 = ((max_M - 1) / kSeg) * kSeg; s0 >= 0; s0 -= kSeg) {
     {
