@@ -148,14 +148,12 @@ __global__ void k_init(int32_t* ctl, uint64_t* sp_masks, int32_t* sp_rows, int64
 
 typedef float mx4_t __attribute__((ext_vector_type(4)));
 
-// C[m, :] = op(A[row(m), :]) B for m in [m0, m0 + rows), 64x64 tiles, fp32
-// MFMA (16x16x4) with fp32 accumulation.  row(m) = arow ? arow[m] : m;
-// op(a) = relu(a + abias) if abias else a.  The 16-wide K slices are staged
-// in LDS; the next one is fetched into registers while the current one is
-// multiplied.
+// C[m, :] = A[row(m), :] B for m in [m0, m0 + rows), 64x64 tiles, fp32
+// MFMA (16x16x4) with fp32 accumulation.  row(m) = arow ? arow[m] : m.  The
+// 16-wide K slices are staged in LDS; the next one is fetched into registers
+// while the current one is multiplied.
 __global__ void __launch_bounds__(256) k_gemm(const float* __restrict__ A, int64_t lda,
                                               const int32_t* __restrict__ arow,
-                                              const float* __restrict__ abias,
                                               const float* __restrict__ B, int64_t ldb,
                                               float* __restrict__ C, int64_t ldc, int64_t m0,
                                               int64_t rows, int64_t N, int64_t K,
@@ -187,12 +185,7 @@ __global__ void __launch_bounds__(256) k_gemm(const float* __restrict__ A, int64
   auto fetch = [&](int64_t k0) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float a = 0.f;
-      if (aok[i] && k0 + kk < K) {
-        a = arp[i][k0 + kk];
-        if (abias) a = fmaxf(a + abias[k0 + kk], 0.f);
-      }
-      ra[i] = a;
+      ra[i] = aok[i] && k0 + kk < K ? arp[i][k0 + kk] : 0.f;
       const int64_t kr = k0 + kb0 + 4 * i;
       rb[i] = (kr < K && nok) ? B[kr * ldb + nb + nn] : 0.f;
     }
@@ -272,9 +265,8 @@ __device__ __forceinline__ unsigned bf16_pair(float& a, float& b) {
 template <int NT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict__ arow,
-             const float* __restrict__ abias, const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
-             int64_t ldc, int64_t m0, int64_t rows, int64_t N, int64_t K, const int32_t* dyn_count, int64_t dyn_off,
-             int64_t dyn_cap, int64_t dyn_mult) {
+             const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc, int64_t m0, int64_t rows,
+             int64_t N, int64_t K, const int32_t* dyn_count, int64_t dyn_off, int64_t dyn_cap, int64_t dyn_mult) {
   constexpr int kCols = 32 * NT, kBT = 2 * NT;          // columns and column tiles of the workgroup
   constexpr int kPerB = 32 * kCols / 256;               // B values per thread and step: 8 or 16, consecutive k
   __shared__ u4_t As[3][8 * 64], Bs[3][kBT * 64];       // [part][tile][lane]: 8 bf16 of one row (column)
@@ -319,17 +311,14 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
       rb[q] = whole || k < K ? bp[k * ldb] : 0.f;
     }
   };
-  auto stage = [&](int64_t k0) {
+  auto stage = [&]() {
     const int g = ak >> 3;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = tid / 8 + 32 * i;
       float v[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        v[q] = ra[i][q];
-        if (abias) v[q] = k0 + ak + q < K ? fmaxf(v[q] + abias[k0 + ak + q], 0.f) : 0.f;
-      }
+      for (int q = 0; q < 4; ++q) v[q] = ra[i][q];
       const int at = ((row >> 4) * 64 + g * 16 + ((row & 15) ^ (8 * (g & 1)))) * 2 + ((ak >> 2) & 1);
 #pragma unroll
       for (int p = 0; p < 3; ++p)
@@ -356,7 +345,7 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
     for (int b = 0; b < NT; ++b) acc[a][b] = mx4_t{0.f, 0.f, 0.f, 0.f};
   fetch(0);
   for (int64_t k0 = 0; k0 < K; k0 += 32) {
-    stage(k0);
+    stage();
     __syncthreads();
     if (k0 + 32 < K) fetch(k0 + 32);
     bf8_t av[3][4];
@@ -404,7 +393,7 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
         if (!(fabsf(v) <= 3.4e38f)) {
           const float* ar = A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda;
           v = 0.f;
-          for (int64_t k = 0; k < K; ++k) v = fmaf(abias ? fmaxf(ar[k] + abias[k], 0.f) : ar[k], B[k * ldb + n], v);
+          for (int64_t k = 0; k < K; ++k) v = fmaf(ar[k], B[k * ldb + n], v);
         }
         C[m * ldc + n] = v;
       }
@@ -1559,24 +1548,23 @@ __global__ void __launch_bounds__(KW * 64) k_transform(const float* __restrict__
   }
 }
 
-int launch_gemm(hipStream_t s, const float* A, int64_t lda, const int32_t* arow, const float* abias,
-                const float* B, int64_t ldb, float* C, int64_t ldc, int64_t m0, int64_t rows, int64_t N,
-                int64_t K, const int32_t* dyn = nullptr, int64_t dyn_off = 0, int64_t dyn_cap = 0,
-                int64_t dyn_mult = 0, int64_t least = 256) {
+int launch_gemm(hipStream_t s, const float* A, int64_t lda, const int32_t* arow, const float* B, int64_t ldb, float* C,
+                int64_t ldc, int64_t m0, int64_t rows, int64_t N, int64_t K, const int32_t* dyn = nullptr,
+                int64_t dyn_off = 0, int64_t dyn_cap = 0, int64_t dyn_mult = 0, int64_t least = 256) {
   if (rows <= 0) return GNNSHAP_OK;
   GS_TIMED("k_gemm", s);
   if (takes_split(rows, N, K, least)) {
     const int nt = N > 64 ? 4 : 2;
     const dim3 g(static_cast<unsigned>(gnnshap::ceil_div(rows, kSplitRows)),
                  static_cast<unsigned>(gnnshap::ceil_div(N, 32 * nt)));
-    (nt == 4 ? k_gemm_split<4> : k_gemm_split<2>)<<<g, 256, 0, s>>>(A, lda, arow, abias, B, ldb, C, ldc, m0, rows, N,
-                                                                   K, dyn, dyn_off, dyn_cap, dyn_mult);
+    (nt == 4 ? k_gemm_split<4> : k_gemm_split<2>)<<<g, 256, 0, s>>>(A, lda, arow, B, ldb, C, ldc, m0, rows, N, K,
+                                                                   dyn, dyn_off, dyn_cap, dyn_mult);
     GS_LAUNCHED();
     return GNNSHAP_OK;
   }
   dim3 grid(static_cast<unsigned>(gnnshap::ceil_div(rows, 64)), static_cast<unsigned>(gnnshap::ceil_div(N, 64)));
-  k_gemm<<<grid, 256, 0, s>>>(A, lda, arow, abias, B, ldb, C, ldc, m0, rows, N, K, dyn, dyn_off,
-                              dyn_cap, dyn_mult);
+  k_gemm<<<grid, 256, 0, s>>>(A, lda, arow, B, ldb, C, ldc, m0, rows, N, K, dyn, dyn_off, dyn_cap,
+                              dyn_mult);
   GS_LAUNCHED();
   return GNNSHAP_OK;
 }
@@ -1691,7 +1679,7 @@ int run_pass(hipStream_t s, const gnnshap_subgraph* sg, const gnnshap_gcn* m, co
                                   w.Zc[j], Zb, sh.nd[j - 1], bias, w.Hb[j], sh.nd[j]))
       return st;
     if (j + 1 < L) {
-      if (int st = launch_gemm(s, w.Hb[j], sh.dims[j], nullptr, nullptr, m->W[j], sh.dims[j + 1], w.Zb[j + 1],
+      if (int st = launch_gemm(s, w.Hb[j], sh.dims[j], nullptr, m->W[j], sh.dims[j + 1], w.Zb[j + 1],
                                sh.dims[j + 1], 0, cap * sh.nd[j], sh.dims[j + 1], sh.dims[j], dyn, row_off,
                                cap, sh.nd[j]))
         return st;
@@ -1839,7 +1827,7 @@ int gnnshap::eval_coalitions_impl(const gnnshap_subgraph* sg, const gnnshap_gcn*
                       gnnshap::ceil_div(k, kRowsPerBlock) <= INT32_MAX;
   if (direct) {
     if (!m->XW1) {
-      if (int st = launch_gemm(s, X, sh.dims[0], sg->node_gid, nullptr, m->W[0], sh.dims[1], w.Zc[1], sh.dims[1], 0,
+      if (int st = launch_gemm(s, X, sh.dims[0], sg->node_gid, m->W[0], sh.dims[1], w.Zc[1], sh.dims[1], 0,
                                sh.n_nodes, sh.dims[1], sh.dims[0]))
         return st;
     }
@@ -1872,7 +1860,7 @@ int gnnshap::eval_coalitions_impl(const gnnshap_subgraph* sg, const gnnshap_gcn*
     k_gather_rows<<<gnnshap::grid_for(sh.n_nodes * sh.dims[1], 256, 2048), 256, 0, s>>>(m->XW1, sg->node_gid,
                                                                                         sh.n_nodes, sh.dims[1], w.Zc[1]);
     GS_LAUNCHED();
-  } else if (int st = launch_gemm(s, X, sh.dims[0], sg->node_gid, nullptr, m->W[0], sh.dims[1], w.Zc[1], sh.dims[1],
+  } else if (int st = launch_gemm(s, X, sh.dims[0], sg->node_gid, m->W[0], sh.dims[1], w.Zc[1], sh.dims[1],
                                   0, sh.n_nodes, sh.dims[1], sh.dims[0])) {
     return st;
   }
@@ -1882,7 +1870,7 @@ int gnnshap::eval_coalitions_impl(const gnnshap_subgraph* sg, const gnnshap_gcn*
         w.Zc[j], m->b ? m->b[j - 1] : nullptr, w.Bc[j], sh.bnd0, sh.bnd1, sh.dims[j]);
     GS_LAUNCHED();
     if (j + 1 < L) {
-      if (int st = launch_gemm(s, w.Bc[j], sh.dims[j], nullptr, nullptr, m->W[j], sh.dims[j + 1], w.Zc[j + 1],
+      if (int st = launch_gemm(s, w.Bc[j], sh.dims[j], nullptr, m->W[j], sh.dims[j + 1], w.Zc[j + 1],
                                sh.dims[j + 1], sh.bnd0, sh.bnd1 - sh.bnd0, sh.dims[j + 1], sh.dims[j]))
         return st;
     }
@@ -1902,7 +1890,7 @@ int gnnshap::eval_coalitions_impl(const gnnshap_subgraph* sg, const gnnshap_gcn*
     // layer 2 and the output layer for every class
     const gnnshap::WideShape& ws = sh.ws;
     if (int st = gnnshap::launch_wide3_ends_l1(ws, w.wide, sg, w.Zc[1], m->b ? m->b[0] : nullptr, s)) return st;
-    if (int st = launch_gemm(s, w.wide.hf, ws.h, nullptr, nullptr, m->W[1], ws.h2, w.wide.z2e, ws.h2, 0, ws.n1 + 1,
+    if (int st = launch_gemm(s, w.wide.hf, ws.h, nullptr, m->W[1], ws.h2, w.wide.z2e, ws.h2, 0, ws.n1 + 1,
                              ws.h2, ws.h))
       return st;
     if (int st = gnnshap::launch_wide3_ends_l2(ws, w.wide, sg, w.Zc[2], m->b ? m->b[1] : nullptr, m->W[2],
@@ -1921,7 +1909,7 @@ int gnnshap::eval_coalitions_impl(const gnnshap_subgraph* sg, const gnnshap_gcn*
       if (ws.agg3) {
         // three hops: layer 2's sums at the target and its in-neighbours, then W_2 there only
         if (int st = gnnshap::launch_wide3_agg(ws, w.wide, sg, masks, sh.wpr, r0, nloc, pairs, s)) return st;
-        if (int st = launch_gemm(s, w.wide.A3, ws.h, nullptr, nullptr, m->W[1], ws.h2, w.wide.Z2, ws.h2, 0,
+        if (int st = launch_gemm(s, w.wide.A3, ws.h, nullptr, m->W[1], ws.h2, w.wide.Z2, ws.h2, 0,
                                  (pairs ? 2 : 1) * nloc * ws.n2, ws.h2, ws.h))
           return st;
         if (int st = gnnshap::launch_wide3_t(ws, w.wide, sg, masks, sh.wpr, r0, nloc, m->b ? m->b[1] : nullptr,
@@ -1929,7 +1917,7 @@ int gnnshap::eval_coalitions_impl(const gnnshap_subgraph* sg, const gnnshap_gcn*
           return st;
         continue;
       }
-      if (int st = launch_gemm(s, w.wide.H1, ws.h, nullptr, nullptr, m->W[1], ws.h2, w.wide.Z2, ws.h2, 0,
+      if (int st = launch_gemm(s, w.wide.H1, ws.h, nullptr, m->W[1], ws.h2, w.wide.Z2, ws.h2, 0,
                                (pairs ? 2 : 1) * nloc * ws.n1, ws.h2, ws.h))
         return st;
       if (int st = gnnshap::launch_wide3_l2(ws, w.wide, sg, masks, sh.wpr, r0, nloc, m->b ? m->b[1] : nullptr,
@@ -2006,7 +1994,7 @@ extern "C" int gnnshap_transform_features(const float* X, int64_t n, int32_t d, 
   }
   if (gnnshap::ceil_div(n, 64) > INT32_MAX || gnnshap::ceil_div(h, 64) > 65535)
     return gnnshap::fail(GNNSHAP_EUNSUPPORTED, "matrix too large");
-  return launch_gemm(s, X, d, nullptr, nullptr, W, h, Z, h, 0, n, h, d, nullptr, 0, 0, 0, narrow ? 128 : 256);
+  return launch_gemm(s, X, d, nullptr, W, h, Z, h, 0, n, h, d, nullptr, 0, 0, 0, narrow ? 128 : 256);
   GS_TRY_END
 }
 
