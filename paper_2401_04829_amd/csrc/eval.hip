@@ -229,15 +229,19 @@ __global__ void __launch_bounds__(256) k_gemm(const float* __restrict__ A, int64
 }
 
 // The same product for large shapes on bf16 matrix instructions (16x the fp32
-// rate): every fp32 operand is the sum of three bf16 parts (hi = bf16(x), mid =
-// bf16(x - hi), lo = bf16(x - hi - mid), each rounded to nearest; 24 bits in
-// all), and the product of two such sums is taken as the six part products
-// down to 2^-16 of the largest (the three dropped ones are below 2^-25, half
-// an ulp of fp32 at most and of random sign).  Accumulation is fp32 over 32
-// products per step instead of 4, so the distance from 64 bits is no larger
-// than that of the fp32 instruction.  Values that round to infinity in bf16
-// or are not finite give a non-finite sum; such an output is computed again
-// in fp32.
+// rate): every operand, times 2^24, is the sum of three bf16 parts (hi =
+// bf16(x), mid = bf16(x - hi), lo = bf16(x - hi - mid), each rounded to
+// nearest; 24 bits in all), and the product of two such sums is taken as the
+// six part products down to 2^-16 of the largest (the three dropped ones are
+// below 2^-25, half an ulp of fp32 at most and of random sign).  The factor
+// keeps the parts exact for every fp32 number, subnormal ones among them: all
+// parts are multiples of 2^-125, where without it the lower parts of operands
+// below 2^-109 fell under the smallest bf16 number (2.7e-4 off at 1e-37); it
+// leaves the result exactly (times 2^-48) at the end.  Accumulation is fp32
+// over 32 products per step instead of 4, so the distance from 64 bits is no
+// larger than that of the fp32 instruction.  Operands above 2^104 or results
+// above 2^80, or that are not finite, give a non-finite sum; such an output is
+// computed again in fp32.
 //
 // One workgroup: 128 rows x 32 NT columns, four wavefronts of 64 x 16 NT; K in
 // steps of 32, split while they are staged in LDS in operand order (16-byte
@@ -252,6 +256,7 @@ typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u2_t __attribute__((ext_vector_type(2)));
 typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any float's address
 constexpr int kSplitRows = 128;
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;   // of an operand, of a product
 
 // Two floats as packed bf16 (round to nearest even), and what they leave.
 __device__ __forceinline__ unsigned bf16_pair(float& a, float& b) {
@@ -318,7 +323,7 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
       const int row = tid / 8 + 32 * i;
       float v[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] = ra[i][q];
+      for (int q = 0; q < 4; ++q) v[q] = ra[i][q] * kSplitScale;
       const int at = ((row >> 4) * 64 + g * 16 + ((row & 15) ^ (8 * (g & 1)))) * 2 + ((ak >> 2) & 1);
 #pragma unroll
       for (int p = 0; p < 3; ++p)
@@ -328,7 +333,7 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
     for (int h = 0; h < kPerB / 8; ++h) {
       float v[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = rb[8 * h + q];
+      for (int q = 0; q < 8; ++q) v[q] = rb[8 * h + q] * kSplitScale;
       const int at = (bn >> 4) * 64 + ((bk >> 3) + h) * 16 + (bn & 15);
 #pragma unroll
       for (int p = 0; p < 3; ++p)
@@ -389,8 +394,8 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
       for (int b = 0; b < NT; ++b) {
         const int64_t n = nb + 16 * (wn + b) + r;
         if (n >= N) continue;
-        float v = acc[a][b][q];
-        if (!(fabsf(v) <= 3.4e38f)) {
+        float v = acc[a][b][q] * kSplitUnscale;
+        if (!(fabsf(acc[a][b][q]) <= 3.4e38f)) {
           const float* ar = A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda;
           v = 0.f;
           for (int64_t k = 0; k < K; ++k) v = fmaf(ar[k], B[k * ldb + n], v);

@@ -41,6 +41,29 @@ def test_transform_against_float64(dev, n, d, h):
     assert bool(((Z - exact).abs() <= bound).all()), float(((Z - exact).abs() / bound).max())
 
 
+@pytest.mark.parametrize("ex,ew", [(0, 0), (-100, 20), (-115, 60), (-123, 99), (40, -123), (-60, -60), (60, -110),
+                                   (110, -100), (-125, 116), (50, 50)])
+def test_transform_at_the_ends_of_the_range(dev, ex, ew):
+    """Operands of 2^ex and 2^ew times numbers of order one, rows and columns
+    16 binades wide: down to the smallest normal fp32 numbers and below (the
+    exact result is that of the fp32 values as they are), and sums of up to
+    2^101, beyond those that the split product holds.  Bound: d roundings of
+    at most 2^-24 of the sum of magnitudes, results below 2^-126 half an ulp
+    of theirs besides."""
+    n, d, h = 16500, 128, 128
+    print("transform at", ex, ew, flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(ex * 300 + ew)
+    pow2 = lambda shape: torch.randint(-8, 8, shape, generator=g, device=dev).double()
+    X = (torch.randn((n, d), generator=g, device=dev).double() * 2.0 ** (ex + pow2((n, 1)))).float()
+    W = (torch.randn((d, h), generator=g, device=dev).double() * 2.0 ** (ew + pow2((1, h)))).float()
+    Z = _transform(X, W).double()
+    exact = X.double() @ W.double()
+    bound = (d + 4) * 2.0 ** -24 * (X.double().abs() @ W.double().abs()) + 2.0 ** -150
+    worst = float(((Z - exact).abs() / bound).max())
+    assert worst <= 1.0
+
+
 def test_transform_special_values(dev):
     """Infinities, NaN and values above the largest bf16 number give what
     fp32 arithmetic gives; the other rows are untouched by them."""
