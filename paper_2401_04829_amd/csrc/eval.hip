@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(256) k_gemm(const float* __restrict__ A, int64
 // next step's values are loaded while this one is multiplied.  Bound by the
 // latency of a step (staging, two barriers), then by the matrix
 // instructions (6 x 2 m n k flop); X W_1 of 232,965 x 602 x 128: 921 us
-// (k_transform) before, 353 us now, 2.2e-7 and 1.0e-7 off the 64-bit result.
+// (k_transform) before, 338 us now, 2.2e-7 and 1.0e-7 off the 64-bit result.
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u2_t __attribute__((ext_vector_type(2)));
@@ -265,6 +265,43 @@ __device__ __forceinline__ unsigned bf16_pair(float& a, float& b) {
   a -= __uint_as_float(p << 16);
   b -= __uint_as_float(p & 0xffff0000u);
   return p;
+}
+
+// One output of a split product from its scaled sum: the sum itself, or, if
+// it is not finite, the product of row ar and column b (stride ldb) in fp32.
+__device__ __forceinline__ float split_output(float sum, const float* __restrict__ ar, const float* __restrict__ b,
+                                              int64_t ldb, int64_t K) {
+  if (fabsf(sum) <= 3.4e38f) return sum * kSplitUnscale;
+  float v = 0.f;
+  for (int64_t k = 0; k < K; ++k) v = fmaf(ar[k], b[k * ldb], v);
+  return v;
+}
+
+// The sums of one step (32 k) of NA tiles of 16 rows and one of 16 columns,
+// from their parts; from zero, small products first, so that the running sum
+// is rounded once per step and not six times (602 products: 3.7e-7 off instead
+// of 2.2e-7 otherwise).
+template <int NA>
+__device__ __forceinline__ void split_step(const bf8_t (&a)[3][NA], const bf8_t (&b)[3], mx4_t (&sum)[NA]) {
+  constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int i = 0; i < 6; ++i)
+#pragma unroll
+    for (int t = 0; t < NA; ++t)
+      sum[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[pa[i]][t], b[pb[i]],
+                                                       i == 0 ? mx4_t{0.f, 0.f, 0.f, 0.f} : sum[t], 0, 0, 0);
+}
+
+// The parts of eight consecutive k of one row (column), as operands of tile t.
+template <int NA>
+__device__ __forceinline__ void split8(const float (&x)[8], bf8_t (&part)[3][NA], int t) {
+  float v[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) v[q] = x[q] * kSplitScale;
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+    part[p][t] = __builtin_bit_cast(bf8_t, u4_t{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]), bf16_pair(v[4], v[5]),
+                                                bf16_pair(v[6], v[7])});
 }
 
 template <int NT>
@@ -363,22 +400,8 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
       bf8_t bv[3];
 #pragma unroll
       for (int p = 0; p < 3; ++p) bv[p] = __builtin_bit_cast(bf8_t, Bs[p][(wn + b) * 64 + lane]);
-      // the step's sum from zero, (part of A, part of B) small products first,
-      // so that the running sum is rounded once per step and not six times
-      // (602 products: 3.7e-7 off instead of 2.2e-7 otherwise)
       mx4_t sum[4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[2][a], bv[0], mx4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[0][a], bv[2], sum[a], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[1][a], bv[1], sum[a], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[1][a], bv[0], sum[a], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[0][a], bv[1], sum[a], 0, 0, 0);
-#pragma unroll
-      for (int a = 0; a < 4; ++a) sum[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[0][a], bv[0], sum[a], 0, 0, 0);
+      split_step<4>(av, bv, sum);
 #pragma unroll
       for (int a = 0; a < 4; ++a) acc[a][b] += sum[a];
     }
@@ -394,28 +417,145 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
       for (int b = 0; b < NT; ++b) {
         const int64_t n = nb + 16 * (wn + b) + r;
         if (n >= N) continue;
-        float v = acc[a][b][q] * kSplitUnscale;
-        if (!(fabsf(acc[a][b][q]) <= 3.4e38f)) {
-          const float* ar = A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda;
-          v = 0.f;
-          for (int64_t k = 0; k < K; ++k) v = fmaf(ar[k], B[k * ldb + n], v);
-        }
-        C[m * ldc + n] = v;
+        C[m * ldc + n] = split_output(acc[a][b][q], A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda, B + n, ldb, K);
       }
     }
 }
 
-// Whether a product takes k_gemm_split: columns and K that its tiles do not
-// mostly pad, and at least `least` workgroups.  One step of a workgroup takes
-// 2-3 us whatever the grid, so a small grid is faster on the many small tiles
-// of the fp32 kernels.  Against k_gemm the line is 256 workgroups, one per CU
-// (8,192 x 256 x 256, 128 workgroups: 23.4 us k_gemm, 30.5 split; 16,384 x
-// 600 x 41, 128: 37.3, 52.3; 232,965 x 602 x 128, 1,821: 921 k_transform,
-// 353 split), against k_transform, which has one workgroup per 16 rows, 128
-// (16,384 x 128 x 128: 20.2 us, 18.9 split; 8,192: 11.0, 18.3).
-bool takes_split(int64_t rows, int64_t N, int64_t K, int64_t least) {
-  return N >= 40 && K >= 32 && gnnshap::ceil_div(rows, kSplitRows) * gnnshap::ceil_div(N, 128) >= least;
+// The same sums, and so the same bits, for few rows: 16 x 64 outputs per
+// workgroup, its eight wavefronts taking the steps of 32 k in turn, straight
+// from memory (no staging, no barrier before the products); their sums go
+// through LDS and are added in step order, wavefront w < 4 adding tile w.
+// Bound by the latency of a wavefront's first loads while the grid is small,
+// then by the splitting (VALU, again for every 16 rows).  300 x 602 x 128:
+// 8 us, 10,000 rows: 27 us (k_transform 16 and 52, k_gemm 36 and 48; sixteen
+// wavefronts 8 and 34).
+constexpr int kShortWaves = 8;
+
+__global__ void __launch_bounds__(kShortWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
+k_gemm_split_short(const float* __restrict__ A, int64_t lda, const int32_t* __restrict__ arow,
+                   const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc, int64_t m0,
+                   int64_t rows, int64_t N, int64_t K, const int32_t* dyn_count, int64_t dyn_off, int64_t dyn_cap,
+                   int64_t dyn_mult) {
+  __shared__ mx4_t part[kShortWaves][4 * 64];
+  if (dyn_count) {
+    const int64_t r = rows_in_pass(dyn_count, dyn_off, dyn_cap) * dyn_mult;
+    if (r < rows) rows = r;
+  }
+  const int64_t mb = m0 + static_cast<int64_t>(blockIdx.x) * 16;
+  if (mb >= m0 + rows) return;
+  const int64_t nb = static_cast<int64_t>(blockIdx.y) * 64;
+  const int lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // rows and columns beyond the last: its values, not stored
+  const int64_t mr = mb + r < m0 + rows ? mb + r : m0 + rows - 1;
+  const float* ap = A + (arow ? static_cast<int64_t>(arow[mr]) : mr) * lda + 8 * g;
+  const int64_t nr = N - 1 - nb;   // the last column from nb on
+  uint32_t bo[4];                   // bytes from the step's first row to the lane's column of row 8 g
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+    bo[b] = static_cast<uint32_t>(8 * g * ldb + (16 * b + r < nr ? 16 * b + r : nr)) * 4u;
+  const int steps = static_cast<int>((K + 31) / 32);
+  float ra[8], rb[4][8];
+  auto fetch = [&](int step) {
+    const float* a = ap + 32 * step;
+    const char* bk = reinterpret_cast<const char*>(B + nb + static_cast<int64_t>(step) * 32 * ldb);
+    if (32 * step + 32 <= K) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f4u_t v = *reinterpret_cast<const f4u_t*>(a + 4 * h);
+        ra[4 * h] = v.x;
+        ra[4 * h + 1] = v.y;
+        ra[4 * h + 2] = v.z;
+        ra[4 * h + 3] = v.w;
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) rb[b][q] = *reinterpret_cast<const float*>(bk + q * ldb * 4 + bo[b]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const bool in = 32 * step + 8 * g + q < K;
+        ra[q] = in ? a[q] : 0.f;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) rb[b][q] = in ? *reinterpret_cast<const float*>(bk + q * ldb * 4 + bo[b]) : 0.f;
+      }
+    }
+  };
+  mx4_t acc = {0.f, 0.f, 0.f, 0.f};
+  if (wave < steps) fetch(wave);
+  for (int s0 = 0; s0 < steps; s0 += kShortWaves) {
+    if (s0 + wave < steps) {
+      bf8_t av[3][1];
+      split8<1>(ra, av, 0);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        bf8_t bv[3][1];
+        split8<1>(rb[b], bv, 0);
+        const bf8_t col[3] = {bv[0][0], bv[1][0], bv[2][0]};
+        mx4_t sum[1];
+        split_step<1>(av, col, sum);
+        part[wave][b * 64 + lane] = sum[0];
+      }
+      if (s0 + kShortWaves + wave < steps) fetch(s0 + kShortWaves + wave);
+    }
+    __syncthreads();
+    if (wave < 4) {
+#pragma unroll
+      for (int w = 0; w < kShortWaves; ++w)
+        if (s0 + w < steps) acc += part[w][wave * 64 + lane];
+    }
+    if (s0 + kShortWaves < steps) __syncthreads();
+  }
+  const int64_t n = nb + 16 * wave + r;
+  if (wave >= 4 || n >= N) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t m = mb + 4 * g + q;
+    if (m < m0 + rows)
+      C[m * ldc + n] = split_output(acc[q], A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda, B + n, ldb, K);
+  }
 }
+
+// Whether a product takes the split kernels: a rule on its columns and K alone,
+// so that a row's result does not depend on how many rows go with it.
+// Against k_gemm (64-column tiles): K from 128 and columns that fill tiles of
+// 128 (232,965 x 602 x 100: 455 us k_gemm, 338 split; x 256: 889, 654; x 41
+// and x 130, where tiles of 128 pad: 228 and 663, 255 and 640; 100,000 x 60 x
+// 100: 31, 33; 40,000 to 80,000 rows are up to a tenth slower at K = 128 and
+// faster from K = 400).
+bool takes_split(int64_t N, int64_t K) { return K >= 128 && gnnshap::ceil_div(N, 64) % 2 == 0; }
+
+// Against k_transform (16, 32, .. 128 columns): from 48 columns and K = 32
+// (232,965 x 602 x 48: 794 us k_transform, 255 split, 300 rows: 9, 8; 100,000
+// x 32 x 48: 33, 15).
+bool transform_splits(int64_t N, int64_t K) { return N >= 48 && K >= 32; }
+
+int launch_split(hipStream_t s, const float* A, int64_t lda, const int32_t* arow, const float* B, int64_t ldb,
+                 float* C, int64_t ldc, int64_t m0, int64_t rows, int64_t N, int64_t K, const int32_t* dyn,
+                 int64_t dyn_off, int64_t dyn_cap, int64_t dyn_mult) {
+  // One step of a 128-row workgroup takes 2-3 us whatever the grid, so few
+  // rows are faster in many small workgroups that split K; the lines, in tiles
+  // of 128 x 64 (two per CU are 512): 20,000 x 602 x 128, 314 tiles: short 50,
+  // 64 wide 56, 128 wide 68 us; 28,000, 438: 65, 57, 68; 40,000, 626: 91, 100,
+  // 77; 70,000 x 602 x 48, 547: 81, 99; 100,000, 782: 112, 118; 28,000 x 60 x
+  // 128, 438: 21, 13, 16.
+  const int64_t tr = gnnshap::ceil_div(rows, kSplitRows), tiles = tr * gnnshap::ceil_div(N, 64);
+  if (tiles < (K <= 64 ? 160 : N <= 64 ? 768 : 384)) {
+    const dim3 g(static_cast<unsigned>(gnnshap::ceil_div(rows, 16)), static_cast<unsigned>(gnnshap::ceil_div(N, 64)));
+    k_gemm_split_short<<<g, kShortWaves * 64, 0, s>>>(A, lda, arow, B, ldb, C, ldc, m0, rows, N, K, dyn, dyn_off,
+                                                      dyn_cap, dyn_mult);
+  } else {
+    const int nt = N <= 64 || tiles <= 512 ? 2 : 4;
+    const dim3 g(static_cast<unsigned>(tr), static_cast<unsigned>(gnnshap::ceil_div(N, 32 * nt)));
+    (nt == 4 ? k_gemm_split<4> : k_gemm_split<2>)<<<g, 256, 0, s>>>(A, lda, arow, B, ldb, C, ldc, m0, rows, N, K, dyn,
+                                                                   dyn_off, dyn_cap, dyn_mult);
+  }
+  GS_LAUNCHED();
+  return GNNSHAP_OK;
+}
+
 
 // Zc[u, :] = XW1[node_gid[u], :]
 __global__ void k_gather_rows(const float* __restrict__ src, const int32_t* __restrict__ idx, int64_t n, int h,
@@ -1555,18 +1695,11 @@ __global__ void __launch_bounds__(KW * 64) k_transform(const float* __restrict__
 
 int launch_gemm(hipStream_t s, const float* A, int64_t lda, const int32_t* arow, const float* B, int64_t ldb, float* C,
                 int64_t ldc, int64_t m0, int64_t rows, int64_t N, int64_t K, const int32_t* dyn = nullptr,
-                int64_t dyn_off = 0, int64_t dyn_cap = 0, int64_t dyn_mult = 0, int64_t least = 256) {
+                int64_t dyn_off = 0, int64_t dyn_cap = 0, int64_t dyn_mult = 0) {
   if (rows <= 0) return GNNSHAP_OK;
   GS_TIMED("k_gemm", s);
-  if (takes_split(rows, N, K, least)) {
-    const int nt = N > 64 ? 4 : 2;
-    const dim3 g(static_cast<unsigned>(gnnshap::ceil_div(rows, kSplitRows)),
-                 static_cast<unsigned>(gnnshap::ceil_div(N, 32 * nt)));
-    (nt == 4 ? k_gemm_split<4> : k_gemm_split<2>)<<<g, 256, 0, s>>>(A, lda, arow, B, ldb, C, ldc, m0, rows, N, K,
-                                                                   dyn, dyn_off, dyn_cap, dyn_mult);
-    GS_LAUNCHED();
-    return GNNSHAP_OK;
-  }
+  if (takes_split(N, K))
+    return launch_split(s, A, lda, arow, B, ldb, C, ldc, m0, rows, N, K, dyn, dyn_off, dyn_cap, dyn_mult);
   dim3 grid(static_cast<unsigned>(gnnshap::ceil_div(rows, 64)), static_cast<unsigned>(gnnshap::ceil_div(N, 64)));
   k_gemm<<<grid, 256, 0, s>>>(A, lda, arow, B, ldb, C, ldc, m0, rows, N, K, dyn, dyn_off, dyn_cap,
                               dyn_mult);
@@ -1981,7 +2114,11 @@ extern "C" int gnnshap_transform_features(const float* X, int64_t n, int32_t d, 
   if (n < 1 || d < 1 || h < 1) return gnnshap::fail(GNNSHAP_EINVAL, "bad sizes");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool narrow = h % 16 == 0 && h <= 128 && gnnshap::ceil_div(n, 16) <= INT32_MAX;
-  if (narrow && !takes_split(n, h, d, 128)) {
+  if (narrow && transform_splits(h, d)) {
+    GS_TIMED("k_gemm", s);
+    return launch_split(s, X, d, nullptr, W, h, Z, h, 0, n, h, d, nullptr, 0, 0, 0);
+  }
+  if (narrow) {
     const unsigned g = static_cast<unsigned>(gnnshap::ceil_div(n, 16));
     GS_TIMED("k_transform", s);
     switch (h / 16) {
@@ -1999,7 +2136,7 @@ extern "C" int gnnshap_transform_features(const float* X, int64_t n, int32_t d, 
   }
   if (gnnshap::ceil_div(n, 64) > INT32_MAX || gnnshap::ceil_div(h, 64) > 65535)
     return gnnshap::fail(GNNSHAP_EUNSUPPORTED, "matrix too large");
-  return launch_gemm(s, X, d, nullptr, W, h, Z, h, 0, n, h, d, nullptr, 0, 0, 0, narrow ? 128 : 256);
+  return launch_gemm(s, X, d, nullptr, W, h, Z, h, 0, n, h, d);
   GS_TRY_END
 }
 

@@ -1,7 +1,7 @@
-"""X W of large shapes on split bf16 matrix products, against float64: tile
-edges in rows, columns and K, rows whose start is not 16-byte aligned, a wide
-range of magnitudes, infinities, NaN and values that round to infinity in
-bf16."""
+"""X W on split bf16 matrix products, against float64: tile edges in rows,
+columns and K, rows whose start is not 16-byte aligned, the same bits for any
+number of rows, a wide range of magnitudes, infinities, NaN and values that
+round to infinity in bf16."""
 import numpy as np
 import pytest
 import torch
@@ -39,6 +39,41 @@ def test_transform_against_float64(dev, n, d, h):
     # fp32 products and sums: d roundings of at most 2^-24 of the sum of magnitudes
     bound = (d + 4) * 2.0 ** -24 * (X.double().abs() @ W.double().abs())
     assert bool(((Z - exact).abs() <= bound).all()), float(((Z - exact).abs() / bound).max())
+
+
+# one row to the largest of each form: 16 x 64 outputs per workgroup (up to 159,
+# 383 or 767 tiles of 128 x 64), 128 x 64 and 128 x 128; K of one step and a
+# part, less than, exactly and more than the eight steps of one turn
+@pytest.mark.parametrize("n,d,h", [(1, 128, 64), (15, 33, 48), (16, 257, 65), (17, 255, 112), (300, 602, 128),
+                                   (301, 289, 250), (10112, 64, 128), (10113, 63, 128), (20353, 64, 64),
+                                   (12160, 256, 200), (12289, 250, 256), (24449, 130, 128), (24577, 130, 128),
+                                   (32769, 128, 66), (98177, 70, 48), (98176, 70, 48)])
+def test_split_products_at_tile_edges(dev, n, d, h):
+    print("split product", n, d, h, flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n + d)
+    X = torch.randn((n, d), generator=g, device=dev)
+    W = torch.randn((d, h), generator=g, device=dev)
+    Z = _transform(X, W).double()
+    exact = X.double() @ W.double()
+    bound = (d + 4) * 2.0 ** -24 * (X.double().abs() @ W.double().abs())
+    worst = float(((Z - exact).abs() / bound).max())
+    assert worst <= 1.0
+
+
+@pytest.mark.parametrize("n,d,h", [(60000, 602, 128), (40000, 33, 48), (100000, 100, 64), (90000, 130, 100),
+                                   (30000, 256, 256), (40000, 602, 41), (40000, 20, 64), (40000, 200, 32)])
+def test_rows_do_not_depend_on_their_number(dev, n, d, h):
+    """A row's bits are the same alone, among few and among all rows, and
+    wherever it stands among them."""
+    print("rows of", n, d, h, flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n + h)
+    X = torch.randn((n, d), generator=g, device=dev)
+    W = torch.randn((d, h), generator=g, device=dev)
+    Z = _transform(X, W)
+    for a, b in ((7, 8), (0, 300), (n - 1001, n), (5, 13005), (100, 30000)):
+        assert torch.equal(_transform(X[a:b], W), Z[a:b]), (a, b)
 
 
 @pytest.mark.parametrize("ex,ew", [(0, 0), (-100, 20), (-115, 60), (-123, 99), (40, -123), (-60, -60), (60, -110),
