@@ -188,3 +188,35 @@ def test_gat_lanes_and_batch_at_edges(dev, heads, F):
         for t in range(len(targets)):
             for a, b in zip(single[t], (batch[t].y, batch[t].f_empty_full, batch[t].cls)):
                 assert torch.equal(a, b)
+
+
+def _star(dev, n, X, P):
+    """Node 0 with the in-neighbours 1 .. n, which have none."""
+    indptr, indices = W.in_csr_from_directed(n + 1, np.arange(1, n + 1), np.zeros(n, np.int64))
+    return GatExplainer(indptr, indices, X, P), indptr, indices
+
+
+@pytest.mark.parametrize("heads,F", [(16, 16), (8, 16), (4, 64), (3, 80), (4, 20)])
+def test_gat_sums_over_features_are_pairwise(dev, heads, F):
+    """The layer-2 sums of one feature of 1 and many just below half its last
+    place: added one after the other to the 1 they are lost (15 of 16, or all
+    of them), added in pairs they count.  All nodes have the same layer-1 row
+    (W_1 = 0) and the same logits, so a target with one in-neighbour has
+    exactly that sum as its value.  Bound: half a unit in the last place of
+    the sum (2^-23 of it at most) per level of a tree over 256 features, and
+    one for the division."""
+    nf, s = heads * F, 0.99 * 2.0 ** -24
+    b1 = np.full(nf, s, np.float32)
+    P = dict(W1=np.zeros((3, nf), np.float32), att_src1=np.zeros((heads, F), np.float32),
+             att_dst1=np.zeros((heads, F), np.float32), b1=b1, W2=np.ones((nf, 2), np.float32),
+             att_src2=np.zeros(2, np.float32), att_dst2=np.zeros(2, np.float32), b2=np.zeros(2, np.float32))
+    for at in (0, nf // 2 + 3, nf - 1):
+        _say("gat sums", heads, F, at)
+        P["b1"] = b1.copy()
+        P["b1"][at] = 1.0
+        ex, indptr, indices = _star(dev, 2, np.ones((3, 3), np.float32), P)
+        res = ex.explain(0, 2, 1)
+        torch.cuda.synchronize()
+        exact = 1.0 + (nf - 1) * float(np.float32(s))
+        got = np.concatenate([res.y.cpu().numpy(), res.f_empty_full.cpu().numpy()]).astype(np.float64)
+        assert np.abs(got - exact).max() <= 9 * 2.0 ** -24 * exact, (got - exact) * 2.0 ** 24
