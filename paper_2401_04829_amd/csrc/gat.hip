@@ -201,6 +201,14 @@ __device__ float value_at_v(const GatDev& g, int32_t c, Present present) {
 // per class: 89 us per Cora-shaped target before).
 constexpr int kEndsWaves = 16;
 
+__device__ __forceinline__ float pair_sum(float (&t)[kEndsWaves]) {
+#pragma unroll
+  for (int n = kEndsWaves / 2; n > 0; n >>= 1)
+#pragma unroll
+    for (int w = 0; w < n; ++w) t[w] += t[w + n];
+  return t[0];
+}
+
 __device__ __forceinline__ void ends_body(const GatJob& J) {
   __shared__ float rows[kEndsWaves + 1][kGatMaxFeat];   // the wavefronts' sums; the last one: the row under the empty coalition
   __shared__ float mxs[kEndsWaves], sums[kEndsWaves];
@@ -217,24 +225,33 @@ __device__ __forceinline__ void ends_body(const GatJob& J) {
   layer1(g, 0, all, o);
   const float sdv = dot_nf(g, o, g.u2d, 1);
   float mx = -INFINITY, sum = 0.f;
-  if (wv == 0) {
-    mx = leaky(dot_nf(g, o, g.u2s, 1) + sdv, g.slope);
+  auto first = [&](float lx) {
+    mx = lx;
     sum = 1.f;
 #pragma unroll
     for (int i = 0; i < kGatSlots; ++i) acc[i] = o[i];
-  } else {
+  };
 #pragma unroll
-    for (int i = 0; i < kGatSlots; ++i) acc[i] = 0.f;
-  }
+  for (int i = 0; i < kGatSlots; ++i) acc[i] = 0.f;
+  if (wv == 0) first(leaky(dot_nf(g, o, g.u2s, 1) + sdv, g.slope));
   for (int64_t e = wv; e < g.indeg_v; e += kEndsWaves) {
     layer1(g, g.esrc[e], all, o);
     const float lx = leaky(dot_nf(g, o, g.u2s, 1) + sdv, g.slope);
-    const float mn = fmaxf(mx, lx);
-    const float r = mx == mn ? 1.f : expf(mx - mn), wx = lx == mn ? 1.f : expf(lx - mn);
-    sum = sum * r + wx;
+    if (sum == 0.f) {
+      first(lx);
+    } else if (lx > mx) {
+      const float r = expf(mx - lx);
+      sum = sum * r + 1.f;
 #pragma unroll
-    for (int i = 0; i < kGatSlots; ++i) acc[i] = acc[i] * r + wx * o[i];
-    mx = mn;
+      for (int i = 0; i < kGatSlots; ++i) acc[i] = acc[i] * r + o[i];
+      mx = lx;
+    } else {
+      // (two logits of -inf without v among them: their weight is taken below)
+      const float wx = wv > 0 && lx == -INFINITY && mx == -INFINITY ? 1.f : expf(lx - mx);
+      sum += wx;
+#pragma unroll
+      for (int i = 0; i < kGatSlots; ++i) acc[i] += wx * o[i];
+    }
   }
 #pragma unroll
   for (int i = 0; i < kGatSlots; ++i)
@@ -244,25 +261,34 @@ __device__ __forceinline__ void ends_body(const GatJob& J) {
     sums[wv] = sum;
   }
   __syncthreads();
+  // The wavefronts' sums at the largest logit of all.  As in the kernels of
+  // the coalitions, one logit of +inf takes all the weight and a second one
+  // leaves no number.
   float top = mxs[0];
-  for (int w = 1; w < kEndsWaves; ++w) top = fmaxf(top, mxs[w]);
-  float total = 0.f;
-  float scale[kEndsWaves];
+  int infs = 0;
 #pragma unroll
   for (int w = 0; w < kEndsWaves; ++w) {
-    scale[w] = sums[w] > 0.f ? expf(mxs[w] - top) : 0.f;   // (a wavefront without neighbours has no sum)
-    total += sums[w] * scale[w];
+    top = fmaxf(top, mxs[w]);
+    infs += mxs[w] == INFINITY ? 1 : 0;
   }
+  float scale[kEndsWaves], t[kEndsWaves];
+#pragma unroll
+  for (int w = 0; w < kEndsWaves; ++w) {
+    // (a wavefront without neighbours has no sum)
+    scale[w] = sums[w] == 0.f ? 0.f : mxs[w] == top && infs < 2 ? 1.f : expf(mxs[w] - top);
+    t[w] = sums[w] * scale[w];
+  }
+  const float total = pair_sum(t);
 #pragma unroll
   for (int i = 0; i < kGatSlots; ++i) {
     const int f = lane + 64 * i;
-    float v = 0.f;
+    acc[i] = o[i] = 0.f;
     if (f < g.nf) {
 #pragma unroll
-      for (int w = 0; w < kEndsWaves; ++w) v += rows[w][f] * scale[w];
+      for (int w = 0; w < kEndsWaves; ++w) t[w] = rows[w][f] * scale[w];
+      acc[i] = pair_sum(t) / total;
+      o[i] = rows[kEndsWaves][f];
     }
-    acc[i] = v / total;
-    o[i] = f < g.nf ? rows[kEndsWaves][f] : 0.f;
   }
   for (int32_t c = wv; c < g.C; c += kEndsWaves) {
     const float fe = dot_nf(g, o, g.W2 + c, g.C) + g.b2[c], ff = dot_nf(g, acc, g.W2 + c, g.C) + g.b2[c];

@@ -220,3 +220,49 @@ def test_gat_sums_over_features_are_pairwise(dev, heads, F):
         exact = 1.0 + (nf - 1) * float(np.float32(s))
         got = np.concatenate([res.y.cpu().numpy(), res.f_empty_full.cpu().numpy()]).astype(np.float64)
         assert np.abs(got - exact).max() <= 9 * 2.0 ** -24 * exact, (got - exact) * 2.0 ** 24
+
+
+@pytest.mark.parametrize("F", [16, 20])
+@pytest.mark.parametrize("plus,minus", [((1,), ()), ((6,), ()), ((17,), ()), ((17,), (1, 6, 22)), ((), (6,)),
+                                        ((), (6, 22)), ((), (1,)), ((3, 6), ()), ((6, 22), ())])
+def test_gat_infinite_logits(dev, F, plus, minus):
+    """In-neighbours whose layer-2 logit overflows to +inf or -inf (finite
+    features): f(E_c) and the coalition values follow one rule wherever the
+    neighbour stands: one +inf takes all the weight, two leave no number, -inf
+    has none.  The finite logits are so far apart that the largest one (equal
+    for all other neighbours) takes the rest."""
+    _say("gat infinite logits", F, plus, minus)
+    n = 24
+    X = np.zeros((n + 1, 3), np.float32)
+    X[:, 0], X[:, 1] = 0.5, 1.0
+    X[0, 0] = 0.1
+    X[list(plus), 0] = 2.0
+    X[list(minus), 2] = 2.0
+    W1 = np.zeros((3, F), np.float32)
+    W1[0, 0], W1[1, 1], W1[2, 2] = 1.0, 0.3, 1.0
+    W2 = np.zeros((F, 2), np.float32)
+    W2[:, 0] = 0.25
+    W2[0, 1], W2[2, 1] = 1.0, -1.0
+    P = dict(W1=W1, att_src1=np.zeros((1, F), np.float32), att_dst1=np.zeros((1, F), np.float32),
+             b1=np.zeros(F, np.float32), W2=W2, att_src2=np.array([0.0, 3e38], np.float32),
+             att_dst2=np.zeros(2, np.float32), b2=np.zeros(2, np.float32))
+    ex, indptr, indices = _star(dev, n, X, P)
+    res = ex.explain(0, 200, 1, target_class=0)
+    torch.cuda.synchronize()
+    rows = 0.25 * (X[:, 0] + 0.3 + X[:, 2])          # a node's layer-1 row times W_2[:, 0], ELU the identity
+
+    def value(has):
+        many = [j for j in plus if has[j - 1]]
+        rest = [j for j in range(1, n + 1) if has[j - 1] and j not in plus and j not in minus]
+        if many:
+            return rows[many[0]] if len(many) == 1 else np.nan
+        if rest:
+            return rows[rest[0]]
+        return None                                   # v alone beside neighbours of no weight
+
+    sel = sampler.unpack(masks_np(res.masks), n)
+    want = [value(s) for s in sel]
+    keep = [i for i, w in enumerate(want) if w is not None]
+    assert len(keep) > 100
+    np.testing.assert_allclose(res.y.cpu().numpy()[keep], [want[i] for i in keep], rtol=1e-6)
+    np.testing.assert_allclose(res.f_empty_full.cpu().numpy()[1], value(np.ones(n, bool)), rtol=1e-6)
