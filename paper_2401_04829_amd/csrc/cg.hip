@@ -956,14 +956,16 @@ gnnshap::CgShape gnnshap::cg_shape(int64_t M, int64_t wpr, int64_t kr, int64_t r
   s.kr = kr;
   s.nrb = ceil_div(kr, 64);
   // sparse rows: the longest run of random rows from the first whose sizes are
-  // at most M / kSparseDiv, cut to whole 64-row groups
+  // at most M / kSparseDiv and ascend (a block's last row is its largest, as
+  // its padded lists need; other orders of a caller's class table end the
+  // run), cut to whole 64-row groups
   if (kr > 0 && classes) {
     const int64_t tmax = M / kSparseDiv;
     std::vector<int32_t> sz;
     sz.reserve(static_cast<size_t>(kr));
     for (int64_t i = 0; i < ncls && static_cast<int64_t>(sz.size()) < kr; ++i) {
       if (classes[i].row_begin + classes[i].row_count <= rb0) continue;
-      if (classes[i].size > tmax) break;
+      if (classes[i].size > tmax || (!sz.empty() && classes[i].size < sz.back())) break;
       const int64_t from = std::max<int64_t>(classes[i].row_begin, rb0);
       for (int64_t r = from; r < classes[i].row_begin + classes[i].row_count; ++r) sz.push_back(classes[i].size);
     }
@@ -986,8 +988,10 @@ gnnshap::CgWs gnnshap::cg_carve(Carver& c, const CgShape& sh) {
   w.s = c.take<double>(sh.M);
   w.us = c.take<double>(sh.rs > 0 ? sh.rs : 1);
   w.rdig = c.take<char>(digit_bytes(sh.wpr));
-  w.udig = c.take<char>(std::max<int64_t>(digit_bytes(sh.nbits), 1));
-  w.uu = c.take<double>(2 * std::max<int64_t>(2 * sh.nbits + sh.rbd0, 1));
+  // (sized for no sparse rows, so that a table with fewer of them than the
+  // plan's own, which workspace queries assume, needs no more)
+  w.udig = c.take<char>(std::max<int64_t>(digit_bytes(sh.nrb), 1));
+  w.uu = c.take<double>(2 * std::max<int64_t>(2 * sh.nrb, 1));
   w.rr = c.take<double>(3 * 2 * sh.wpr);
   w.mx = c.take<double>(4 * 2 * sh.wpr);
   w.hist = c.take<double>(2);

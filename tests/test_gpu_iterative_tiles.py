@@ -8,7 +8,8 @@ import torch
 
 from oracle import sampler
 from paper_2401_04829_amd import _lib as L
-from tests.gpu_util import require_gpu, sample_on_gpu
+from paper_2401_04829_amd.explainer import _vp
+from tests.gpu_util import masks_np, require_gpu, sample_on_gpu
 from tests.test_gpu_iterative import _game, _oracle_rows, _solve
 
 pytestmark = pytest.mark.gpu
@@ -71,3 +72,61 @@ def test_more_rows_than_one_accumulation_segment(dev):
     got, info = _solve(dev, plan, classes, masks, y, fef)
     assert info == 0
     assert np.abs(got - want).max() <= 1e-4 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("order", ["as planned", "small sizes mixed", "descending"])
+def test_class_tables_in_any_order(dev, order):
+    """The random classes of a plan in another order of sizes, as the solve
+    accepts them (the sparse rows are the first ones of small sizes): phi
+    against the exact solution of the projected normal equations on these
+    rows; bound as for the tile edges."""
+    M, p = 1300, 30000
+    print("class order", order, flush=True)
+    plan, classes = L.gnnshap_plan_samples(M, p, 3, 4)
+    plan.iterative_threshold = 1
+    full = [c for c in classes if c.full]
+    rand = [c for c in classes if not c.full]
+    if order == "small sizes mixed":
+        few = [c for c in rand if c.size <= M // 128]
+        assert len(few) >= 6 and min(c.row_count for c in few) >= 64
+        few = [c for pair in zip(few[::-1], few) for c in pair][:len(few)]
+        rand = few + [c for c in rand if c.size > M // 128]
+    elif order == "descending":
+        rand = rand[::-1]
+    table = type(classes)(*[L.gnnshap_class(size=c.size, full=c.full, row_count=c.row_count, weight=c.weight)
+                            for c in full + rand])
+    row = 0
+    for c in table:
+        c.row_begin = row
+        row += c.row_count
+    masks = torch.empty((plan.num_rows, plan.words_per_row), dtype=torch.int64, device=dev)
+    weights = torch.empty(plan.num_rows, device=dev)
+    ws = torch.empty(max(L.gnnshap_sample_workspace(plan), 256), dtype=torch.uint8, device=dev)
+    L.gnnshap_sample_coalitions(plan, table, _vp(masks), _vp(weights), _vp(ws), ws.numel(),
+                                torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    mb = sampler.unpack(masks_np(masks), M)
+    sizes = np.concatenate([np.full(c.row_count, c.size) for c in table])
+    np.testing.assert_array_equal(mb[:plan.num_rows // 2].sum(1), sizes)
+    w = weights.cpu().numpy().astype(np.float64)
+    v, f0, f1 = _game(M, mb, 3)
+    yv = v(mb).astype(np.float32)
+    fef = np.array([f0, f1], np.float32)
+    phi, info = _solve(dev, plan, table, masks, torch.tensor(yv, device=dev), torch.tensor(fef, device=dev))
+    assert info == 0
+    _check_projected(phi, mb, w, yv, fef)
+
+
+def _check_projected(phi, mb, w, yv, fef):
+    """phi against the exact solution of the projected normal equations:
+    |psi - psi*|_2 <= 1e-6 |b| / lambda_min, the iteration's tolerance, plus
+    fp32 roundings."""
+    M = mb.shape[1]
+    delta = float(fef[1]) - float(fef[0])
+    P = mb - mb.mean(1, keepdims=True)
+    A = (P * w[:, None]).T @ P
+    b = P.T @ (w * (yv.astype(np.float64) - float(fef[0]) - delta / M * mb.sum(1)))
+    S = A + A.trace() / M * np.full((M, M), 1.0 / M)
+    ref = delta / M + np.linalg.solve(S, b)
+    bound = 1e-6 * np.linalg.norm(b) / np.linalg.eigvalsh(S)[0] + 1e-6 * np.linalg.norm(ref)
+    assert np.linalg.norm(phi - ref) <= bound, (np.linalg.norm(phi - ref), bound)
