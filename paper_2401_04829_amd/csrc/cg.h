@@ -11,7 +11,7 @@ namespace gnnshap {
 // Device state of one iterative solve.
 struct CgState {
   double rr0;      // squared norm of the initial residual
-  int32_t done;    // set by the iteration that stops
+  int32_t last;    // passes of iterations beyond this one do nothing: set by the pass that stops
   int32_t iters;   // iterations run
   int32_t status;  // 0 converged, 1 iteration limit, 2 lost positive curvature
   int32_t pad;

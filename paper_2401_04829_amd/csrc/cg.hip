@@ -411,7 +411,7 @@ __global__ void __launch_bounds__(256) k_cg_init(Args a, const double* __restric
   }
   if (j == 0) {
     a.r[a.M] = 0.0;
-    a.st->done = 0;
+    a.st->last = INT32_MAX;
     a.st->iters = 0;
     a.st->status = 0;
   }
@@ -448,7 +448,7 @@ __device__ __forceinline__ void cg_stop(const Args& a, int64_t t, double g) {
   const bool bad = !(g == g) || g > 1e300;
   const bool conv = !bad && g <= a.tol2 * g0;
   if (conv || bad || t >= a.maxit) {
-    a.st->done = 1;
+    a.st->last = static_cast<int32_t>(t) - 1;
     a.st->iters = static_cast<int32_t>(t);
     a.st->status = conv ? 0 : (bad ? 2 : 1);
     __hip_atomic_store(a.host_flag + 1, static_cast<int32_t>(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -484,7 +484,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6
   // workgroup 0 may set this while others start: a wavefront that sees it ends
   // (barriers wait for the wavefronts that are left), the rest computes values
   // that nobody reads
-  if (a.st->done) return;
+  if (a.st->last < static_cast<int32_t>(t)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t nx = std::max<int64_t>((4 * a.nbits + TW - 1) / TW, 1);
@@ -581,7 +581,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
   const int m = member_of(g, bid);
   const Args& a = g.a[m];
   const int64_t t = g.t[m];
-  if (a.st->done) return;
+  // set by an earlier launch, or to t by this one: all wavefronts go the same
+  // way, as they must before x is written
+  if (a.st->last < static_cast<int32_t>(t)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   BitProducts<TW> bp;
@@ -659,7 +661,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
   const double mq = sums[3] / static_cast<double>(a.M);
   if (!(den > 0.0 && step < 1e300 && beta == beta)) {   // identical in every workgroup
     if (bid == 0 && tid == 0) {
-      a.st->done = 1;
+      a.st->last = static_cast<int32_t>(t);
       a.st->iters = static_cast<int32_t>(t);
       a.st->status = 2;
       __hip_atomic_store(a.host_flag + 1, static_cast<int32_t>(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

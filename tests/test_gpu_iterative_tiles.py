@@ -130,3 +130,32 @@ def _check_projected(phi, mb, w, yv, fef):
     ref = delta / M + np.linalg.solve(S, b)
     bound = 1e-6 * np.linalg.norm(b) / np.linalg.eigvalsh(S)[0] + 1e-6 * np.linalg.norm(ref)
     assert np.linalg.norm(phi - ref) <= bound, (np.linalg.norm(phi - ref), bound)
+
+
+@pytest.mark.parametrize("M", [700, 5003])
+def test_a_solve_that_breaks_down_leaves_its_iterate(dev, M):
+    """A negative weight of the random rows (no enumerated class) makes the
+    operator negative definite: the first step has no positive curvature, in
+    every workgroup.  info says so, and phi is the iterate as it was, Delta / M
+    for every player, whichever workgroups run when the first one finds it."""
+    plan, classes = L.gnnshap_plan_samples(M, 40000 if M > 5000 else 400, 3, 4)
+    assert plan.random_begin == 0
+    plan.iterative_threshold = 1
+    masks = torch.empty((plan.num_rows, plan.words_per_row), dtype=torch.int64, device=dev)
+    weights = torch.empty(plan.num_rows, device=dev)
+    ws = torch.empty(max(L.gnnshap_sample_workspace(plan), 256), dtype=torch.uint8, device=dev)
+    L.gnnshap_sample_coalitions(plan, classes, _vp(masks), _vp(weights), _vp(ws), ws.numel(),
+                                torch.cuda.current_stream().cuda_stream)
+    plan.random_weight = -1e-4
+    for c in classes:
+        c.weight = plan.random_weight
+    g = torch.Generator(device=dev)
+    g.manual_seed(1)
+    y = torch.randn(plan.num_rows, generator=g, device=dev)
+    fef = torch.tensor([0.25, 3.0], device=dev)
+    want = np.float32((3.0 - 0.25) / M)
+    for turn in range(20):
+        print("breakdown", M, turn, flush=True)
+        phi, info = _solve(dev, plan, classes, masks, y, fef)
+        assert info == M + 1
+        assert np.all(phi.astype(np.float32) == want)
