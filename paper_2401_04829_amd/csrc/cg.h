@@ -24,6 +24,7 @@ struct CgWs {
   double* p;       // M: search direction
   double* s;       // M: A p
   double* us;      // rs: R r of the sparse rows
+  double* qd;      // parts x (4 words_per_row + 5) x 256: digit sums of R^T u by part (parts > 1)
   char* rdig;      // digits of r, MFMA operands over the players
   char* udig;      // digits of R r of the bit rows, MFMA operands over these rows
   double* uu;      // (2 nbits + rbd0) x 2: partial |u|^2 and |m|.u
@@ -49,6 +50,7 @@ struct CgShape {
   int64_t rs, nnz;         // sparse rows [0, rs) (whole row blocks), their players
   int64_t rbd0;            // first row block of the bit products (rs / 64)
   int64_t nbits;           // row blocks of the bit products
+  int64_t parts;           // parts of them in pass B (1: its own workgroups take all)
   int64_t nell;            // padded entries of the sparse rows' lists
 };
 // The split of the random rows [rb0, rb0 + kr) of a class table into sparse

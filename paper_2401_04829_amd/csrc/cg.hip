@@ -42,7 +42,8 @@
 // lists and the entries of r they name without following pointers; for pass
 // B by player, in ascending row order, eight lanes summing one player's list.
 //
-// Per iteration t, two launches:
+// Per iteration t, two launches (three where pass B's products are split over
+// parts of the rows, whose digit sums pass B adds: exact, so the same bits):
 //   pass A   stopping test on gamma_t; u = R r of the bit rows (a workgroup
 //            per 64 rows, its wavefronts sharing the players), the digits of
 //            u, partial |u|^2 and |m|.u; in workgroups of their own the same
@@ -120,6 +121,8 @@ struct Args {
   int32_t* ex;     // fixed-point exponents: r of even and odd iterations, u
   gnnshap::CgState* st;
   int32_t* host_flag;  // mapped host memory: [0] done, [1] iterations
+  double* qd;          // parts x the digit sums of R^T u (parts > 1)
+  int64_t parts;       // parts of the bit rows in pass B's products
 };
 
 // The members of one launch of a pass: member m owns workgroups
@@ -263,6 +266,7 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 // The digit operand of half h of group q.
 __device__ __forceinline__ v8i load_operand(const char* __restrict__ dig, int q, int h) {
@@ -279,6 +283,11 @@ __device__ __forceinline__ v4f mma_half(uint32_t m, v8i b, v4f acc) {
   const v8i a = {static_cast<int>(m & 0x11111111u), static_cast<int>(m & 0x22222222u),
                  static_cast<int>(m2 & 0x11111111u), static_cast<int>(m2 & 0x22222222u), 0, 0, 0, 0};
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, acc, 4, 2, 0, 0, 0, 0);
+}
+
+// Blocks of 64 bit rows per part of pass B's products, whole groups of four.
+__host__ __device__ __forceinline__ int64_t part_blocks(int64_t nbits, int64_t parts) {
+  return ((nbits + 3) / 4 + parts - 1) / parts * 4;
 }
 
 // A workgroup's product of 16 TW bit rows (or players' columns) with the
@@ -328,15 +337,15 @@ struct BitProducts {
     for (int t = 0; t < TW; ++t) a[t] = mma_half(static_cast<uint32_t>(s.w[t] >> 32), s.b1, a[t]);
   }
 
-  // this wavefront's first group, so that its loads run under whatever comes before run()
+  // this wavefront's first group, so that its loads run under whatever comes before sums()
   __device__ __forceinline__ void start(int wave) { load(min(wave, (nk + 3) / 4 - 1)); }
 
-  // row[c] (wavefronts 0 .. TW - 1): 2^-e times the product of row 16 wave + 4 (lane / 16) + c,
-  // in all 16 lanes of a row of lanes.  The digit sums of the wavefronts are
-  // added (whole eighths) and combined in fp64.  buf: kWaves * TW * 256 floats.
-  // Every thread calls it; it ends behind a barrier that covers all LDS
-  // writes before it.
-  __device__ __forceinline__ void run(int wave, int e, float* buf, double (&row)[4]) {
+  // row[c] (wavefronts 0 .. TW - 1), lane 16 g + d: the sum of digit d over
+  // row 16 wave + 4 g + c, in eighths: a whole number, exact.  The wavefronts'
+  // sums are added (whole eighths).  buf: kWaves * TW * 256 floats.  Every
+  // thread calls it; it ends behind a barrier that covers all LDS writes
+  // before it.
+  __device__ __forceinline__ void sums(int wave, float* buf, double (&row)[4]) {
     const int lane = threadIdx.x & 63;
     const int nq = (nk + 3) / 4;
     row[0] = row[1] = row[2] = row[3] = 0.0;
@@ -368,12 +377,17 @@ struct BitProducts {
         for (int c = 0; c < 4; ++c) row[c] += static_cast<double>(sum[c]);
       }
     }
-    // lane 16 g + d holds digit d: times 16^d (and 8: the sums are in eighths), then over the digits
-    const double weight = __longlong_as_double(static_cast<long long>(1023 + 4 * (lane & 15) + 3) << 52);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) row[c] = __builtin_ldexp(row_sum_d(row[c] * weight), -e);
   }
 };
+
+// 2^-e times the product of row 4 (lane / 16) + c from its digits' sums, in all
+// 16 lanes of a row of lanes: lane 16 g + d holds digit d, times 16^d (and 8:
+// the sums are in eighths), then over the digits in fp64.
+__device__ __forceinline__ void combine_digits(double (&row)[4], int e) {
+  const double weight = __longlong_as_double(static_cast<long long>(1023 + 4 * (threadIdx.x & 15) + 3) << 52);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) row[c] = __builtin_ldexp(row_sum_d(row[c] * weight), -e);
+}
 
 // The value of lane 16 g + d, d < 4: row[d].
 __device__ __forceinline__ double pick_row(const double (&row)[4], int lane) {
@@ -542,7 +556,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6
   }
   if (a.nbits == 0) return;
   double row[4];
-  bp.run(wave, er, buf, row);
+  bp.sums(wave, buf, row);
+  combine_digits(row, er);
   // |u_b| <= sqrt(M) |r| (Cauchy-Schwarz) gives the digits of u their exponent
   const int eu = fixed_exponent(1.0000001 * __builtin_sqrt(static_cast<double>(a.M) * gamma));
   if (wave < TW) {
@@ -569,8 +584,37 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6
   if (bid == 0 && tid == 0) a.ex[2] = eu;
 }
 
-// Pass B.  Workgroup x: players 16 TW x .. (see the recurrences above).
+// The products of pass B for part y of the bit rows and players 16 TW x ..,
+// workgroup y ceil(4 wpr / TW) + x: the digits' sums, for pass B to add.  For
+// systems of few players and so many rows that pass B's own workgroups, one
+// per 64 or 96 players, would leave most CUs idle for long.
 template <int TW>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_cg_pass_b_part(GroupArgs g) {
+  __shared__ alignas(16) float buf[kWaves * TW * 256];
+  int64_t bid;
+  const int m = member_of(g, bid);
+  const Args& a = g.a[m];
+  const int64_t t = g.t[m];
+  if (a.st->last < static_cast<int32_t>(t)) return;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t nx = (4 * a.wpr + TW - 1) / TW, x = bid % nx, y = bid / nx;
+  const int64_t per = part_blocks(a.nbits, a.parts), b0 = y * per;
+  const int64_t nb = a.nbits - b0 < per ? a.nbits - b0 : per;
+  double row[4] = {};
+  if (nb > 0) {   // (the last parts may be empty)
+    BitProducts<TW> bp;
+    bp.set(a.T, a.rbd0 + b0, x * TW, 4 * a.wpr, a.nrb, nb, a.udig + b0 / 4 * (2 * kOperand));
+    bp.start(wave);
+    bp.sums(wave, buf, row);
+  }
+  if (wave < TW)
+    reinterpret_cast<v4d*>(a.qd)[((y * nx + x) * TW + wave) * 64 + (threadIdx.x & 63)] = v4d{row[0], row[1], row[2], row[3]};
+}
+
+// Pass B.  Workgroup x: players 16 TW x .. (see the recurrences above).  PARTS:
+// some of the members have their products in parts (the branch costs the others
+// 1 %).
+template <int TW, bool PARTS>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_cg_pass_b(GroupArgs g) {
   __shared__ alignas(16) float buf[kWaves * TW * 256];
   __shared__ double sparse[16 * TW];
@@ -586,8 +630,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
   if (a.st->last < static_cast<int32_t>(t)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool whole = a.nbits > 0 && !(PARTS && a.parts > 1);
   BitProducts<TW> bp;
-  if (a.nbits > 0) {
+  if (whole) {
     bp.set(a.T, a.rbd0, bid * TW, 4 * a.wpr, a.nrb, a.nbits, a.udig);
     bp.start(wave);
   }
@@ -646,11 +691,26 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     if ((tid & 7) == 0 && 64 * h + (tid >> 3) < 16 * TW) sparse[64 * h + (tid >> 3)] = v;
   }
   double row[4] = {};
-  if (a.nbits > 0) {
-    bp.run(wave, eu, buf, row);
+  if (whole) {
+    bp.sums(wave, buf, row);
   } else {
+    if (PARTS && a.parts > 1 && wave < TW) {
+      // the parts' sums (whole numbers below 2^53 together: any order is exact)
+      const v4d* qd = reinterpret_cast<const v4d*>(a.qd) + (bid * TW + wave) * 64 + lane;
+      const int64_t stride = ((4 * a.wpr + TW - 1) / TW) * TW * 64;
+      for (int64_t q = 0; q < a.parts; q += 8) {
+        v4d v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = q + k < a.parts ? qd[(q + k) * stride] : v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) row[c] += v[k][c];
+      }
+    }
     __syncthreads();
   }
+  combine_digits(row, eu);
   const double gamma = sums[0], uu = sums[2];
   double beta = 0.0, den = a.alpha * gamma + a.wr2 * uu;
   if (t > 0) {
@@ -715,7 +775,11 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 // The instance of a pass for `tiles` tiles per workgroup (4 or 6).
 using PassFn = void (*)(GroupArgs);
 PassFn pass_a(int tiles) { return tiles == 4 ? k_cg_pass_a<4> : k_cg_pass_a<6>; }
-PassFn pass_b(int tiles) { return tiles == 4 ? k_cg_pass_b<4> : k_cg_pass_b<6>; }
+PassFn pass_b_part(int tiles) { return tiles == 4 ? k_cg_pass_b_part<4> : k_cg_pass_b_part<6>; }
+PassFn pass_b(int tiles, bool parts) {
+  return tiles == 4 ? (parts ? k_cg_pass_b<4, true> : k_cg_pass_b<4, false>)
+                    : (parts ? k_cg_pass_b<6, true> : k_cg_pass_b<6, false>);
+}
 
 // ---- the sparse rows' lists, built once per solve ------------------------------------------
 
@@ -978,6 +1042,13 @@ gnnshap::CgShape gnnshap::cg_shape(int64_t M, int64_t wpr, int64_t kr, int64_t r
   }
   s.rbd0 = s.rs / 64;
   s.nbits = s.nrb - s.rbd0;
+  // Pass B in parts: up to 128 word columns (two workgroups of 64 players per
+  // CU are 512) and from 196,608 bit rows on, whose products take a workgroup
+  // 32 us and more, against the ~12 us that another launch and the parts' sums
+  // cost.  The solve of 5,001 players x 1,600,000 coalitions 4.29 -> 3.32 ms,
+  // x 800,000 2.65 -> 2.12, 2,000 x 1,600,000 3.36 -> 2.14; 12,000 x 1,600,000
+  // (188 workgroups) is left whole at 7.2 ms.
+  s.parts = wpr <= 128 && s.nbits >= 3072 ? std::min<int64_t>({512 / wpr, s.nbits / 512, 64}) : 1;
   return s;
 }
 
@@ -994,6 +1065,7 @@ gnnshap::CgWs gnnshap::cg_carve(Carver& c, const CgShape& sh) {
   // plan's own, which workspace queries assume, needs no more)
   w.udig = c.take<char>(std::max<int64_t>(digit_bytes(sh.nrb), 1));
   w.uu = c.take<double>(2 * std::max<int64_t>(2 * sh.nrb, 1));
+  w.qd = c.take<double>(sh.parts > 1 ? sh.parts * (4 * sh.wpr + 5) * 256 : 1);
   w.rr = c.take<double>(3 * 2 * sh.wpr);
   w.mx = c.take<double>(4 * 2 * sh.wpr);
   w.hist = c.take<double>(2);
@@ -1070,6 +1142,8 @@ int gnnshap::CgGroup::add(const CgProblem& pr, const CgShape& sh, const CgWs& w)
   a.p = w.p;
   a.s = w.s;
   a.us = w.us;
+  a.qd = w.qd;
+  a.parts = sh.parts;
   a.rdig = w.rdig;
   a.udig = w.udig;
   a.uu = w.uu;
@@ -1233,12 +1307,20 @@ int gnnshap::CgGroup::step() {
       pass_a(ta)<<<n, kThreads, 0, s>>>(g);
     }
     GS_LAUNCHED();
+    n = fill_group(g, S.mem, dt, [](const Member& m, int64_t t) { return t < kMaxIt && m.sh.parts > 1; },
+                   [tb](const Member& m) { return static_cast<uint32_t>(blocks_b(m.sh, tb) * m.sh.parts); });
+    const bool parts = g.n > 0;
+    if (parts) {
+      GS_TIMED("k_cg_pass_b_part", s);
+      pass_b_part(tb)<<<n, kThreads, 0, s>>>(g);
+    }
+    GS_LAUNCHED();
     n = fill_group(g, S.mem, dt, [](const Member&, int64_t t) { return t < kMaxIt; },
                    [tb](const Member& m) { return static_cast<uint32_t>(blocks_b(m.sh, tb)); });
     if (g.n > 0) {
       {
         GS_TIMED("k_cg_pass_b", s);
-        pass_b(tb)<<<n, kThreads, 0, s>>>(g);
+        pass_b(tb, parts)<<<n, kThreads, 0, s>>>(g);
       }
       GS_LAUNCHED();
     }

@@ -49,28 +49,56 @@ def test_products_at_tile_edges(dev, M, p):
     assert np.linalg.norm(phi - ref) <= bound, (np.linalg.norm(phi - ref), bound)
 
 
-def test_more_rows_than_one_accumulation_segment(dev):
-    """More than 4096 x 8 groups of 256 random rows: the digit sums are
-    emptied between segments.  Against the factored solver on the same rows
-    (exact counts), within the iteration's 1e-6 and the factorisation's fp32."""
-    M, p = 64, 18_400_000
-    print("iterative segments", M, p, flush=True)
+def _linear_and_tanh(masks, M, a):
+    at = torch.arange(64, device=masks.device)
+    out = []
+    for m in masks.split(1 << 14 if M > 64 else 1 << 20):
+        t = ((m[:, :, None] >> at) & 1).view(m.shape[0], -1)[:, :M].float() @ a
+        out.append(t + torch.tanh(t))
+    return torch.cat(out)
+
+
+def _factored_and_iterative(dev, M, p):
+    """phi of the same rows by the factored solver (exact counts) and iteratively."""
     plan, classes, masks, _ = sample_on_gpu(M, p, 7, 8)
-    kr = plan.num_rows // 2 - plan.random_begin
-    assert kr > 4096 * 8 * 256
     g = torch.Generator(device=dev)
     g.manual_seed(9)
-    a = torch.randn(M, generator=g, device=dev)
-    at = torch.arange(64, device=dev)
-    t = torch.cat([((m[:, :1] >> at) & 1).float() @ a for m in masks.split(1 << 20)])
-    y = t + torch.tanh(t)
-    f1 = float(a.sum() + torch.tanh(a.sum()))
-    fef = torch.tensor([0.0, f1], device=dev)
-    want, info = _solve(dev, plan, classes, masks, y, fef)
-    assert info == 0
-    plan.iterative_threshold = 1
-    got, info = _solve(dev, plan, classes, masks, y, fef)
-    assert info == 0
+    a = torch.randn(M, generator=g, device=dev) / M ** 0.5
+    y = _linear_and_tanh(masks, M, a)
+    fef = torch.stack([torch.zeros((), device=dev), a.sum() + torch.tanh(a.sum())])
+    got = []
+    for threshold in (1 << 30, 1):
+        plan.iterative_threshold = threshold
+        phi, info = _solve(dev, plan, classes, masks, y, fef)
+        assert info == 0
+        got.append(phi)
+    return plan, got
+
+
+@pytest.mark.parametrize("M,p", [(8200, 2_300_000), (64, 18_400_000)])
+def test_more_rows_than_one_accumulation_segment(dev, M, p):
+    """More bit rows than the 512 x 8 groups of 256 (1,048,576) whose digit
+    sums fp32 is sure to hold: more than 128 word columns, where a workgroup
+    of pass B takes all of them and empties its sums between segments (lost or
+    doubled ones would show; that a segment's sum is exact is asserted where
+    its length is defined), and few columns, where they are taken in parts.
+    Against the factored solver on the same rows, within the iteration's 1e-6
+    and the factorisation's fp32."""
+    print("iterative segments", M, p, flush=True)
+    plan, (want, got) = _factored_and_iterative(dev, M, p)
+    sparse = 64 * 1024 if M >= 128 else 0            # at most: kept as lists
+    assert plan.num_rows // 2 - plan.random_begin - sparse > 512 * 8 * 256
+    assert np.abs(got - want).max() <= 1e-4 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("M,p", [(64, 397_000), (64, 397_500), (65, 400_000), (127, 500_002), (200, 700_000),
+                                 (2000, 560_000)])
+def test_bit_rows_in_parts(dev, M, p):
+    """Pass B's products whole just below 3,072 blocks of 64 bit rows and in
+    parts from there on (of equal and unequal length, the last one shorter),
+    one to 32 word columns.  Against the factored solver on the same rows."""
+    print("iterative parts", M, p, flush=True)
+    plan, (want, got) = _factored_and_iterative(dev, M, p)
     assert np.abs(got - want).max() <= 1e-4 * np.abs(want).max()
 
 
