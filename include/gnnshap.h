@@ -234,7 +234,8 @@ typedef struct {
  * The first GCN layer transforms each node's features independently of the
  * coalition (Sec. 3.4.2: the coalitions of a batch share the node features),
  * so X W_1 is computed once per graph and model and passed as
- * gnnshap_gcn.XW1; each explanation then gathers the rows of its subgraph. */
+ * gnnshap_gcn.XW1; each explanation then gathers the rows of its subgraph.
+ * A row of Z has the same bits whatever n is and wherever the row stands. */
 int gnnshap_transform_features(const float* X, int64_t n, int32_t d, const float* W, int32_t h,
                                float* Z, void* stream);
 

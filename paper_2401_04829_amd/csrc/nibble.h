@@ -17,8 +17,8 @@ constexpr int64_t kTabWords = 16;    // nibble tables per workgroup: 16 words (3
 // table reads.  One table is 16 fp64 entries, 128 bytes: its entries fall in
 // distinct LDS banks, so 64 lanes reading one table never conflict.  The
 // tables of a workgroup are one static LDS array, word w's 16 tables at
-// byte 2048 w.
-//
+// byte 2048 w (build_tables_bounded fills them).
+
 // acc[0..3] += sum over the set bits b of word of v[b], from the word's 16
 // tables at byte 2048 W of `tabs` (W a constant, so that the table offsets
 // are immediates of the LDS reads).  Each 32-bit half is masked into two

@@ -93,7 +93,10 @@ __device__ __forceinline__ uint64_t binom(int64_t n, int64_t r) {
 
 __device__ __forceinline__ void set_bit(uint32_t* bs, int64_t j) { bs[j >> 5] |= 1u << (j & 31); }
 
-constexpr int64_t kMaxComb = 64;   // enumerated subsets stepped incrementally up to this size
+// Enumerated subsets stepped incrementally up to this size, where a wavefront
+// has several rows (from 65,536 representative rows on); single rows are
+// unranked, which the other wavefronts hide as they do the draws.
+constexpr int64_t kMaxComb = 64;
 
 // Steps lane = 0 .. min(63, left - 1) of Floyd's algorithm, step `lane` with
 // draw u of [0, j], j = j0 + lane: t = the drawn player, or j if t is in the

@@ -13,16 +13,17 @@
 //     (all c-subsets: diagonal C(M-1,c-1), off-diagonal C(M-2,c-2));
 //   * the random rows share one weight w_r, so their part is 2 w_r P C_R P
 //     with C_R the integer co-occurrence counts of the random representative
-//     rows, computed exactly by popcounts on a bit-transposed copy.
+//     rows, computed exactly on matrix instructions from a bit-transposed copy.
 // Systems of up to 448 players are factored and solved by one workgroup
 // (several targets' systems side by side in a batch).  Larger ones, up to
 // the iterative threshold (above it the system is not formed: cg.hip), use a
 // blocked right-looking Cholesky over the whole GPU with 128-wide panels: one workgroup factors the diagonal block and
 // inverts its factor, then the panel solve (a product with that inverse) and
-// the trailing update run as fp32 MFMA GEMMs.  The triangular solves go by
-// 256-row segments whose triangle sits in LDS, with multi-block GEMVs carrying
-// each segment to the rows outside it.  The right-hand side is accumulated in
-// fp64.
+// the trailing update run as fp32 MFMA GEMMs; the forward substitution rides
+// along (the inverse times the panel's right-hand side, then its product off
+// the rows below).  The backward one goes by 256-row segments whose triangle
+// sits in LDS, with multi-block GEMVs carrying each segment to the rows before
+// it.  The right-hand side is accumulated in fp64.
 #include <algorithm>
 #include <cmath>
 
@@ -209,15 +210,12 @@ __global__ void __launch_bounds__(512) k_transpose_blocked(const uint64_t* __res
   transpose_body(masks + w, wpr, row0, nrows, 64, T + w * gridDim.x * 64, rb, 0);
 }
 
-// Counts C[i, j] = sum_rb popcount(T[rb, i] & T[rb, j]) for 64x64 tiles with J >= I,
-// stored in both halves (row stride ld): gram_body.
-// Row sums of a 64 x 64 count tile (I, J) held 4 x 4 per thread (thread
-// (ty, tx) = (tid / 16, tid % 16) holds rows ty + 16 q and columns tx + 16 r,
-// q, r < 4, so that a wavefront's LDS reads of the tile's words fall on
-// consecutive words: no bank conflicts),
-// added to usum with integer atomics (exact in any order): rows of I get the
-// tile's row sums; for an off-diagonal tile the rows of J get its column
-// sums (the mirrored tile).  Every thread of the workgroup calls it.
+// Row sums of a 64 x 64 tile (I, J), J >= I, of the counts C[i, j] = rows that
+// hold players i and j, held 4 x 4 per thread (thread (ty, tx) = (tid / 16, tid
+// % 16): rows ty + 16 q and columns tx + 16 r, q, r < 4), added to usum with
+// integer atomics (exact in any order): rows of I get the tile's row sums; for
+// an off-diagonal tile the rows of J get its column sums (the mirrored tile).
+// Every thread of the workgroup calls it.
 __device__ __forceinline__ void tile_row_sums(const int (&acc)[4][4], int64_t M, int64_t I, int64_t J,
                                               int64_t* __restrict__ usum) {
   __shared__ int colsum[64];
@@ -1392,11 +1390,11 @@ __device__ __forceinline__ void k_gemm_nt_body(const float* A, int64_t lda, cons
 // many workgroups of a quarter of the work each.
 int syrk_edge(int64_t tiles) { return tiles < 256 ? 1 : 2; }
 
-template <bool kLower, int XR, int XC>
+template <int XR, int XC>
 __global__ void __launch_bounds__(256) k_gemm_nt(const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                                                  int64_t ldc, int64_t m, int64_t n, int64_t K, float alpha,
                                                  float beta, int64_t tiles_n) {
-  k_gemm_nt_body<kLower, XR, XC>(A, lda, B, ldb, C, ldc, m, n, K, alpha, beta, tiles_n, blockIdx.x);
+  k_gemm_nt_body<false, XR, XC>(A, lda, B, ldb, C, ldc, m, n, K, alpha, beta, tiles_n, blockIdx.x);
 }
 
 // ---- multi-block path: triangular solves ------------------------------------------------
@@ -1582,9 +1580,11 @@ __global__ void k_finish(const float* __restrict__ z, int64_t M, const double* _
 // ---- multi-block path, batched: one system per blockIdx.y ---------------------------------
 //
 // Every launch covers the step of the largest system; a system whose M ends
-// before the step returns at once (whole workgroups, before any barrier), so
-// each system sees exactly the launches, grids and arguments it would see
-// alone and its factor and phi are the same bits.
+// before the step returns at once (whole workgroups, before any barrier).
+// The tiles of the trailing update may be of another size than the system
+// alone would take (syrk_edge counts the whole launch), but every element is
+// the same sum over k in the same order and one subtraction from C whatever
+// the tile, so factor and phi are the same bits.
 
 __global__ void __launch_bounds__(256) k_potrf_mb(const gnnshap::MbJob* __restrict__ jobs, int64_t o) {
   const gnnshap::MbJob J = jobs[blockIdx.y];
@@ -2296,7 +2296,7 @@ int gnnshap::solve_wls_start(const gnnshap_sample_plan* plan, const gnnshap_clas
     float* panel = w.G + r0 * ld + o;
     {
       GS_TIMED("k_trsm", s);   // panel <- panel L_jj^-T = panel Winv^T
-      k_gemm_nt<false, 1, 2><<<static_cast<unsigned>(gnnshap::ceil_div(rows, 64)), 256, 0, s>>>(
+      k_gemm_nt<1, 2><<<static_cast<unsigned>(gnnshap::ceil_div(rows, 64)), 256, 0, s>>>(
           panel, ld, w.Winv, kPB, panel, ld, rows, kPB, kPB, 1.f, 0.f, 1);
     }
     GS_LAUNCHED();
