@@ -51,7 +51,7 @@ struct CgShape {
   int64_t rbd0;            // first row block of the bit products (rs / 64)
   int64_t nbits;           // row blocks of the bit products
   int64_t parts;           // parts of them in pass B (1: its own workgroups take all)
-  int64_t nell;            // padded entries of the sparse rows' lists
+  int64_t nell;            // room for the padded entries of the sparse rows' lists
 };
 // The split of the random rows [rb0, rb0 + kr) of a class table into sparse
 // rows (coalition size at most M / kSparseDiv, whole blocks of 64 rows) and

@@ -1016,6 +1016,16 @@ bool event_done(hipEvent_t ev) {
   return true;   // complete, or an error that the wait on it reports
 }
 
+// Pass B in parts: up to 128 word columns (two workgroups of 64 players per
+// CU are 512) and from 196,608 bit rows on, whose products take a workgroup
+// 32 us and more, against the ~12 us that another launch and the parts' sums
+// cost.  The solve of 5,001 players x 1,600,000 coalitions 4.29 -> 3.32 ms,
+// x 800,000 2.65 -> 2.12, 2,000 x 1,600,000 3.36 -> 2.14; 12,000 x 1,600,000
+// (188 workgroups) is left whole at 7.2 ms.
+int64_t parts_of(int64_t wpr, int64_t nbits) {
+  return wpr <= 128 && nbits >= 3072 ? std::min<int64_t>({512 / wpr, nbits / 512, 64}) : 1;
+}
+
 }  // namespace
 
 gnnshap::CgShape gnnshap::cg_shape(int64_t M, int64_t wpr, int64_t kr, int64_t rb0, const gnnshap_class* classes,
@@ -1042,17 +1052,13 @@ gnnshap::CgShape gnnshap::cg_shape(int64_t M, int64_t wpr, int64_t kr, int64_t r
     s.rs = (std::min<int64_t>(static_cast<int64_t>(sz.size()), kr) / 64) * 64;
     if (s.rs > 64 * 1024) s.rs = 64 * 1024;   // the row lists' scan holds 1024 blocks
     for (int64_t b = 0; b < s.rs; ++b) s.nnz += sz[b];
-    for (int64_t q = 0; q < s.rs / 64; ++q) s.nell += 64 * static_cast<int64_t>(sz[64 * q + 63]);
+    // the padded lists: a block's rows have the entries of its last one, and the
+    // sizes ascend to tmax, so this holds them for any order of the classes
+    if (s.rs > 0) s.nell = s.nnz + 64 * tmax;
   }
   s.rbd0 = s.rs / 64;
   s.nbits = s.nrb - s.rbd0;
-  // Pass B in parts: up to 128 word columns (two workgroups of 64 players per
-  // CU are 512) and from 196,608 bit rows on, whose products take a workgroup
-  // 32 us and more, against the ~12 us that another launch and the parts' sums
-  // cost.  The solve of 5,001 players x 1,600,000 coalitions 4.29 -> 3.32 ms,
-  // x 800,000 2.65 -> 2.12, 2,000 x 1,600,000 3.36 -> 2.14; 12,000 x 1,600,000
-  // (188 workgroups) is left whole at 7.2 ms.
-  s.parts = wpr <= 128 && s.nbits >= 3072 ? std::min<int64_t>({512 / wpr, s.nbits / 512, 64}) : 1;
+  s.parts = parts_of(wpr, s.nbits);
   return s;
 }
 
@@ -1065,11 +1071,13 @@ gnnshap::CgWs gnnshap::cg_carve(Carver& c, const CgShape& sh) {
   w.s = c.take<double>(sh.M);
   w.us = c.take<double>(sh.rs > 0 ? sh.rs : 1);
   w.rdig = c.take<char>(digit_bytes(sh.wpr));
-  // (sized for no sparse rows, so that a table with fewer of them than the
-  // plan's own, which workspace queries assume, needs no more)
+  // (the digits, the partial sums and the parts are sized for no sparse rows, so
+  // that a table with fewer of them than the plan's own, which workspace
+  // queries assume, needs no more)
   w.udig = c.take<char>(std::max<int64_t>(digit_bytes(sh.nrb), 1));
   w.uu = c.take<double>(2 * std::max<int64_t>(2 * sh.nrb, 1));
-  w.qd = c.take<double>(sh.parts > 1 ? sh.parts * (4 * sh.wpr + 5) * 256 : 1);
+  const int64_t parts = parts_of(sh.wpr, sh.nrb);
+  w.qd = c.take<double>(parts > 1 ? parts * (4 * sh.wpr + 5) * 256 : 1);
   w.rr = c.take<double>(3 * 2 * sh.wpr);
   w.mx = c.take<double>(4 * 2 * sh.wpr);
   w.hist = c.take<double>(2);

@@ -3,6 +3,7 @@ and its host-only logic (the sample plan, argument checks, workspace
 queries) agrees with the oracle.  No device work is launched."""
 import ctypes
 import math
+import re
 
 import numpy as np
 import pytest
@@ -222,3 +223,36 @@ def test_gat_entry_points_reject_bad_arguments():
             setattr(mb, k, v)
         assert lib.gnnshap_gat_eval_workspace(ctypes.byref(sg), ctypes.byref(mb), 100, ctypes.byref(n)) == L.EINVAL, bad
     assert lib.gnnshap_gat_eval_workspace(ctypes.byref(sg), ctypes.byref(m), 0, ctypes.byref(n)) == L.EINVAL
+
+
+@pytest.mark.parametrize("M", [400, 700, 1000])
+def test_iterative_workspace_holds_any_class_order(M):
+    """The workspace of a plan, as queried, is enough for its random classes in
+    any order (where no more than 65,536 of its rows are of sizes that the
+    solver may list), on both sides of the lengths at which the solver splits
+    its rows.  The required size is read from the refusal of an empty one."""
+    rng = np.random.default_rng(M)
+    for p in range(400000, 540000, 3500):
+        plan, classes = L.gnnshap_plan_samples(M, p, 1, 2)
+        plan.iterative_threshold = 1
+        have = L.gnnshap_solve_workspace(plan)
+        full = [c for c in classes if c.full]
+        rand = [c for c in classes if not c.full]
+        small = [c for c in rand if c.size <= M // 128]
+        if sum(c.row_count for c in small) > 65536:
+            continue
+        rest = rand[len(small):]
+        for order in (small + rest, small[:-2] + small[:-3:-1] + rest, small[::-1] + rest, rest + small,
+                      [small[i] for i in rng.permutation(len(small))] + rest):
+            assert sorted(c.size for c in order) == [c.size for c in rand]
+            table = type(classes)(*[L.gnnshap_class(size=c.size, full=c.full, row_count=c.row_count, weight=c.weight)
+                                    for c in full + order])
+            row = 0
+            for c in table:
+                c.row_begin = row
+                row += c.row_count
+            with pytest.raises(L.GnnShapError, match="solve workspace needs") as e:
+                L.gnnshap_solve_wls(plan, table, 1, 1, 1, 1, 1, 1, 0, None)
+            assert e.value.status == L.ECAPACITY
+            need = int(re.search(r"needs (\d+) bytes", str(e.value)).group(1))
+            assert need <= have, (p, [c.size for c in order][:4], need, have)
