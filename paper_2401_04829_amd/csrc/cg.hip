@@ -734,8 +734,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
     return;
   }
   // |(R^T u)_j| <= sqrt(kr) |u| bounds the new s and r, and so gives the
-  // digits of r their exponent
-  const double bw = a.alpha * sums[4] + a.wr2 * (__builtin_sqrt(static_cast<double>(a.kr) * uu) + __builtin_fabs(mq));
+  // digits of r their exponent (either weight may be negative)
+  const double bw = __builtin_fabs(a.alpha) * sums[4] +
+                    __builtin_fabs(a.wr2) * (__builtin_sqrt(static_cast<double>(a.kr) * uu) + __builtin_fabs(mq));
   const int e = fixed_exponent(1.0000001 * (sums[4] + step * (bw + beta * sums[5])));
   if (wave < TW) {
     double rn = 0.0, sn = 0.0;

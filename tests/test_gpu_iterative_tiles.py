@@ -187,3 +187,35 @@ def test_a_solve_that_breaks_down_leaves_its_iterate(dev, M):
         phi, info = _solve(dev, plan, classes, masks, y, fef)
         assert info == M + 1
         assert np.all(phi.astype(np.float32) == want)
+
+
+@pytest.mark.parametrize("negative", ["random", "enumerated"])
+def test_weights_of_either_sign(dev, negative):
+    """A negative weight of the random or of the enumerated rows whose operator
+    stays positive definite: phi against the exact solution of the projected
+    normal equations."""
+    M, p = 300, 12000
+    print("weights", negative, flush=True)
+    plan, classes, masks, _ = sample_on_gpu(M, p, 5, 6)
+    plan.iterative_threshold = 1
+    mb, _ = _oracle_rows(plan, masks, 5, 6)
+    half = plan.num_rows // 2
+    in_full = np.arange(half) < plan.random_begin
+    in_full = np.concatenate([in_full, in_full])
+    assert 0 < plan.random_begin < half
+    P = mb - mb.mean(1, keepdims=True)
+    full = np.linalg.eigvalsh(P[in_full].T @ P[in_full])
+    rand = np.linalg.eigvalsh(P[~in_full].T @ P[~in_full])
+    if negative == "random":       # half the enumerated part at its largest eigenvalue
+        w_full, w_rand = 1.0, -0.5 * full[-1] / rand[-1]
+    else:                          # (rand[0] = 0: the vector of ones, which P takes out)
+        w_full, w_rand = -0.5 * rand[1] / full[-1], 1.0
+    plan.random_weight = w_rand
+    for c in classes:
+        c.weight = w_full if c.full else w_rand
+    v, f0, f1 = _game(M, mb, 11)
+    yv = v(mb).astype(np.float32)
+    fef = np.array([f0, f1], np.float32)
+    phi, info = _solve(dev, plan, classes, masks, torch.tensor(yv, device=dev), torch.tensor(fef, device=dev))
+    assert info == 0
+    _check_projected(phi, mb, np.where(in_full, w_full, w_rand), yv, fef)
