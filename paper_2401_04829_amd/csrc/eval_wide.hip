@@ -385,8 +385,9 @@ __global__ void __launch_bounds__(kBlockRows, 2) k_wide_l1(
     // constant input rows: (features x players) x (players x coalitions) on
     // fp32 MFMA 16x16x4, four players per step.  Lane (rl, g) gives player
     // sp + g's feature rl of each tile and its coefficient in coalition rl of
-    // each row tile (0 when the coalition does not hold it), so a coefficient
-    // is computed by one lane and not by four, and the multiply-adds run at
+    // each row tile (0 when the coalition does not hold it; lanes beyond the
+    // last player give 0 times 0, as 0 times its infinity would be no number),
+    // so a coefficient is computed by one lane and not by four, and the multiply-adds run at
     // twice the VALU rate.  With ~40 such players per node this loop took
     // longer than the contraction above.
     int e_n = sp0 < sp1 ? spec_e[min(sp0 + g, sp1 - 1)] : 0;
@@ -398,7 +399,7 @@ __global__ void __launch_bounds__(kBlockRows, 2) k_wide_l1(
       float zu[kTiles];
 #pragma unroll
       for (int ft = 0; ft < kTiles; ++ft)
-        zu[ft] = Zc[static_cast<int64_t>(u) * h + 16 * (ft0 + (ft < nt ? ft : nt - 1)) + rl];
+        zu[ft] = in ? Zc[static_cast<int64_t>(u) * h + 16 * (ft0 + (ft < nt ? ft : nt - 1)) + rl] : 0.f;
       const int nuu = PAIRS ? dst_ptr[u + 1] - dst_ptr[u] : 0;
       uint64_t mw[4];
       int du[4];

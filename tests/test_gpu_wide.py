@@ -369,3 +369,54 @@ def test_wide_three_layers_several_passes(dev):
     ms, _ = sampler.sample(sampler.plan(M, p), seed, 0)
     np.testing.assert_array_equal(masks_np(r.masks), sampler.pack(ms))
     _check_y(r.y.cpu().numpy(), ms, game, f0, f1, r.f_empty_full.cpu().numpy(), deg_v)
+
+
+@pytest.mark.parametrize("pairs", [False, True])
+def test_wide_infinite_row_of_a_neighbour(dev, pairs):
+    """A feature of +inf in the transformed row of an in-neighbour u of the
+    target, which is the last of one to five sources in H_1 of nodes 1 to 5:
+    a coalition that brings it into a node that the target sees has an infinite
+    value, however many sources go with it; one that holds no edge of u is finite."""
+    n, u, f = 400, 6, 5
+    rng = np.random.default_rng(21)
+    src, dst = list(range(1, 7)), [0] * 6
+    for x in range(1, 6):
+        others = [a for a in range(1, 6) if a != x][:x - 1]
+        out = rng.choice(np.arange(7, n), 40, replace=False).tolist()
+        src += others + [u] + out
+        dst += [x] * (len(others) + 1 + len(out))
+    indptr, indices = W.in_csr_from_pairs(n, np.array(src), np.array(dst))
+    Ws, bs = W.glorot_gcn([8, 64, 3], 4, bias="random")
+    ex = explainer_for(dict(indptr=indptr, indices=indices, X=W.gaussian_features(n, 8, 3), weights=Ws, biases=bs,
+                            hops=2))
+    ex.prepare()
+    ref = subgraph.extract(indptr, indices, 0, 2)
+    M, dp = ref["num_edges"], np.asarray(ref["dst_ptr"])
+    gid, esrc = np.asarray(ref["node_gid"]), np.asarray(ref["edge_src"])
+    ex.XW1[u, f] = float("inf")
+    half = 200
+    mb = rng.random((half, M)) < rng.uniform(0.2, 0.8, size=(half, 1))
+    mb = np.concatenate([mb, ~mb])
+    into = {}                                        # (source, destination) -> player
+    for d in range(len(dp) - 1):
+        for e in range(dp[d], dp[d + 1]):
+            into[int(gid[esrc[e]]), int(gid[d])] = e
+    reached = np.zeros(2 * half, bool)
+    for x in range(1, 6):
+        one = mb[:, into[u, x]] & mb[:, into[x, 0]] & ~mb[:, into[u, 0]]
+        assert one.sum() > 10
+        reached |= one
+    masks = torch.from_numpy(sampler.pack(mb).view(np.int64)).to(dev)
+    sub = ex.extract(0)
+    y = torch.empty(2 * half, device=dev)
+    fef = torch.empty(2, device=dev)
+    ws = torch.empty(L.gnnshap_eval_workspace(sub.sg, ex.model, 2 * half), dtype=torch.uint8, device=dev)
+    _say("wide infinite", pairs, M)
+    call = L.gnnshap_eval_sampled_coalitions if pairs else L.gnnshap_eval_coalitions
+    call(sub.sg, ex.model, _vp(ex.X), 0, _vp(masks), 2 * half, (M + 63) // 64, _vp(y), _vp(fef), None, _vp(ws),
+         ws.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    y = y.cpu().numpy()
+    assert np.isinf(y[reached]).all(), np.flatnonzero(reached & ~np.isinf(y))[:8]
+    calm = ~mb[:, [into[u, x] for x in range(6)]].any(axis=1)
+    assert np.isfinite(y[calm]).all()
