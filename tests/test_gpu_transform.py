@@ -61,6 +61,25 @@ def test_split_products_at_tile_edges(dev, n, d, h):
     assert worst <= 1.0
 
 
+@pytest.mark.parametrize("n,d,h", [(3000, 64, 64), (3000, 128, 128), (7000, 256, 256), (40000, 256, 128),
+                                   (40000, 602, 128)])
+def test_errors_of_split_products_have_no_direction(dev, n, d, h):
+    """Results of either sign: the mean error over all of them, in their rms.
+    The roundings (1e-7 each) leave 3e-10 over 192,000 and more; an odd number
+    of steps of 32 leaves what one step drops, a quarter of 2^-24 of its own
+    sum: 1.5e-8 / sqrt(19) at 602.  Steps that all drop the same way leave
+    7.9e-9 (two steps) to 2.7e-8 (nineteen)."""
+    print("mean error", n, d, h, flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n + d)
+    X = torch.randn((n, d), generator=g, device=dev)
+    W = torch.randn((d, h), generator=g, device=dev)
+    exact = X.double() @ W.double()
+    err = (_transform(X, W).double() - exact) / exact.pow(2).mean().sqrt()
+    assert float(err.pow(2).mean().sqrt()) <= 1.2e-7
+    assert abs(float(err.mean())) <= 4e-9, float(err.mean())
+
+
 @pytest.mark.parametrize("n,d,h", [(60000, 602, 128), (40000, 33, 48), (100000, 100, 64), (90000, 130, 100),
                                    (30000, 256, 256), (40000, 602, 41), (40000, 20, 64), (40000, 200, 32)])
 def test_rows_do_not_depend_on_their_number(dev, n, d, h):
