@@ -248,7 +248,7 @@ __global__ void __launch_bounds__(256) k_gemm(const float* __restrict__ A, int64
 // or results above 2^80, or that are not finite, give a non-finite sum; such
 // an output is computed again in fp32.
 //
-// One workgroup: 128 rows x 32 NT columns, four wavefronts of 64 x 16 NT; K in
+// One workgroup: 32 MT rows x 32 NT columns, four wavefronts of 16 MT x 16 NT; K in
 // steps of 32, split while they are staged in LDS in operand order (16-byte
 // reads in lane order; the rows of odd k groups are swapped by 8 so that the
 // staging writes of eight rows x eight k quads spread over the banks).  The
@@ -260,8 +260,20 @@ typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 typedef unsigned u4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u2_t __attribute__((ext_vector_type(2)));
 typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any float's address
-constexpr int kSplitRows = 128;
 constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;   // of an operand, of a product
+
+// Long sums are added in turns of kTurn steps, and the turns' sums in order: in
+// one chain, rows of many zeros had lost against k_transform, whose wavefronts
+// split K and which does not round where it adds nothing (2,708 x 1,433 x 128,
+// 1.3 % of the features not zero: 6.1e-8 off by k_transform, 7.9e-8 in one
+// chain, 6.4e-8 in turns; 10 %: 1.16e-7, 1.26e-7, 8.0e-8; dense 3.4e-7, 1.3e-7,
+// 8.3e-8).  The turns' registers are there for tiles of 64 columns; the wide tile
+// gives half its rows for them (100,000 x 1,433 x 128: 423 us instead of 378;
+// 232,965 x 602 x 128 would take 384 instead of 339), so more than 64 columns
+// take turns beyond 1,024 products.  (At 602, one chain: 8 to 11 % more error
+// than k_transform on the rows of zeros, 0.4 times as much on dense ones.)
+constexpr int kTurn = 8;
+bool split_turns(int64_t N, int64_t K) { return N <= 64 || K > 1024; }
 
 // The sign of a step's rows, and of its sum in the total.
 __device__ __forceinline__ float step_sign(int64_t step) { return step & 1 ? -1.f : 1.f; }
@@ -312,38 +324,39 @@ __device__ __forceinline__ void split8(const float (&x)[8], float scale, bf8_t (
                                                 bf16_pair(v[6], v[7])});
 }
 
-template <int NT>
+template <int NT, int MT, bool TURNS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict__ arow,
              const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc, int64_t m0, int64_t rows,
              int64_t N, int64_t K, const int32_t* dyn_count, int64_t dyn_off, int64_t dyn_cap, int64_t dyn_mult) {
+  constexpr int kRows = 32 * MT;                        // rows,
   constexpr int kCols = 32 * NT, kBT = 2 * NT;          // columns and column tiles of the workgroup
   constexpr int kPerB = 32 * kCols / 256;               // B values per thread and step: 8 or 16, consecutive k
-  __shared__ u4_t As[3][8 * 64], Bs[3][kBT * 64];       // [part][tile][lane]: 8 bf16 of one row (column)
+  __shared__ u4_t As[3][2 * MT * 64], Bs[3][kBT * 64];       // [part][tile][lane]: 8 bf16 of one row (column)
   if (dyn_count) {
     const int64_t r = rows_in_pass(dyn_count, dyn_off, dyn_cap) * dyn_mult;
     if (r < rows) rows = r;
   }
-  const int64_t mb = m0 + static_cast<int64_t>(blockIdx.x) * kSplitRows;
+  const int64_t mb = m0 + static_cast<int64_t>(blockIdx.x) * kRows;
   if (mb >= m0 + rows) return;
   const int64_t nb = static_cast<int64_t>(blockIdx.y) * kCols;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // A: thread (row tid / 8 + 32 i, k quad tid % 8); B: column tid % kCols, k from kPerB (tid / kCols)
   const int ak = (tid & 7) * 4;
-  const float* arp[4];
+  const float* arp[MT];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < MT; ++i) {
     const int64_t m = mb + tid / 8 + 32 * i;
     const int64_t c = m < m0 + rows ? m : m0 + rows - 1;   // rows beyond the last: its values, not stored
     arp[i] = A + (arow ? static_cast<int64_t>(arow[c]) : c) * lda;
   }
   const int bn = tid % kCols, bk = tid / kCols * kPerB;
   const float* bp = B + (nb + bn < N ? nb + bn : N - 1);
-  float ra[4][4], rb[kPerB];
+  float ra[MT][4], rb[kPerB];
   auto fetch = [&](int64_t k0) {
     const bool whole = k0 + 32 <= K;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < MT; ++i) {
       if (whole) {
         const f4u_t v = *reinterpret_cast<const f4u_t*>(arp[i] + k0 + ak);
         ra[i][0] = v.x;
@@ -364,7 +377,7 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
   auto stage = [&](float scale) {
     const int g = ak >> 3;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < MT; ++i) {
       const int row = tid / 8 + 32 * i;
       float v[4];
 #pragma unroll
@@ -385,39 +398,50 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
         Bs[p][at] = u4_t{bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]), bf16_pair(v[4], v[5]), bf16_pair(v[6], v[7])};
     }
   };
-  // wavefront (wave / 2, wave % 2): rows 64 (wave / 2) .., columns 16 NT (wave % 2) ..
-  const int wm = (wave >> 1) * 4, wn = (wave & 1) * NT, g = lane >> 4, r = lane & 15;
+  // wavefront (wave / 2, wave % 2): rows 16 MT (wave / 2) .., columns 16 NT (wave % 2) ..
+  const int wm = (wave >> 1) * MT, wn = (wave & 1) * NT, g = lane >> 4, r = lane & 15;
   const int la = g * 16 + (r ^ (8 * (g & 1)));
-  mx4_t acc[4][NT];
+  mx4_t acc[MT][NT], total[MT][NT];   // total: TURNS
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < MT; ++a)
 #pragma unroll
-    for (int b = 0; b < NT; ++b) acc[a][b] = mx4_t{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < NT; ++b) total[a][b] = acc[a][b] = mx4_t{0.f, 0.f, 0.f, 0.f};
+  auto end_turn = [&]() {
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int b = 0; b < NT; ++b) {
+        total[a][b] += acc[a][b];
+        acc[a][b] = mx4_t{0.f, 0.f, 0.f, 0.f};
+      }
+  };
   fetch(0);
   for (int64_t k0 = 0; k0 < K; k0 += 32) {
+    if (TURNS && k0 > 0 && k0 % (32 * kTurn) == 0) end_turn();
     const float sign = step_sign(k0 / 32);
     stage(sign * kSplitScale);
     __syncthreads();
     if (k0 + 32 < K) fetch(k0 + 32);
-    bf8_t av[3][4];
+    bf8_t av[3][MT];
 #pragma unroll
     for (int p = 0; p < 3; ++p)
 #pragma unroll
-      for (int a = 0; a < 4; ++a) av[p][a] = __builtin_bit_cast(bf8_t, As[p][(wm + a) * 64 + la]);
+      for (int a = 0; a < MT; ++a) av[p][a] = __builtin_bit_cast(bf8_t, As[p][(wm + a) * 64 + la]);
 #pragma unroll
     for (int b = 0; b < NT; ++b) {
       bf8_t bv[3];
 #pragma unroll
       for (int p = 0; p < 3; ++p) bv[p] = __builtin_bit_cast(bf8_t, Bs[p][(wn + b) * 64 + lane]);
-      mx4_t sum[4];
-      split_step<4>(av, bv, sum);
+      mx4_t sum[MT];
+      split_step<MT>(av, bv, sum);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) acc[a][b] += sign * sum[a];
+      for (int a = 0; a < MT; ++a) acc[a][b] += sign * sum[a];
     }
     __syncthreads();
   }
+  if (TURNS) end_turn();
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < MT; ++a)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int64_t m = mb + 16 * (wm + a) + 4 * g + q;
@@ -426,7 +450,8 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
       for (int b = 0; b < NT; ++b) {
         const int64_t n = nb + 16 * (wn + b) + r;
         if (n >= N) continue;
-        C[m * ldc + n] = split_output(acc[a][b][q], A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda, B + n, ldb, K);
+        C[m * ldc + n] = split_output((TURNS ? total : acc)[a][b][q],
+                                      A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda, B + n, ldb, K);
       }
     }
 }
@@ -434,18 +459,19 @@ k_gemm_split(const float* __restrict__ A, int64_t lda, const int32_t* __restrict
 // The same sums, and so the same bits, for few rows: 16 x 64 outputs per
 // workgroup, its eight wavefronts taking the steps of 32 k in turn, straight
 // from memory (no staging, no barrier before the products); their sums go
-// through LDS and are added in step order, wavefront w < 4 adding tile w.
+// through LDS and are added in step order (turns: kTurn of them at a time),
+// wavefront w < 4 adding tile w.
 // Bound by the latency of a wavefront's first loads while the grid is small,
 // then by the splitting (VALU, again for every 16 rows).  300 x 602 x 128:
 // 8 us, 10,000 rows: 27 us (k_transform 16 and 52, k_gemm 36 and 48; sixteen
 // wavefronts 8 and 34).
-constexpr int kShortWaves = 8;
+constexpr int kShortWaves = kTurn;
 
 __global__ void __launch_bounds__(kShortWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
 k_gemm_split_short(const float* __restrict__ A, int64_t lda, const int32_t* __restrict__ arow,
                    const float* __restrict__ B, int64_t ldb, float* __restrict__ C, int64_t ldc, int64_t m0,
                    int64_t rows, int64_t N, int64_t K, const int32_t* dyn_count, int64_t dyn_off, int64_t dyn_cap,
-                   int64_t dyn_mult) {
+                   int64_t dyn_mult, bool turns) {
   __shared__ mx4_t part[kShortWaves][4 * 64];
   if (dyn_count) {
     const int64_t r = rows_in_pass(dyn_count, dyn_off, dyn_cap) * dyn_mult;
@@ -492,7 +518,7 @@ k_gemm_split_short(const float* __restrict__ A, int64_t lda, const int32_t* __re
       }
     }
   };
-  mx4_t acc = {0.f, 0.f, 0.f, 0.f};
+  mx4_t acc = {0.f, 0.f, 0.f, 0.f}, total = acc;
   if (wave < steps) fetch(wave);
   for (int s0 = 0; s0 < steps; s0 += kShortWaves) {
     if (s0 + wave < steps) {
@@ -514,6 +540,10 @@ k_gemm_split_short(const float* __restrict__ A, int64_t lda, const int32_t* __re
 #pragma unroll
       for (int w = 0; w < kShortWaves; ++w)
         if (s0 + w < steps) acc += step_sign(w) * part[w][wave * 64 + lane];
+      if (turns || s0 + kShortWaves >= steps) {
+        total += acc;
+        acc = mx4_t{0.f, 0.f, 0.f, 0.f};
+      }
     }
     if (s0 + kShortWaves < steps) __syncthreads();
   }
@@ -523,7 +553,7 @@ k_gemm_split_short(const float* __restrict__ A, int64_t lda, const int32_t* __re
   for (int q = 0; q < 4; ++q) {
     const int64_t m = mb + 4 * g + q;
     if (m < m0 + rows)
-      C[m * ldc + n] = split_output(acc[q], A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda, B + n, ldb, K);
+      C[m * ldc + n] = split_output(total[q], A + (arow ? static_cast<int64_t>(arow[m]) : m) * lda, B + n, ldb, K);
   }
 }
 
@@ -550,16 +580,19 @@ int launch_split(hipStream_t s, const float* A, int64_t lda, const int32_t* arow
   // 64 wide 56, 128 wide 68 us; 28,000, 438: 65, 57, 68; 40,000, 626: 91, 100,
   // 77; 70,000 x 602 x 48, 547: 81, 99; 100,000, 782: 112, 118; 28,000 x 60 x
   // 128, 438: 21, 13, 16.
-  const int64_t tr = gnnshap::ceil_div(rows, kSplitRows), tiles = tr * gnnshap::ceil_div(N, 64);
+  const int64_t tiles = gnnshap::ceil_div(rows, 128) * gnnshap::ceil_div(N, 64);
+  const bool turns = split_turns(N, K);
   if (tiles < (K <= 64 ? 160 : N <= 64 ? 768 : 384)) {
     const dim3 g(static_cast<unsigned>(gnnshap::ceil_div(rows, 16)), static_cast<unsigned>(gnnshap::ceil_div(N, 64)));
     k_gemm_split_short<<<g, kShortWaves * 64, 0, s>>>(A, lda, arow, B, ldb, C, ldc, m0, rows, N, K, dyn, dyn_off,
-                                                      dyn_cap, dyn_mult);
+                                                      dyn_cap, dyn_mult, turns);
   } else {
-    const int nt = N <= 64 || tiles <= 512 ? 2 : 4;
-    const dim3 g(static_cast<unsigned>(tr), static_cast<unsigned>(gnnshap::ceil_div(N, 32 * nt)));
-    (nt == 4 ? k_gemm_split<4> : k_gemm_split<2>)<<<g, 256, 0, s>>>(A, lda, arow, B, ldb, C, ldc, m0, rows, N, K, dyn,
-                                                                   dyn_off, dyn_cap, dyn_mult);
+    const bool wide = N > 64 && tiles > 512;
+    const dim3 g(static_cast<unsigned>(gnnshap::ceil_div(rows, wide && turns ? 64 : 128)),
+                 static_cast<unsigned>(gnnshap::ceil_div(N, wide ? 128 : 64)));
+    (wide ? (turns ? k_gemm_split<4, 2, true> : k_gemm_split<4, 4, false>)
+          : (turns ? k_gemm_split<2, 4, true> : k_gemm_split<2, 4, false>))<<<g, 256, 0, s>>>(
+        A, lda, arow, B, ldb, C, ldc, m0, rows, N, K, dyn, dyn_off, dyn_cap, dyn_mult);
   }
   GS_LAUNCHED();
   return GNNSHAP_OK;

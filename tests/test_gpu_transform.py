@@ -80,6 +80,46 @@ def test_errors_of_split_products_have_no_direction(dev, n, d, h):
     assert abs(float(err.mean())) <= 4e-9, float(err.mean())
 
 
+@pytest.mark.parametrize("n,d,h", [(301, 1025, 128), (17, 1300, 66), (25000, 1030, 100), (33000, 1100, 128),
+                                   (33025, 1027, 66), (98177, 300, 64), (301, 600, 64)])
+def test_split_products_in_turns(dev, n, d, h):
+    """Sums of several turns of eight steps, in every form: against float64, and
+    rows alone against the same rows among all."""
+    print("turns", n, d, h, flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n + d)
+    X = torch.randn((n, d), generator=g, device=dev)
+    W = torch.randn((d, h), generator=g, device=dev)
+    Z = _transform(X, W)
+    exact = X.double() @ W.double()
+    bound = (d + 4) * 2.0 ** -24 * (X.double().abs() @ W.double().abs())
+    assert float(((Z.double() - exact).abs() / bound).max()) <= 1.0
+    for i, k in ((0, 1), (n // 2, 17 if n > 40 else 3), (n - 16, 16)):
+        assert torch.equal(_transform(X[i:i + k].contiguous(), W).view(torch.int32), Z[i:i + k].view(torch.int32))
+
+
+@pytest.mark.parametrize("d,h,share,bound", [(1433, 128, 0.013, 7.2e-8), (1433, 128, 0.1, 1.0e-7),
+                                             (1433, 64, 0.013, 7.2e-8), (500, 64, 0.1, 7.6e-8),
+                                             (602, 128, 1.0, 1.0e-7)])
+def test_rounding_of_sparse_rows(dev, d, h, share, bound):
+    """Rows of which a share is not zero (ones, or log-normal values where there
+    are more): rms error in rms of the results.  Bounds: halfway between the
+    steps in turns (6.4e-8, 8.0e-8, 6.4e-8, 7.0e-8) and in one chain (7.9e-8,
+    1.26e-7, 7.9e-8, 8.3e-8); dense rows, one chain: 9.2e-8."""
+    print("sparse rows", d, h, share, flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(d + h)
+    n = 2708
+    X = torch.ones((n, d), device=dev) if share < 0.05 else torch.randn((n, d), generator=g, device=dev)
+    if 0.05 < share < 1.0:
+        X = torch.exp(X)
+    X = X * (torch.rand((n, d), generator=g, device=dev) < share)
+    W = (torch.rand((d, h), generator=g, device=dev) * 2 - 1) * (6 / (d + h)) ** 0.5
+    exact = X.double() @ W.double()
+    err = (_transform(X, W).double() - exact).pow(2).mean().sqrt() / exact.pow(2).mean().sqrt()
+    assert float(err) <= bound, float(err)
+
+
 @pytest.mark.parametrize("n,d,h", [(60000, 602, 128), (40000, 33, 48), (100000, 100, 64), (90000, 130, 100),
                                    (30000, 256, 256), (40000, 602, 41), (40000, 20, 64), (40000, 200, 32)])
 def test_rows_do_not_depend_on_their_number(dev, n, d, h):
